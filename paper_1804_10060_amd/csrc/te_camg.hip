@@ -366,7 +366,8 @@ __global__ void __launch_bounds__(64) k_hgs8(int64_t n, int B, const int64_t *__
     int *pb = reinterpret_cast<int *>(xs + 8 * (B + 1)) + g * (B + 1);
     const int64_t e0 = nb > 0 ? pin[b0] : 0;
     for (int r = l; r < nb; r += 8) xb[r] = x_in ? x_in[b0 + r] : 0.0;
-    for (int r = l; r <= nb; r += 8) pb[r] = (int)(pin[b0 + r] - e0);
+    // a group past the last block (nb = 0) reads nothing: b0 may lie beyond pin
+    for (int r = l; r <= nb; r += 8) pb[r] = nb > 0 ? (int)(pin[b0 + r] - e0) : 0;
     __syncthreads();
     // a slot holds the raw loads of one row and the mask of its present
     // entries; nothing is computed from the loaded values until the row runs
