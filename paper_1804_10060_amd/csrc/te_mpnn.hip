@@ -17,13 +17,17 @@
 // (weights [in][out]), so the three directional weights of a layer form one
 // [192][64] matrix against the [N][192] sums.
 //
-// Vertex kernels run one wave per vertex with the 64 channels on the lanes
-// (the neighbour gather is then a coalesced 256-byte row read; a vertex's
-// channel values reach every lane by readlane); weight gradients X^T Y are
-// blocked reductions over vertices with per-block partial tiles summed in a
-// fixed order (deterministic, no atomics).  The graph is symmetric, so the
-// adjoints of the neighbour mean and of the directional sums are gathers
-// too: d h_u = sum_{v in N(u)} (d m_v / deg_v + sum_k w^k_vu d d_k[v]).
+// The dense products run on the float32 matrix cores: a layer forward and
+// backward is one [N][320] x [320][64] product whose rows are gathered into
+// LDS by the workgroup that multiplies them (k_mp_layer), its weight gradient
+// one [320][N] x [N][64] product (k_wgrad).  The graph is symmetric, so the
+// adjoints of the neighbour mean and of the directional sums are gathers too:
+//   dL/dh_u gains (sum_{v in N(u)} ga_v / deg_v) W_n^T
+//                 + sum_k (sum_{v in N(u)} w^k_vu ga_v) W_dk^T.
+// Sums over the vertices (means, bias and weight gradients, loss) are
+// per-workgroup partials added in a fixed order in double: deterministic, no
+// atomics.  On 334,368 vertices a training step (forward, backward, Adam) went
+// from 22.8 to 4.9 ms.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -44,22 +48,35 @@ constexpr int64_t NPARAM = OFF_BOUT + MO;
 constexpr float S_T = 500.f, S_F = 2.0e9f, S_X = 0.5f;
 constexpr double S_U = 1.0e-3;
 constexpr int MB = 256, MW = MB / 64;
-constexpr int VB = 4;   // vertices per wave step of the dense layer transforms
+constexpr int MK = 5 * MH;        // concatenated layer input: own row, neighbour mean, three directional sums
+constexpr int LROW = MK + 4;      // its LDS row, padded so that 16 rows read 16 bytes each without bank conflicts
 constexpr int RED_BLOCKS = 512;
+constexpr int LAYER_BLOCKS = 768; // workgroups of a layer: the three a CU holds at once (LDS), on 256 CUs
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __host__ __device__ constexpr int64_t off_ws(int l) { return LAYER0 + l * LAYER_SZ; }
 __host__ __device__ constexpr int64_t off_wn(int l) { return LAYER0 + l * LAYER_SZ + MH * MH; }
 __host__ __device__ constexpr int64_t off_wg(int l) { return LAYER0 + l * LAYER_SZ + 2 * MH * MH; }
 __host__ __device__ constexpr int64_t off_wd(int l) { return LAYER0 + l * LAYER_SZ + 3 * MH * MH; }
 __host__ __device__ constexpr int64_t off_b(int l) { return LAYER0 + l * LAYER_SZ + 6 * MH * MH; }
+// weight matrix of slab p of the concatenated layer input
+__host__ __device__ constexpr int64_t off_slab(int l, int p) {
+    return p == 0 ? off_ws(l) : (p == 1 ? off_wn(l) : off_wd(l) + (p - 2) * MH * MH);
+}
 
 __device__ __forceinline__ float lane_val(float v, int k) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
 }
 
-static inline unsigned vgrid(int64_t n) {
-    int64_t g = (n + MW - 1) / MW;
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, 65536));
+// The block's double per channel and wave (one value per lane group of 16,
+// channel 16 w + lane % 16) into part[blockIdx][64]: the four lanes of a
+// channel added in a fixed order.
+__device__ __forceinline__ void store_colsum(double cs, double *__restrict__ part) {
+    cs += __shfl_xor(cs, 16, 64);
+    cs += __shfl_xor(cs, 32, 64);
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    if (lane < 16) part[blockIdx.x * (int64_t)MH + 16 * w + lane] = cs;
 }
 
 // ---------------------------------------------------------------------------
@@ -79,160 +96,307 @@ __global__ void k_features(int64_t n, const double *__restrict__ xc, const doubl
     }
 }
 
-// h0 = relu(X W_in + b_in): one wave per vertex, lane = channel
+// h0 = relu(X W_in + b_in), one wave per vertex, lane = channel; the block's
+// column sums of h0 for the first layer's mean over the vertices; and the
+// handle's copies of X and the mask, which the backward pass reads.
 __global__ void __launch_bounds__(MB) k_in(int64_t n, const float *__restrict__ P, const float *__restrict__ X,
-                                           float *__restrict__ h0) {
-    const int c = threadIdx.x & 63;
-    for (int64_t v = blockIdx.x * (int64_t)MW + threadIdx.x / 64; v < n; v += (int64_t)gridDim.x * MW) {
-        float a = P[OFF_BIN + c];
-        for (int k = 0; k < MF; ++k) a += X[v * MF + k] * P[OFF_WIN + k * MH + c];
-        h0[v * MH + c] = a > 0.f ? a : 0.f;
-    }
-}
-
-// column sums of an [n][64] array: partials[block][64]
-__global__ void __launch_bounds__(MB) k_colsum(int64_t n, const float *__restrict__ H, double *__restrict__ part) {
+                                           const uint8_t *__restrict__ mask, float *__restrict__ Xc,
+                                           uint8_t *__restrict__ maskc, float *__restrict__ h0,
+                                           double *__restrict__ part) {
     __shared__ double lds[MB];
     const int c = threadIdx.x & 63, w = threadIdx.x / 64;
-    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double t = 0.0;
-    for (int64_t v = lo + w; v < hi; v += MW) t += H[v * MH + c];
-    lds[threadIdx.x] = t;
+    float win[MF];
+#pragma unroll
+    for (int k = 0; k < MF; ++k) win[k] = P[OFF_WIN + k * MH + c];
+    const float b = P[OFF_BIN + c];
+    double cs = 0.0;
+    for (int64_t v = blockIdx.x * (int64_t)MW + w; v < n; v += (int64_t)gridDim.x * MW) {
+        const float xv = c < MF ? X[v * MF + c] : 0.f;
+        if (c < MF) Xc[v * MF + c] = xv;
+        if (c < 3) maskc[v * 3 + c] = mask[v * 3 + c];
+        float a = b;
+#pragma unroll
+        for (int k = 0; k < MF; ++k) a += lane_val(xv, k) * win[k];
+        a = a > 0.f ? a : 0.f;
+        h0[v * MH + c] = a;
+        cs += a;
+    }
+    lds[threadIdx.x] = cs;
     __syncthreads();
     if (threadIdx.x < 64) {
-        double s = 0.0;
-        for (int k = 0; k < MW; ++k) s += lds[k * 64 + threadIdx.x];
-        part[blockIdx.x * 64 + threadIdx.x] = s;
+        double t = 0.0;
+        for (int k = 0; k < MW; ++k) t += lds[k * 64 + threadIdx.x];
+        part[blockIdx.x * (int64_t)MH + threadIdx.x] = t;
     }
 }
 
-// g = colsum/n (from partials), gw = g W_g + b (forward) ; one block of 64
-__global__ void k_global(int nparts, const double *__restrict__ part, int64_t n, const float *__restrict__ P, int l,
-                         float *__restrict__ g, float *__restrict__ gw) {
-    __shared__ float gs[64];
-    const int c = threadIdx.x;
+// Sums of the [nparts][64] partials per channel: 16 lane groups take every
+// 16th part, their sums are added in order.  Valid in threads 0..63.
+constexpr int SB = 1024;
+__device__ __forceinline__ double sum_parts64(int nparts, const double *__restrict__ part, double *lds) {
+    const int c = threadIdx.x & 63, y = threadIdx.x / 64;
     double s = 0.0;
-    for (int b = 0; b < nparts; ++b) s += part[b * 64 + c];
-    gs[c] = float(s / double(n));
-    g[c] = gs[c];
-    __syncthreads();
-    float a = P[off_b(l) + c];
-    for (int k = 0; k < MH; ++k) a += gs[k] * P[off_wg(l) + k * MH + c];
-    gw[c] = a;
-}
-
-// one message-passing layer: m = mean of neighbours, d = directional sums,
-// a = h W_s + m W_n + d W_d + gw, h' = h + relu(a); stores m, d and a for the
-// backward pass.  W_s, W_n, W_dx and W_dy sit in LDS (64 KB), W_dz is read
-// through the cache; a wave takes VB vertices at a time, each weight value
-// serving all of them.
-__global__ void __launch_bounds__(MB) k_mp_fwd(int64_t n, const int64_t *__restrict__ gp, const int32_t *__restrict__ gi,
-                                               const float *__restrict__ xf, const float *__restrict__ invdl,
-                                               const float *__restrict__ P, int l, const float *__restrict__ gw,
-                                               const float *__restrict__ h, float *__restrict__ m,
-                                               float *__restrict__ d, float *__restrict__ a, float *__restrict__ hn) {
-    extern __shared__ float W[];   // [4][64][64]: W_s, W_n, W_dx, W_dy
-    for (int t = threadIdx.x; t < MH * MH; t += MB) {
-        W[t] = P[off_ws(l) + t];
-        W[MH * MH + t] = P[off_wn(l) + t];
-    }
-    for (int t = threadIdx.x; t < 2 * MH * MH; t += MB) W[2 * MH * MH + t] = P[off_wd(l) + t];
-    __syncthreads();
-    const float *__restrict__ Wz = P + off_wd(l) + 2 * MH * MH;
-    const int c = threadIdx.x & 63;
-    const float gwc = gw[c];
-    const int64_t step = (int64_t)gridDim.x * MW * VB;
-    for (int64_t v0 = (blockIdx.x * (int64_t)MW + threadIdx.x / 64) * VB; v0 < n; v0 += step) {
-        float hv[VB], mv[VB], d0[VB], d1[VB], d2[VB], acc[VB];
-#pragma unroll
-        for (int i = 0; i < VB; ++i) {
-            const int64_t v = v0 + i;
-            hv[i] = mv[i] = d0[i] = d1[i] = d2[i] = 0.f;
-            acc[i] = gwc;
-            if (v >= n) continue;
-            const int64_t lo = gp[v], hi = gp[v + 1];
-            const float xv0 = xf[v * 3], xv1 = xf[v * 3 + 1], xv2 = xf[v * 3 + 2], iv = invdl[v];
-            float s = 0.f;
-            for (int64_t e = lo; e < hi; ++e) {
-                const int64_t u = gi[e];
-                const float hu = h[u * MH + c];
-                s += hu;
-                d0[i] += (xf[u * 3] - xv0) * iv * hu;
-                d1[i] += (xf[u * 3 + 1] - xv1) * iv * hu;
-                d2[i] += (xf[u * 3 + 2] - xv2) * iv * hu;
-            }
-            mv[i] = hi > lo ? s / float(hi - lo) : 0.f;
-            hv[i] = h[v * MH + c];
-        }
 #pragma unroll 4
-        for (int k = 0; k < MH; ++k) {
-            const float ws = W[k * MH + c], wn = W[MH * MH + k * MH + c], wx = W[2 * MH * MH + k * MH + c],
-                        wy = W[3 * MH * MH + k * MH + c], wz = Wz[k * MH + c];
+    for (int b = y; b < nparts; b += SB / 64) s += part[(int64_t)b * MH + c];
+    lds[threadIdx.x] = s;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x < 64)
 #pragma unroll
-            for (int i = 0; i < VB; ++i) {
-                acc[i] += lane_val(hv[i], k) * ws;
-                acc[i] += lane_val(mv[i], k) * wn;
-                acc[i] += lane_val(d0[i], k) * wx;
-                acc[i] += lane_val(d1[i], k) * wy;
-                acc[i] += lane_val(d2[i], k) * wz;
+        for (int k = 0; k < SB / 64; ++k) t += lds[k * 64 + threadIdx.x];
+    return t;
+}
+
+// out[c] = sum_k v[k] M(k, c) over 64 k, the 16 lane groups taking 4 k each;
+// M row-major [k][c], or its transpose.  Valid in threads 0..63; v in LDS.
+template <bool TRANS>
+__device__ __forceinline__ float vec_mat64(const float *v, const float *__restrict__ M, float *lds) {
+    const int c = threadIdx.x & 63, y = threadIdx.x / 64;
+    float t = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int k = 4 * y + q;
+        t += v[k] * (TRANS ? M[c * MH + k] : M[k * MH + c]);
+    }
+    lds[threadIdx.x] = t;
+    __syncthreads();
+    float o = 0.f;
+    if (threadIdx.x < 64)
+#pragma unroll
+        for (int k = 0; k < SB / 64; ++k) o += lds[k * 64 + threadIdx.x];
+    return o;
+}
+
+// g = colsum/n (from partials), gw = g W_g + b (forward); one workgroup
+__global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restrict__ part, int64_t n,
+                                               const float *__restrict__ P, int l, float *__restrict__ g,
+                                               float *__restrict__ gw) {
+    __shared__ double lds[SB];
+    __shared__ float gs[64], ldf[SB];
+    const int c = threadIdx.x;
+    const double s = sum_parts64(nparts, part, lds);
+    if (c < 64) {
+        gs[c] = float(s / double(n));
+        g[c] = gs[c];
+    }
+    __syncthreads();
+    const float a = vec_mat64<false>(gs, P + off_wg(l), ldf);
+    if (c < 64) gw[c] = P[off_b(l) + c] + a;
+}
+
+// One message-passing layer, forward or backward.  Both are one product of
+// the concatenated rows [s | m | d_x | d_y | d_z] (320 wide) with the layer's
+// five 64 x 64 matrices:
+//   forward   s = h, m = mean of the neighbours' h, d_k = sum_u w^k_vu h_u;
+//             a = [..] W + gw,  h' = h + relu(a); m, d and a are kept for the
+//             backward pass
+//   backward  s = ga, m = sum_u ga_u / deg_u, d_k = sum_u w^k_uv ga_u: the
+//             adjoint gathers commute with the transposed matrices, so only
+//             the 64 channels of ga are gathered, not the 256 of their images;
+//             gh' = gh + [..] W^T + gg / n, then ga' = gh' where the gate of
+//             the layer below is open
+// A workgroup takes tiles of 16 MT vertices (contiguous, in XCD order: the
+// gathered rows of a tile stay in one L2).  Each wave gathers 4 MT of them
+// with its 64 lanes on the channels: the wave's neighbour entries are one
+// list, each lane looks up one entry's vertex and weights, the rows of eight
+// entries are loaded together.  The rows meet in LDS, and each wave multiplies
+// them by its 16 output channels' weights, which stay in 80 registers for
+// all tiles (v_mfma_f32_16x16x4: lane (q, i) holds channels 16 kb + 4 q + s of
+// row i, so one 16-byte LDS read feeds four instructions).
+// Bound: 2 * 320 * 64 flop per vertex (0.09 ms on 334,368 vertices at the
+// float32 matrix rate) and about 1.5 KB of rows per vertex (0.10 ms); what is
+// left is the latency of the gather's dependent loads.  334,368 vertices, per
+// layer: forward 1.72 -> 0.43 ms, backward (two kernels) 1.62 -> 0.44 ms, with
+// one wave per vertex and vector FMAs before; 4,624 vertices: 45 -> 14 us.
+template <int MT, bool BWD>
+__global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, const int64_t *__restrict__ gp,
+                                                    const int32_t *__restrict__ gi, const float *__restrict__ xf,
+                                                    const float *__restrict__ invdl, const float *__restrict__ P, int l,
+                                                    const float *__restrict__ gvec, const float *__restrict__ src,
+                                                    float *__restrict__ mout, float *__restrict__ dout,
+                                                    float *__restrict__ aout, const float *__restrict__ gate,
+                                                    float *__restrict__ hout, float *__restrict__ gout,
+                                                    double *__restrict__ part) {
+    constexpr int VT = 16 * MT, VW = VT / MW, EU = 8;
+    __shared__ float T[VT][LROW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    const int i16 = lane & 15, q = lane >> 4, col = 16 * w + i16;
+    float wr[MK / 4];
+#pragma unroll
+    for (int kb = 0; kb < MK / 16; ++kb) {
+        const float *M = P + off_slab(l, kb / 4);
+        const int k0 = (kb % 4) * 16 + 4 * q;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wr[kb * 4 + t] = BWD ? M[col * MH + k0 + t] : M[(k0 + t) * MH + col];
+    }
+    const float gv = BWD ? gvec[col] / float(n) : gvec[col];
+    double cs = 0.0;
+    const int64_t nb = gridDim.x, x = blockIdx.x & 7, xi = blockIdx.x >> 3;
+    const int64_t lb = x * (nb >> 3) + (x < (nb & 7) ? x : (nb & 7)) + xi;   // workgroups of one XCD adjacent
+    const int64_t t_lo = ntiles * lb / nb, t_hi = ntiles * (lb + 1) / nb;
+    for (int64_t tile = t_lo; tile < t_hi; ++tile) {
+        const int64_t v0 = tile * VT + w * VW;
+        const int r0 = w * VW;
+        const int nv = (int)(v0 < n ? (n - v0 < VW ? n - v0 : VW) : 0);   // the wave's vertices inside the mesh
+        for (int i = 0; i < VW; ++i) T[r0 + i][lane] = i < nv ? src[(v0 + i) * MH + lane] : 0.f;
+        const int64_t e0 = nv > 0 ? gp[v0] : 0;
+        // lane i: end of vertex i's entries in the wave's list
+        int pe = 0;
+        if (nv > 0) pe = (int)(gp[v0 + (lane + 1 < nv ? lane + 1 : nv)] - e0);
+        const int tot = __builtin_amdgcn_readlane(pe, VW - 1);
+        int cur = 0, beg = 0, end = __builtin_amdgcn_readlane(pe, 0);
+        float s = 0.f, d0 = 0.f, d1 = 0.f, d2 = 0.f;
+        auto flush = [&]() {
+            const float m = BWD ? s : (end > beg ? s / float(end - beg) : 0.f);
+            float *row = T[r0 + cur];
+            row[MH + lane] = m;
+            row[2 * MH + lane] = d0;
+            row[3 * MH + lane] = d1;
+            row[4 * MH + lane] = d2;
+            if (!BWD && cur < nv) {
+                const int64_t v = v0 + cur;
+                mout[v * MH + lane] = m;
+                dout[v * MD + lane] = d0;
+                dout[v * MD + MH + lane] = d1;
+                dout[v * MD + 2 * MH + lane] = d2;
+            }
+            s = d0 = d1 = d2 = 0.f;
+            ++cur;
+            beg = end;
+            end = cur < VW ? __builtin_amdgcn_readlane(pe, cur) : tot;
+        };
+        for (int c0 = 0; c0 < tot; c0 += 64) {
+            const int e = c0 + lane, cnt = tot - c0 < 64 ? tot - c0 : 64;
+            int u = 0;
+            float w0 = 0.f, w1 = 0.f, w2 = 0.f, wm = 1.f;
+            int vi = 0;   // the vertex an entry belongs to
+#pragma unroll
+            for (int i = 0; i + 1 < VW; ++i) vi += e >= __builtin_amdgcn_readlane(pe, i) ? 1 : 0;
+            if (e < tot) {
+                u = gi[e0 + e];
+                const int64_t v = v0 + vi;
+                const float *xu = xf + (int64_t)u * 3, *xv = xf + v * 3;
+                if (BWD) {
+                    const float iu = invdl[u];
+                    w0 = (xv[0] - xu[0]) * iu;
+                    w1 = (xv[1] - xu[1]) * iu;
+                    w2 = (xv[2] - xu[2]) * iu;
+                    const int64_t du = gp[u + 1] - gp[u];
+                    wm = du > 0 ? 1.f / float(du) : 0.f;
+                } else {
+                    const float iv = invdl[v];
+                    w0 = (xu[0] - xv[0]) * iv;
+                    w1 = (xu[1] - xv[1]) * iv;
+                    w2 = (xu[2] - xv[2]) * iv;
+                }
+            }
+            for (int b = 0; b < cnt; b += EU) {
+                float hr[EU];
+#pragma unroll
+                for (int t = 0; t < EU; ++t) {
+                    const int k = b + t < cnt ? b + t : cnt - 1;
+                    hr[t] = src[(int64_t)__builtin_amdgcn_readlane(u, k) * MH + lane];
+                }
+#pragma unroll
+                for (int t = 0; t < EU; ++t) {
+                    if (b + t >= cnt) break;
+                    while (c0 + b + t >= end) flush();
+                    if (BWD) s += lane_val(wm, b + t) * hr[t];
+                    else s += hr[t];
+                    d0 += lane_val(w0, b + t) * hr[t];
+                    d1 += lane_val(w1, b + t) * hr[t];
+                    d2 += lane_val(w2, b + t) * hr[t];
+                }
             }
         }
+        while (cur < VW) flush();
+        __syncthreads();
+        f32x4 acc[MT];
 #pragma unroll
-        for (int i = 0; i < VB; ++i) {
-            const int64_t v = v0 + i;
-            if (v >= n) break;
-            m[v * MH + c] = mv[i];
-            d[v * MD + c] = d0[i];
-            d[v * MD + MH + c] = d1[i];
-            d[v * MD + 2 * MH + c] = d2[i];
-            a[v * MH + c] = acc[i];
-            hn[v * MH + c] = hv[i] + (acc[i] > 0.f ? acc[i] : 0.f);
-        }
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][r] = gv;
+#pragma unroll
+        for (int kb = 0; kb < MK / 16; ++kb)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(&T[16 * m + i16][16 * kb + 4 * q]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], wr[kb * 4 + t], acc[m], 0, 0, 0);
+            }
+        // lane (q, i) holds rows 4 q + r of channel col
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * m + 4 * q + r;
+                const int64_t v = tile * VT + row;
+                if (v >= n) continue;
+                const int64_t o = v * MH + col;
+                const float av = acc[m][r];
+                if (BWD) {
+                    const float gh = hout[o] + av;
+                    const float ga = gate[o] > 0.f ? gh : 0.f;
+                    hout[o] = gh;
+                    gout[o] = ga;
+                    cs += ga;
+                } else {
+                    const float hv = T[row][col] + (av > 0.f ? av : 0.f);
+                    aout[o] = av;
+                    hout[o] = hv;
+                    cs += hv;
+                }
+            }
+        __syncthreads();   // the next tile overwrites T
+    }
+    store_colsum(cs, part);
+}
+
+// The output layer's rows: four lanes per vertex, lane j of them the 16
+// channels 16 i + 4 j + r.  hv[4 i + r] and the three weights of each.
+constexpr int OV = MB / 4;   // vertices per workgroup step
+__device__ __forceinline__ void out_weights(const float *__restrict__ P, int j, float (&wo)[16][MO]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < MO; ++c) wo[4 * i + r][c] = P[OFF_WOUT + (16 * i + 4 * j + r) * MO + c];
+}
+__device__ __forceinline__ void load_row16(const float *__restrict__ h, int64_t v, int j, float (&hv)[16]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const f32x4 t = *reinterpret_cast<const f32x4 *>(h + v * MH + 16 * i + 4 * j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) hv[4 * i + r] = t[r];
     }
 }
 
-// y = (h W_out + b_out) * keep ; if target: loss and gy = 2 (y - t)/(3n) * keep,
-// gh = gy W_out^T ; per-block partial loss
+// y = (h W_out + b_out) * keep, into the handle's copy and, if given, the caller's
 __global__ void __launch_bounds__(MB) k_out(int64_t n, const float *__restrict__ P, const float *__restrict__ h,
                                             const uint8_t *__restrict__ mask, float *__restrict__ y,
-                                            const float *__restrict__ target, float *__restrict__ gy,
-                                            float *__restrict__ gh, double *__restrict__ lpart) {
-    __shared__ double lds[MW];
-    const int c = threadIdx.x & 63, w = threadIdx.x / 64;
-    double lsum = 0.0;
-    const float inv = 2.f / float(3 * n);
-    for (int64_t v = blockIdx.x * (int64_t)MW + w; v < n; v += (int64_t)gridDim.x * MW) {
-        const float hv = h[v * MH + c];
-        float yv[MO];
-        for (int j = 0; j < MO; ++j) {
-            float t = hv * P[OFF_WOUT + c * MO + j];
-            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-            const float keep = mask[v * 3 + j] ? 0.f : 1.f;
-            yv[j] = (t + P[OFF_BOUT + j]) * keep;
+                                            float *__restrict__ yuser) {
+    const int j = threadIdx.x & 3;
+    float wo[16][MO];
+    out_weights(P, j, wo);
+    for (int64_t v = blockIdx.x * (int64_t)OV + threadIdx.x / 4; v < n; v += (int64_t)gridDim.x * OV) {
+        float hv[16], t[MO] = {0.f, 0.f, 0.f};
+        load_row16(h, v, j, hv);
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+#pragma unroll
+            for (int c = 0; c < MO; ++c) t[c] += hv[k] * wo[k][c];
+#pragma unroll
+        for (int c = 0; c < MO; ++c) {
+            t[c] += __shfl_xor(t[c], 1, 64);
+            t[c] += __shfl_xor(t[c], 2, 64);
         }
-        if (c < MO) y[v * MO + c] = c == 0 ? yv[0] : (c == 1 ? yv[1] : yv[2]);
-        if (target) {
-            float g[MO];
-            for (int j = 0; j < MO; ++j) {
-                const float keep = mask[v * 3 + j] ? 0.f : 1.f;
-                const float d = yv[j] - target[v * MO + j];
-                if (c == 0) lsum += double(d) * double(d);
-                g[j] = inv * d * keep;
-            }
-            if (c < MO) gy[v * MO + c] = c == 0 ? g[0] : (c == 1 ? g[1] : g[2]);
-            float ghc = 0.f;
-            for (int j = 0; j < MO; ++j) ghc += g[j] * P[OFF_WOUT + c * MO + j];
-            gh[v * MH + c] = ghc;
-        }
-    }
-    if (target) {
-        if (c == 0) lds[w] = lsum;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int k = 0; k < MW; ++k) t += lds[k];
-            lpart[blockIdx.x] = t;
+        if (j < MO) {
+            const float o = (j == 0 ? t[0] : (j == 1 ? t[1] : t[2])) + P[OFF_BOUT + j];
+            const float yv = mask[v * 3 + j] ? o * 0.f : o;
+            y[v * MO + j] = yv;
+            if (yuser) yuser[v * MO + j] = yv;
         }
     }
 }
@@ -240,198 +404,276 @@ __global__ void __launch_bounds__(MB) k_out(int64_t n, const float *__restrict__
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-// ga = gh * (a > 0); gmd = (ga W_n^T) / deg; gd_k = ga W_dk^T.  The four
-// matrices sit transposed in LDS (64 KB), so lane c reads W[c][k] of row k
-// of the copy: consecutive lanes, consecutive banks.  A wave takes VB
-// vertices at a time, each LDS value serving all of them.
-
-__global__ void __launch_bounds__(MB) k_mp_bwd1(int64_t n, const int64_t *__restrict__ gp, const float *__restrict__ P,
-                                                int l, const float *__restrict__ gh, const float *__restrict__ a,
-                                                float *__restrict__ ga, float *__restrict__ gmd,
-                                                float *__restrict__ gd) {
-    extern __shared__ float W[];   // [4][64][64] transposed: W_n, W_dx, W_dy, W_dz
-    for (int t = threadIdx.x; t < MH * MH; t += MB) {
-        const int r = t / MH, q = t % MH;   // W[r][q] -> copy[q][r]
-        W[q * MH + r] = P[off_wn(l) + t];
-        W[MH * MH + q * MH + r] = P[off_wd(l) + t];
-        W[2 * MH * MH + q * MH + r] = P[off_wd(l) + MH * MH + t];
-        W[3 * MH * MH + q * MH + r] = P[off_wd(l) + 2 * MH * MH + t];
+// dL/dy (MSE against a target: 2 (y - t) / 3n; or given) with constrained
+// entries zero, gh = gy W_out^T, ga = gh where the last layer's gate a is open;
+// per block: the loss, the output layer's gradients (64 x 3 and 3 values,
+// float partials at wpart) and the column sums of ga.  Lanes as in k_out.
+constexpr int OPART = MH * MO + MO;
+template <bool MSE>
+__global__ void __launch_bounds__(MB) k_out_bwd(int64_t n, const float *__restrict__ P, const float *__restrict__ h,
+                                                const float *__restrict__ a, const uint8_t *__restrict__ mask,
+                                                const float *__restrict__ y, const float *__restrict__ in,
+                                                float *__restrict__ gh, float *__restrict__ ga,
+                                                double *__restrict__ lpart, double *__restrict__ part,
+                                                float *__restrict__ wpart) {
+    __shared__ double s_cs[MW][MH], s_l[MW];
+    __shared__ float s_w[MW][OPART];
+    const int j = threadIdx.x & 3, lane = threadIdx.x & 63, w = threadIdx.x / 64;
+    float wo[16][MO], gw[16][MO], gb[MO] = {0.f, 0.f, 0.f};
+    double cs[16], ls = 0.0;
+    out_weights(P, j, wo);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        cs[k] = 0.0;
+#pragma unroll
+        for (int c = 0; c < MO; ++c) gw[k][c] = 0.f;
+    }
+    const float inv = 2.f / float(3 * n);
+    for (int64_t v = blockIdx.x * (int64_t)OV + threadIdx.x / 4; v < n; v += (int64_t)gridDim.x * OV) {
+        float hv[16], av[16], g[MO];
+        load_row16(h, v, j, hv);
+        load_row16(a, v, j, av);
+#pragma unroll
+        for (int c = 0; c < MO; ++c) {
+            const bool keep = mask[v * 3 + c] == 0;
+            if (MSE) {
+                const float d = y[v * MO + c] - in[v * MO + c];
+                if (j == 0) ls += double(d) * double(d);
+                g[c] = keep ? inv * d : 0.f;
+            } else {
+                g[c] = keep ? in[v * MO + c] : 0.f;
+            }
+            gb[c] += g[c];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f32x4 t, u;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = 4 * i + r;
+                float x = 0.f;
+#pragma unroll
+                for (int c = 0; c < MO; ++c) {
+                    x += g[c] * wo[k][c];
+                    gw[k][c] += hv[k] * g[c];
+                }
+                t[r] = x;
+                u[r] = av[k] > 0.f ? x : 0.f;
+                cs[k] += u[r];
+            }
+            *reinterpret_cast<f32x4 *>(gh + v * MH + 16 * i + 4 * j) = t;
+            *reinterpret_cast<f32x4 *>(ga + v * MH + 16 * i + 4 * j) = u;
+        }
+    }
+    // the wave's 16 vertices in a fixed tree, then the waves in order
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            cs[k] += __shfl_xor(cs[k], o, 64);
+#pragma unroll
+            for (int c = 0; c < MO; ++c) gw[k][c] += __shfl_xor(gw[k][c], o, 64);
+        }
+#pragma unroll
+        for (int c = 0; c < MO; ++c) gb[c] += __shfl_xor(gb[c], o, 64);
+        ls += __shfl_xor(ls, o, 64);
+    }
+    if (lane < 4) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int ch = 16 * (k / 4) + 4 * j + k % 4;
+            s_cs[w][ch] = cs[k];
+#pragma unroll
+            for (int c = 0; c < MO; ++c) s_w[w][ch * MO + c] = gw[k][c];
+        }
+        if (j == 0) {
+            s_l[w] = ls;
+#pragma unroll
+            for (int c = 0; c < MO; ++c) s_w[w][MH * MO + c] = gb[c];
+        }
     }
     __syncthreads();
-    const int c = threadIdx.x & 63;
-    const int64_t step = (int64_t)gridDim.x * MW * VB;
-    for (int64_t v0 = (blockIdx.x * (int64_t)MW + threadIdx.x / 64) * VB; v0 < n; v0 += step) {
-        float g[VB], t[VB][4];
-#pragma unroll
-        for (int i = 0; i < VB; ++i) {
-            const int64_t v = v0 + i;
-            g[i] = v < n && a[v * MH + c] > 0.f ? gh[v * MH + c] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[i][j] = 0.f;
-        }
-#pragma unroll 4
-        for (int k = 0; k < MH; ++k) {
-            // W^T[k][c] of each matrix: W[c][k] (row c of the weight, column k)
-            const float w0 = W[k * MH + c], w1 = W[MH * MH + k * MH + c], w2 = W[2 * MH * MH + k * MH + c],
-                        w3 = W[3 * MH * MH + k * MH + c];
-#pragma unroll
-            for (int i = 0; i < VB; ++i) {
-                const float gk = lane_val(g[i], k);
-                t[i][0] += gk * w0;
-                t[i][1] += gk * w1;
-                t[i][2] += gk * w2;
-                t[i][3] += gk * w3;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < VB; ++i) {
-            const int64_t v = v0 + i;
-            if (v >= n) break;
-            ga[v * MH + c] = g[i];
-            const int64_t deg = gp[v + 1] - gp[v];
-            gmd[v * MH + c] = deg > 0 ? t[i][0] / float(deg) : 0.f;
-            gd[v * MD + c] = t[i][1];
-            gd[v * MD + MH + c] = t[i][2];
-            gd[v * MD + 2 * MH + c] = t[i][3];
-        }
+    const int t = threadIdx.x;
+    if (t < MH) {
+        double v = 0.0;
+        for (int k = 0; k < MW; ++k) v += s_cs[k][t];
+        part[blockIdx.x * (int64_t)MH + t] = v;
+    }
+    if (t < OPART) {
+        float v = 0.f;
+        for (int k = 0; k < MW; ++k) v += s_w[k][t];
+        wpart[blockIdx.x * (int64_t)OPART + t] = v;
+    }
+    if (MSE && t == 0) {
+        double v = 0.0;
+        for (int k = 0; k < MW; ++k) v += s_l[k];
+        lpart[blockIdx.x] = v;
     }
 }
 
-// gh_prev = gh + ga W_s^T + gg / n + sum_{u in N(v)} (gmd_u + sum_k w^k_uv gd_k[u]),
-// w^k_uv = (x_v - x_u)_k / (deg_u l_u)
-__global__ void __launch_bounds__(MB) k_mp_bwd2(int64_t n, const int64_t *__restrict__ gp, const int32_t *__restrict__ gi,
-                                                const float *__restrict__ xf, const float *__restrict__ invdl,
-                                                const float *__restrict__ P, int l, const float *__restrict__ ga,
-                                                const float *__restrict__ gmd, const float *__restrict__ gd,
-                                                const float *__restrict__ gg, float *__restrict__ gh) {
-    __shared__ float Ws[MH * MH];   // W_s transposed (conflict-free reads, as k_mp_bwd1)
-    for (int t = threadIdx.x; t < MH * MH; t += MB) Ws[(t % MH) * MH + t / MH] = P[off_ws(l) + t];
+// Weight gradients of a layer, partial over a chunk of vertices:
+//   part[b][k][c] = sum_v [h | m | d](v, k) ga(v, c),  k < 320, c < 64
+// A wave holds 80 of the 320 rows (20 MFMA tiles of 16 x 16 in 80 registers);
+// four vertices per v_mfma_f32_16x16x4, operands straight from global memory
+// (16 channels of four rows: 64-byte pieces), two steps in flight.
+// Bound: the float32 matrix rate and the rows, 0.09 and 0.10 ms per layer on
+// 334,368 vertices; 1.31 (three LDS-tiled vector products) -> 0.28 ms.
+__global__ void __launch_bounds__(MB, 2) k_wgrad(int64_t n, const float *__restrict__ h, const float *__restrict__ m,
+                                                 const float *__restrict__ d, const float *__restrict__ ga,
+                                                 float *__restrict__ part) {
+    constexpr int MTW = MK / 16 / MW;   // row tiles per wave
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64, i16 = lane & 15, q = lane >> 4;
+    const float *base[MTW];
+    int ld[MTW];
+#pragma unroll
+    for (int t = 0; t < MTW; ++t) {
+        const int tile = w * MTW + t, slab = tile / 4, c0 = (tile % 4) * 16;
+        base[t] = (slab == 0 ? h : (slab == 1 ? m : d + (slab - 2) * MH)) + c0 + i16;
+        ld[t] = slab < 2 ? MH : MD;
+    }
+    f32x4 acc[MTW][4];
+#pragma unroll
+    for (int t = 0; t < MTW; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t chunk = ((n + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;
+    const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    auto load = [&](int64_t r, float (&x)[MTW], float (&g)[4]) {
+        const int64_t v = r + q;
+        const bool ok = v < hi;
+        const int64_t vv = ok ? v : lo;   // inside the chunk
+#pragma unroll
+        for (int t = 0; t < MTW; ++t) {
+            const float z = base[t][vv * ld[t]];
+            x[t] = ok ? z : 0.f;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float z = ga[vv * MH + 16 * c + i16];
+            g[c] = ok ? z : 0.f;
+        }
+    };
+    if (lo < hi) {
+        float x0[MTW], g0[4], x1[MTW], g1[4];
+        load(lo, x0, g0);
+        for (int64_t r = lo; r < hi; r += 8) {
+            load(r + 4, x1, g1);   // past the chunk: zeros
+#pragma unroll
+            for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0[t], g0[c], acc[t][c], 0, 0, 0);
+            load(r + 8, x0, g0);
+#pragma unroll
+            for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1[t], g1[c], acc[t][c], 0, 0, 0);
+        }
+    }
+    float *o = part + blockIdx.x * (int64_t)(MK * MH);
+#pragma unroll
+    for (int t = 0; t < MTW; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[((w * MTW + t) * 16 + 4 * q + r) * MH + 16 * c + i16] = acc[t][c][r];
+}
+
+// The same for the input layer: part[b][k][c] = sum_v X(v, k) ga(v, c),
+// k < 10; one 16-row tile, the waves take every fourth step of four vertices.
+__global__ void __launch_bounds__(MB) k_wgrad_in(int64_t n, const float *__restrict__ X, const float *__restrict__ ga,
+                                                 float *__restrict__ part) {
+    __shared__ float s_w[MW][MF * MH];
+    const int lane = threadIdx.x & 63, w = threadIdx.x / 64, i16 = lane & 15, q = lane >> 4;
+    f32x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t chunk = ((n + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
+    const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int64_t r = lo + 4 * w; r < hi; r += 4 * MW) {
+        const int64_t v = r + q;
+        const bool ok = v < hi;
+        const int64_t vv = ok ? v : lo;
+        const float z = X[vv * MF + (i16 < MF ? i16 : 0)];
+        const float x = ok && i16 < MF ? z : 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float y = ga[vv * MH + 16 * c + i16];
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, ok ? y : 0.f, acc[c], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * q + r < MF) s_w[w][(4 * q + r) * MH + 16 * c + i16] = acc[c][r];
     __syncthreads();
-    const int c = threadIdx.x & 63;
-    const float ggc = gg[c] / float(n);
-    for (int64_t v = blockIdx.x * (int64_t)MW + threadIdx.x / 64; v < n; v += (int64_t)gridDim.x * MW) {
-        const float g = ga[v * MH + c];
-        float t = gh[v * MH + c] + ggc;
+    for (int e = threadIdx.x; e < MF * MH; e += MB) {
+        float t = 0.f;
+        for (int k = 0; k < MW; ++k) t += s_w[k][e];
+        part[blockIdx.x * (int64_t)(MF * MH) + e] = t;
+    }
+}
+
+// Sums over the parts of nel-element partial tables, in double: a workgroup
+// takes 64 elements, its four waves a quarter of the parts each (in order),
+// the quarters added in order.  The sum of element e goes to out(e).
+template <class Out>
+__device__ __forceinline__ void sum_table(int nparts, int nel, const float *__restrict__ part, Out out) {
+    __shared__ double lds[MW][64];
+    const int lane = threadIdx.x & 63, y = threadIdx.x / 64;
+    const int e = blockIdx.x * 64 + lane;
+    const int b0 = nparts * y / MW, b1 = nparts * (y + 1) / MW;
+    double s = 0.0;
+    if (e < nel)
 #pragma unroll 8
-        for (int k = 0; k < MH; ++k) t += lane_val(g, k) * Ws[k * MH + c];
-        const float xv0 = xf[v * 3], xv1 = xf[v * 3 + 1], xv2 = xf[v * 3 + 2];
-        for (int64_t e = gp[v]; e < gp[v + 1]; ++e) {
-            const int64_t u = gi[e];
-            const float iu = invdl[u];
-            t += gmd[u * MH + c];
-            t += (xv0 - xf[u * 3]) * iu * gd[u * MD + c];
-            t += (xv1 - xf[u * 3 + 1]) * iu * gd[u * MD + MH + c];
-            t += (xv2 - xf[u * 3 + 2]) * iu * gd[u * MD + 2 * MH + c];
-        }
-        gh[v * MH + c] = t;
+        for (int b = b0; b < b1; ++b) s += part[(int64_t)b * nel + e];
+    lds[y][lane] = s;
+    __syncthreads();
+    if (y == 0 && e < nel) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < MW; ++k) t += lds[k][lane];
+        out(e, t);
     }
 }
-
-// ga_in = gh * (h0 > 0)
-__global__ void k_relu_mask(int64_t n, const float *__restrict__ h0, const float *__restrict__ gh,
-                            float *__restrict__ ga) {
-    for (int64_t t = blockIdx.x * (int64_t)MB + threadIdx.x; t < n * MH; t += (int64_t)gridDim.x * MB)
-        ga[t] = h0[t] > 0.f ? gh[t] : 0.f;
+__global__ void __launch_bounds__(MB) k_sum_parts(int nparts, int nel, const float *__restrict__ part,
+                                                  float *__restrict__ out) {
+    sum_table(nparts, nel, part, [&](int e, double t) { out[e] = float(t); });
 }
-
-// partial X^T Y over a chunk of vertices: X [n][KX], Y [n][KY]; block partial
-// tile [KX][KY] (thread t owns entries t, t+256, ...)
-template <int KX, int KY>
-__global__ void __launch_bounds__(MB) k_xty(int64_t n, const float *__restrict__ X, const float *__restrict__ Y,
-                                            float *__restrict__ part) {
-    constexpr int ROWS = 32;
-    __shared__ float xs[ROWS * KX], ys[ROWS * KY];
-    constexpr int PER = (KX * KY + MB - 1) / MB;
-    float acc[PER];
-    for (int q = 0; q < PER; ++q) acc[q] = 0.f;
-    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    for (int64_t r0 = lo; r0 < hi; r0 += ROWS) {
-        const int rows = (int)min<int64_t>(ROWS, hi - r0);
-        for (int t = threadIdx.x; t < ROWS * KX; t += MB) xs[t] = (t / KX) < rows ? X[(r0 + t / KX) * KX + t % KX] : 0.f;
-        for (int t = threadIdx.x; t < ROWS * KY; t += MB) ys[t] = (t / KY) < rows ? Y[(r0 + t / KY) * KY + t % KY] : 0.f;
-        __syncthreads();
-        for (int q = 0; q < PER; ++q) {
-            const int e = threadIdx.x + q * MB;
-            if (e < KX * KY) {
-                const int i = e / KY, j = e % KY;
-                float s = 0.f;
-                for (int r = 0; r < rows; ++r) s += xs[r * KX + i] * ys[r * KY + j];
-                acc[q] += s;
-            }
-        }
-        __syncthreads();
-    }
-    for (int q = 0; q < PER; ++q) {
-        const int e = threadIdx.x + q * MB;
-        if (e < KX * KY) part[blockIdx.x * (int64_t)(KX * KY) + e] = acc[q];
-    }
-}
-
-// out[e] (+)= sum_b part[b][e], fixed order in double
-__global__ void k_sum_parts(int nparts, int nel, const float *__restrict__ part, float *__restrict__ out) {
-    for (int e = blockIdx.x * MB + threadIdx.x; e < nel; e += gridDim.x * MB) {
-        double s = 0.0;
-        for (int b = 0; b < nparts; ++b) s += part[(int64_t)b * nel + e];
-        out[e] = float(s);
-    }
+// the [320][64] table of a layer to its five matrices
+__global__ void __launch_bounds__(MB) k_sum_layer(int nparts, const float *__restrict__ part, int l,
+                                                  float *__restrict__ grad) {
+    sum_table(nparts, MK * MH, part, [&](int e, double t) {
+        grad[off_slab(l, e / (MH * MH)) + e % (MH * MH)] = float(t);
+    });
 }
 
 // layer scalars: gb = colsum(ga); gW_g = g^T gb (outer product); gg = gb W_g^T
-__global__ void k_layer_small(int nparts, const double *__restrict__ part, const float *__restrict__ g,
-                              const float *__restrict__ P, int l, float *__restrict__ grad, float *__restrict__ gg) {
-    __shared__ float gb[64];
+__global__ void __launch_bounds__(SB) k_layer_small(int nparts, const double *__restrict__ part,
+                                                    const float *__restrict__ g, const float *__restrict__ P, int l,
+                                                    float *__restrict__ grad, float *__restrict__ gg) {
+    __shared__ double lds[SB];
+    __shared__ float gb[64], ldf[SB];
     const int c = threadIdx.x;
-    double s = 0.0;
-    for (int b = 0; b < nparts; ++b) s += part[b * 64 + c];
-    gb[c] = float(s);
-    grad[off_b(l) + c] = gb[c];
-    __syncthreads();
-    for (int k = 0; k < MH; ++k) grad[off_wg(l) + k * MH + c] = g[k] * gb[c];
-    float t = 0.f;
-    for (int k = 0; k < MH; ++k) t += gb[k] * P[off_wg(l) + c * MH + k];
-    gg[c] = t;
-}
-
-// b grads from partial colsums of widths <= 64
-__global__ void k_colsum_out(int nparts, const double *__restrict__ part, int width, float *__restrict__ out) {
-    const int c = threadIdx.x;
-    if (c >= width) return;
-    double s = 0.0;
-    for (int b = 0; b < nparts; ++b) s += part[b * 64 + c];
-    out[c] = float(s);
-}
-
-// column sums of an [n][3] array into partials[block][64] (first 3 used)
-__global__ void __launch_bounds__(MB) k_colsum3(int64_t n, const float *__restrict__ Y, double *__restrict__ part) {
-    __shared__ double lds[MB * 3];
-    const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double t[3] = {0, 0, 0};
-    for (int64_t v = lo + threadIdx.x; v < hi; v += MB)
-        for (int j = 0; j < 3; ++j) t[j] += Y[v * 3 + j];
-    for (int j = 0; j < 3; ++j) lds[threadIdx.x * 3 + j] = t[j];
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        double s = 0.0;
-        for (int k = 0; k < MB; ++k) s += lds[k * 3 + threadIdx.x];
-        part[blockIdx.x * 64 + threadIdx.x] = s;
+    const double s = sum_parts64(nparts, part, lds);
+    if (c < 64) {
+        gb[c] = float(s);
+        grad[off_b(l) + c] = gb[c];
     }
+    __syncthreads();
+    for (int t = threadIdx.x; t < MH * MH; t += SB) grad[off_wg(l) + t] = g[t / MH] * gb[t % MH];
+    const float t = vec_mat64<true>(gb, P + off_wg(l), ldf);
+    if (c < 64) gg[c] = t;
 }
 
-// gh = (gy * keep) W_out^T, gy_masked stored
-__global__ void __launch_bounds__(MB) k_gy_to_gh(int64_t n, const float *__restrict__ P, const uint8_t *__restrict__ mask,
-                                                 const float *__restrict__ gy_in, float *__restrict__ gy,
-                                                 float *__restrict__ gh) {
-    const int c = threadIdx.x & 63;
-    for (int64_t v = blockIdx.x * (int64_t)MW + threadIdx.x / 64; v < n; v += (int64_t)gridDim.x * MW) {
-        float g[MO];
-        for (int j = 0; j < MO; ++j) g[j] = mask[v * 3 + j] ? 0.f : gy_in[v * MO + j];
-        if (c < MO) gy[v * MO + c] = c == 0 ? g[0] : (c == 1 ? g[1] : g[2]);
-        float t = 0.f;
-        for (int j = 0; j < MO; ++j) t += g[j] * P[OFF_WOUT + c * MO + j];
-        gh[v * MH + c] = t;
-    }
+// the input layer's bias gradient from partial column sums
+__global__ void __launch_bounds__(SB) k_colsum_out(int nparts, const double *__restrict__ part,
+                                                   float *__restrict__ out) {
+    __shared__ double lds[SB];
+    const double s = sum_parts64(nparts, part, lds);
+    if (threadIdx.x < 64) out[threadIdx.x] = float(s);
 }
 
 // u = S_U y * keep, u_t = S_U t  (float64, natural order)
@@ -513,8 +755,8 @@ struct mpnn_handle {
     te::DBuf<double> xc;  // centred coordinates
     te::DBuf<float> xf, invdl;  // float centred coordinates, 1 / (deg l) per vertex
     te::DBuf<float> h[te::ML + 1], m[te::ML], d[te::ML], a[te::ML], g[te::ML], gw;
-    te::DBuf<float> y, gy, gh, ga, gmd, gd, gg, part;
-    te::DBuf<double> dpart;
+    te::DBuf<float> y, gh, ga[2], gg, part;
+    te::DBuf<double> dpart, lpart;
     te::DBuf<float> X;     // last forward input (borrowed copy)
     te::DBuf<uint8_t> mask;
     bool have_forward = false;
@@ -564,14 +806,12 @@ extern "C" int mpnn_create(int64_t n, const int64_t *row_ptr, const int32_t *col
         }
         H->gw.alloc(MH);
         H->y.alloc(n * MO);
-        H->gy.alloc(n * MO);
         H->gh.alloc(n * MH);
-        H->ga.alloc(n * MH);
-        H->gmd.alloc(n * MH);
-        H->gd.alloc(n * MD);
+        for (auto &b : H->ga) b.alloc(n * MH);
         H->gg.alloc(MH);
-        H->part.alloc((size_t)RED_BLOCKS * MD * MH);
-        H->dpart.alloc((size_t)RED_BLOCKS * 64);
+        H->part.alloc((size_t)RED_BLOCKS * MK * MH);
+        H->dpart.alloc((size_t)LAYER_BLOCKS * MH);
+        H->lpart.alloc(RED_BLOCKS);
         H->X.alloc(n * MF);
         H->mask.alloc(n * 3);
         TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -596,64 +836,72 @@ extern "C" int mpnn_features(mpnn_handle *H, const double *T, double T_ref, cons
     });
 }
 
-static int nparts_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(RED_BLOCKS, (n + 255) / 256)); }
+// workgroups of the weight-gradient and output passes: 64 vertices each at least
+static int nparts_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(RED_BLOCKS, (n + 63) / 64)); }
+
+// Tiles of 32 vertices; of 16 while that leaves CUs without a tile, so that a
+// small mesh spreads over twice the workgroups.
+static bool wide_tiles(int64_t n) { return (n + 31) / 32 > LAYER_BLOCKS; }
+static int layer_blocks(int64_t n) {
+    const int64_t nt = wide_tiles(n) ? (n + 31) / 32 : (n + 15) / 16;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(nt, LAYER_BLOCKS));
+}
+template <bool BWD>
+static void launch_layer(mpnn_handle *H, const float *P, int l, const float *gvec, const float *src, float *m, float *d,
+                         float *a, const float *gate, float *hout, float *gout, hipStream_t s) {
+    const int64_t n = H->n;
+    const dim3 g(layer_blocks(n));
+    if (wide_tiles(n))
+        hipLaunchKernelGGL((k_mp_layer<2, BWD>), g, dim3(MB), 0, s, n, (n + 31) / 32, H->gp.p, H->gi.p, H->xf.p,
+                           H->invdl.p, P, l, gvec, src, m, d, a, gate, hout, gout, H->dpart.p);
+    else
+        hipLaunchKernelGGL((k_mp_layer<1, BWD>), g, dim3(MB), 0, s, n, (n + 15) / 16, H->gp.p, H->gi.p, H->xf.p,
+                           H->invdl.p, P, l, gvec, src, m, d, a, gate, hout, gout, H->dpart.p);
+}
 
 extern "C" int mpnn_forward(mpnn_handle *H, const float *P, const float *X, const uint8_t *mask, float *y,
                             hipStream_t s) {
     return guarded([&] {
         TE_REQUIRE(H && P && X && mask, TE_EINVAL, "bad argument");
         const int64_t n = H->n;
-        TE_CHECK_HIP(hipMemcpyAsync(H->X.p, X, n * MF * sizeof(float), hipMemcpyDeviceToDevice, s));
-        TE_CHECK_HIP(hipMemcpyAsync(H->mask.p, mask, n * 3, hipMemcpyDeviceToDevice, s));
-        const int np = nparts_for(n);
-        hipLaunchKernelGGL(k_in, dim3(vgrid(n)), dim3(MB), 0, s, n, P, X, H->h[0].p);
+        const int gi = (int)std::min<int64_t>((n + MW - 1) / MW, LAYER_BLOCKS);
+        hipLaunchKernelGGL(k_in, dim3(gi), dim3(MB), 0, s, n, P, X, mask, H->X.p, H->mask.p, H->h[0].p, H->dpart.p);
+        int np = gi;
         for (int l = 0; l < ML; ++l) {
-            hipLaunchKernelGGL(k_colsum, dim3(np), dim3(MB), 0, s, n, H->h[l].p, H->dpart.p);
-            hipLaunchKernelGGL(k_global, dim3(1), dim3(64), 0, s, np, H->dpart.p, n, P, l, H->g[l].p, H->gw.p);
-            hipLaunchKernelGGL(k_mp_fwd, dim3(vgrid((n + VB - 1) / VB)), dim3(MB), 4 * MH * MH * sizeof(float), s, n,
-                               H->gp.p,
-                               H->gi.p, H->xf.p, H->invdl.p, P, l, H->gw.p, H->h[l].p, H->m[l].p, H->d[l].p,
-                               H->a[l].p, H->h[l + 1].p);
+            hipLaunchKernelGGL(k_global, dim3(1), dim3(SB), 0, s, np, H->dpart.p, n, P, l, H->g[l].p, H->gw.p);
+            launch_layer<false>(H, P, l, H->gw.p, H->h[l].p, H->m[l].p, H->d[l].p, H->a[l].p, nullptr, H->h[l + 1].p,
+                                nullptr, s);
+            np = layer_blocks(n);
         }
-        hipLaunchKernelGGL(k_out, dim3(vgrid(n)), dim3(MB), 0, s, n, P, H->h[ML].p, mask, y ? y : H->y.p,
-                           (const float *)nullptr, (float *)nullptr, (float *)nullptr, (double *)nullptr);
+        hipLaunchKernelGGL(k_out, dim3((unsigned)std::min<int64_t>((n + OV - 1) / OV, 4096)), dim3(MB), 0, s, n, P,
+                           H->h[ML].p, H->mask.p, H->y.p, y == H->y.p ? nullptr : y);
         TE_CHECK_HIP(hipGetLastError());
-        if (y && y != H->y.p) TE_CHECK_HIP(hipMemcpyAsync(H->y.p, y, n * MO * sizeof(float), hipMemcpyDeviceToDevice, s));
         H->have_forward = true;
         return TE_OK;
     });
 }
 
-static void backward_tail(mpnn_handle *H, const float *P, float *grad, hipStream_t s) {
+// Backward pass after the output layer's (gh, ga of the last layer and its
+// column sums from np workgroups are in the handle).
+static void backward_tail(mpnn_handle *H, const float *P, float *grad, int np, hipStream_t s) {
     const int64_t n = H->n;
-    const int np = nparts_for(n);
-    const unsigned vg = vgrid(n);
-    // output layer (gy and gh are in the handle)
-    hipLaunchKernelGGL((k_xty<MH, MO>), dim3(np), dim3(MB), 0, s, n, H->h[ML].p, H->gy.p, H->part.p);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(MB), 0, s, np, MH * MO, H->part.p, grad + OFF_WOUT);
-    hipLaunchKernelGGL(k_colsum3, dim3(np), dim3(MB), 0, s, n, H->gy.p, H->dpart.p);
-    hipLaunchKernelGGL(k_colsum_out, dim3(1), dim3(64), 0, s, np, H->dpart.p, MO, grad + OFF_BOUT);
+    const int nw = nparts_for(n);
+    hipLaunchKernelGGL(k_sum_parts, dim3((OPART + 63) / 64), dim3(MB), 0, s, np, OPART, H->part.p, grad + OFF_WOUT);
+    int cur = 0;
     for (int l = ML - 1; l >= 0; --l) {
-        hipLaunchKernelGGL(k_mp_bwd1, dim3(vgrid((n + VB - 1) / VB)), dim3(MB), 4 * MH * MH * sizeof(float), s, n,
-                           H->gp.p, P, l, H->gh.p,
-                           H->a[l].p, H->ga.p, H->gmd.p, H->gd.p);
-        hipLaunchKernelGGL((k_xty<MH, MH>), dim3(np), dim3(MB), 0, s, n, H->h[l].p, H->ga.p, H->part.p);
-        hipLaunchKernelGGL(k_sum_parts, dim3(16), dim3(MB), 0, s, np, MH * MH, H->part.p, grad + off_ws(l));
-        hipLaunchKernelGGL((k_xty<MH, MH>), dim3(np), dim3(MB), 0, s, n, H->m[l].p, H->ga.p, H->part.p);
-        hipLaunchKernelGGL(k_sum_parts, dim3(16), dim3(MB), 0, s, np, MH * MH, H->part.p, grad + off_wn(l));
-        hipLaunchKernelGGL((k_xty<MD, MH>), dim3(np), dim3(MB), 0, s, n, H->d[l].p, H->ga.p, H->part.p);
-        hipLaunchKernelGGL(k_sum_parts, dim3(48), dim3(MB), 0, s, np, MD * MH, H->part.p, grad + off_wd(l));
-        hipLaunchKernelGGL(k_colsum, dim3(np), dim3(MB), 0, s, n, H->ga.p, H->dpart.p);
-        hipLaunchKernelGGL(k_layer_small, dim3(1), dim3(64), 0, s, np, H->dpart.p, H->g[l].p, P, l, grad, H->gg.p);
-        hipLaunchKernelGGL(k_mp_bwd2, dim3(vg), dim3(MB), 0, s, n, H->gp.p, H->gi.p, H->xf.p, H->invdl.p, P, l,
-                           H->ga.p, H->gmd.p, H->gd.p, H->gg.p, H->gh.p);
+        hipLaunchKernelGGL(k_layer_small, dim3(1), dim3(SB), 0, s, np, H->dpart.p, H->g[l].p, P, l, grad, H->gg.p);
+        hipLaunchKernelGGL(k_wgrad, dim3(nw), dim3(MB), 0, s, n, H->h[l].p, H->m[l].p, H->d[l].p, H->ga[cur].p,
+                           H->part.p);
+        hipLaunchKernelGGL(k_sum_layer, dim3(MK * MH / 64), dim3(MB), 0, s, nw, H->part.p, l, grad);
+        // the gate of the layer below; the input layer's is h0 > 0
+        launch_layer<true>(H, P, l, H->gg.p, H->ga[cur].p, nullptr, nullptr, nullptr,
+                           l > 0 ? H->a[l - 1].p : H->h[0].p, H->gh.p, H->ga[cur ^ 1].p, s);
+        np = layer_blocks(n);
+        cur ^= 1;
     }
-    hipLaunchKernelGGL(k_relu_mask, dim3((unsigned)std::min<int64_t>((n * MH + MB - 1) / MB, 65536)), dim3(MB), 0, s,
-                       n, H->h[0].p, H->gh.p, H->ga.p);
-    hipLaunchKernelGGL((k_xty<MF, MH>), dim3(np), dim3(MB), 0, s, n, H->X.p, H->ga.p, H->part.p);
-    hipLaunchKernelGGL(k_sum_parts, dim3(4), dim3(MB), 0, s, np, MF * MH, H->part.p, grad + OFF_WIN);
-    hipLaunchKernelGGL(k_colsum, dim3(np), dim3(MB), 0, s, n, H->ga.p, H->dpart.p);
-    hipLaunchKernelGGL(k_colsum_out, dim3(1), dim3(64), 0, s, np, H->dpart.p, MH, grad + OFF_BIN);
+    hipLaunchKernelGGL(k_wgrad_in, dim3(nw), dim3(MB), 0, s, n, H->X.p, H->ga[cur].p, H->part.p);
+    hipLaunchKernelGGL(k_sum_parts, dim3((MF * MH + 63) / 64), dim3(MB), 0, s, nw, MF * MH, H->part.p, grad + OFF_WIN);
+    hipLaunchKernelGGL(k_colsum_out, dim3(1), dim3(SB), 0, s, np, H->dpart.p, grad + OFF_BIN);
     TE_CHECK_HIP(hipGetLastError());
 }
 
@@ -666,15 +914,15 @@ extern "C" int mpnn_backward(mpnn_handle *H, const float *P, const float *target
         TE_REQUIRE(H->have_forward, TE_EINVAL, "mpnn_backward needs a preceding mpnn_forward");
         const int64_t n = H->n;
         const int np = nparts_for(n);
-        hipLaunchKernelGGL(k_out, dim3(np), dim3(MB), 0, s, n, P, H->h[ML].p, H->mask.p, H->y.p, target, H->gy.p,
-                           H->gh.p, H->dpart.p);
+        hipLaunchKernelGGL(k_out_bwd<true>, dim3(np), dim3(MB), 0, s, n, P, H->h[ML].p, H->a[ML - 1].p, H->mask.p,
+                           H->y.p, target, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p);
         TE_CHECK_HIP(hipGetLastError());
+        backward_tail(H, P, grad, np, s);
         std::vector<double> lp;
-        download(lp, H->dpart.p, np, s);
+        download(lp, H->lpart.p, np, s);
         double L = 0.0;
         for (double v : lp) L += v;
         if (loss) *loss = L / double(3 * n);
-        backward_tail(H, P, grad, s);
         return TE_OK;
     });
 }
@@ -684,9 +932,11 @@ extern "C" int mpnn_backward_from(mpnn_handle *H, const float *P, const float *g
     return guarded([&] {
         TE_REQUIRE(H && P && gy && grad, TE_EINVAL, "bad argument");
         TE_REQUIRE(H->have_forward, TE_EINVAL, "mpnn_backward_from needs a preceding mpnn_forward");
-        hipLaunchKernelGGL(k_gy_to_gh, dim3(vgrid(H->n)), dim3(MB), 0, s, H->n, P, H->mask.p, gy, H->gy.p, H->gh.p);
+        const int np = nparts_for(H->n);
+        hipLaunchKernelGGL(k_out_bwd<false>, dim3(np), dim3(MB), 0, s, H->n, P, H->h[ML].p, H->a[ML - 1].p, H->mask.p,
+                           H->y.p, gy, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p);
         TE_CHECK_HIP(hipGetLastError());
-        backward_tail(H, P, grad, s);
+        backward_tail(H, P, grad, np, s);
         return TE_OK;
     });
 }
