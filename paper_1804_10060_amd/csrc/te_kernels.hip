@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "te_dev.h"
 
@@ -269,101 +270,129 @@ __global__ void __launch_bounds__(512) k_roww(RowView<VT> A, const XT *__restric
     }
 }
 
-// Format 1 with several right-hand sides: one wave per row, lane = RHS, MU
-// blocks' x rows loaded before they are used (as k_sellm).
-template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
-__global__ void __launch_bounds__(1024) k_rowwm(RowView<VT> A, const XT *__restrict__ x, Epi epi, int nrhs,
-                                                double *__restrict__ partials, int wpb) {
-    constexpr int MU = BC <= 3 ? 4 : 2;
-    __shared__ double lds[1024];
-    const int64_t nb = gridDim.x;
-    const int64_t lb = xcd_logical_block(blockIdx.x, nb);
+// Format 1 with several right-hand sides.  A wave takes S = 64 / C entries of
+// a row at once: lane (slot, column), C the power of two that holds the
+// columns (so up to 32 columns leave no lane without work); wpr waves share a
+// row, wave w its entries w, w + wpr, ... (of slots), and their partial sums
+// meet in LDS, where BR * C threads each add one entry's in a fixed order and
+// run the epilogue.  With C = 64 the block values are wave-uniform and come
+// through the scalar cache, MU blocks' x rows loaded before they are used;
+// with slots every lane loads its block (16-byte pieces, one address per slot).
+// What bounds it: a row is a serial walk over its blocks, so rows x waves in
+// flight must cover the latency.  Against one wave per row with a lane per
+// column for any number of columns: level products at 5 columns (5,000 rows of
+// 46 blocks) 85 -> 35 us, the restrictions to levels of a few hundred long
+// rows 196 -> 16 us at 5 columns and 304 -> 85 us at 64.  Two slots of 32
+// columns measured slower than a lane per column with wave-uniform values
+// (24 columns: 116 against 80 us), so slots end at 16 columns.
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, int C>
+__global__ void __launch_bounds__(1024) k_rowm(RowView<VT> A, const XT *__restrict__ x, Epi epi, int nrhs, int wpr) {
+    constexpr int S = WAVE / C, E = BR * BC;
+    constexpr int VW = sizeof(VT) == 8 ? 2 : (E % 4 == 0 ? 4 : 2);
+    static_assert(E % VW == 0, "block of whole 8- or 16-byte pieces");
+    typedef VT vec_t __attribute__((ext_vector_type(VW)));
+    extern __shared__ __align__(16) char rowm_lds[];   // [waves][BR][C] partial sums
+    AT *buf = reinterpret_cast<AT *>(rowm_lds);
     const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t row = (int64_t)__builtin_amdgcn_readfirstlane((int)(lb * wpb + threadIdx.x / WAVE));
-    double red = 0.0;
-    if (row < A.nrows) {
-        AT acc[BR];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int grp = wv / wpr, ws = wv % wpr, rpg = blockDim.x / WAVE / wpr;
+    const int64_t row = xcd_logical_block(blockIdx.x, gridDim.x) * rpg + grp;
+    const bool live = row < A.nrows;   // uniform in the wave
+    const int slot = lane / C, j = lane % C;
+    const int jj = j < nrhs ? j : nrhs - 1;   // a spare column repeats the last, and is not stored
+    AT acc[BR];
 #pragma unroll
-        for (int i = 0; i < BR; ++i) acc[i] = AT(0);
-        // TR: the block is stored transposed (mirror of a lower block)
-        auto block = [&](const VT *v, const AT *xv, bool tr) {
+    for (int i = 0; i < BR; ++i) acc[i] = AT(0);
+    if (live) {
+        // the entries [lo, hi) of one list, col/idx its columns and blocks (idx
+        // null: block k of entry k); TR: the block is stored transposed
+        auto walk = [&](int64_t lo, int64_t hi, const int32_t *__restrict__ col, const int32_t *__restrict__ idx,
+                        auto tr) {
+            constexpr bool TR = decltype(tr)::value;
+            if constexpr (S == 1) {
+                constexpr int MU = BC <= 3 ? 4 : 2;
+                const int64_t cntw = hi - lo > ws ? (hi - lo - ws + wpr - 1) / wpr : 0;   // this wave's entries
+                for (int64_t t0 = 0; t0 < cntw; t0 += WAVE) {
+                    const int cnt = (int)min((int64_t)WAVE, cntw - t0);
+                    const int64_t kl = lo + ws + (t0 + (lane < cnt ? lane : 0)) * wpr;
+                    const int cl = col[kl];
+                    const int il = idx ? idx[kl] : 0;
+                    auto one = [&](int u, const AT *xv) {
+                        const VT *v = A.val + (idx ? (int64_t)__builtin_amdgcn_readlane(il, u)
+                                                   : lo + ws + (t0 + u) * wpr) * E;
 #pragma unroll
-            for (int i = 0; i < BR; ++i)
+                        for (int i = 0; i < BR; ++i)
 #pragma unroll
-                for (int j = 0; j < BC; ++j) acc[i] += AT(tr ? v[j * BC + i] : v[i * BC + j]) * xv[j];
-        };
-        // column indices 64 at a time (every lane active), taken with readlane
-        const int64_t lo = A.rptr[row], hi = A.rptr[row + 1];
-        for (int64_t k0 = lo; k0 < hi; k0 += WAVE) {
-            const int cnt = (int)min((int64_t)WAVE, hi - k0);
-            const int cl = k0 + lane < hi ? A.col[k0 + lane] : 0;
-            if (lane < nrhs) {
-                int u = 0;
-                for (; u + MU <= cnt; u += MU) {
-                    AT xv[MU][BC];
+                            for (int b = 0; b < BC; ++b) acc[i] += AT(TR ? v[b * BC + i] : v[i * BC + b]) * xv[b];
+                    };
+                    auto load = [&](int u, AT *xv) {
+                        const int64_t c = __builtin_amdgcn_readlane(cl, u);
 #pragma unroll
-                    for (int t = 0; t < MU; ++t) {
-                        const int64_t c = __builtin_amdgcn_readlane(cl, u + t);
+                        for (int b = 0; b < BC; ++b) xv[b] = AT(x[(c * BC + b) * nrhs + jj]);
+                    };
+                    int u = 0;
+                    for (; u + MU <= cnt; u += MU) {
+                        AT xv[MU][BC];
 #pragma unroll
-                        for (int j = 0; j < BC; ++j) xv[t][j] = AT(x[(c * BC + j) * nrhs + lane]);
+                        for (int t = 0; t < MU; ++t) load(u + t, xv[t]);
+#pragma unroll
+                        for (int t = 0; t < MU; ++t) one(u + t, xv[t]);
                     }
-#pragma unroll
-                    for (int t = 0; t < MU; ++t) block(A.val + (k0 + u + t) * (BR * BC), xv[t], false);
+                    for (; u < cnt; ++u) {
+                        AT xv[BC];
+                        load(u, xv);
+                        one(u, xv);
+                    }
                 }
-                for (; u < cnt; ++u) {
-                    const int64_t c = __builtin_amdgcn_readlane(cl, u);
+            } else {
+                for (int64_t k = lo + ws * S + slot; k < hi; k += (int64_t)wpr * S) {
+                    const int64_t c = col[k];
+                    const vec_t *v = reinterpret_cast<const vec_t *>(A.val + (idx ? (int64_t)idx[k] : k) * E);
                     AT xv[BC];
 #pragma unroll
-                    for (int j = 0; j < BC; ++j) xv[j] = AT(x[(c * BC + j) * nrhs + lane]);
-                    block(A.val + (k0 + u) * (BR * BC), xv, false);
-                }
-            }
-        }
-        if constexpr (BR == BC) {
-            if (A.lptr) {
-                const int64_t llo = A.lptr[row], lhi = A.lptr[row + 1];
-                for (int64_t q0 = llo; q0 < lhi; q0 += WAVE) {
-                    const int cnt = (int)min((int64_t)WAVE, lhi - q0);
-                    const int cl = q0 + lane < lhi ? A.lcol[q0 + lane] : 0;
-                    const int il = q0 + lane < lhi ? A.lidx[q0 + lane] : 0;
-                    if (lane < nrhs) {
-                        int u = 0;
-                        for (; u + MU <= cnt; u += MU) {
-                            AT xv[MU][BC];
+                    for (int b = 0; b < BC; ++b) xv[b] = AT(x[(c * BC + b) * nrhs + jj]);
+                    VT e[E];
 #pragma unroll
-                            for (int t = 0; t < MU; ++t) {
-                                const int64_t c = __builtin_amdgcn_readlane(cl, u + t);
+                    for (int g = 0; g < E / VW; ++g) {
+                        const vec_t t = v[g];
 #pragma unroll
-                                for (int j = 0; j < BC; ++j) xv[t][j] = AT(x[(c * BC + j) * nrhs + lane]);
-                            }
-#pragma unroll
-                            for (int t = 0; t < MU; ++t)
-                                block(A.val + (int64_t)__builtin_amdgcn_readlane(il, u + t) * (BR * BC), xv[t], true);
-                        }
-                        for (; u < cnt; ++u) {
-                            const int64_t c = __builtin_amdgcn_readlane(cl, u);
-                            AT xv[BC];
-#pragma unroll
-                            for (int j = 0; j < BC; ++j) xv[j] = AT(x[(c * BC + j) * nrhs + lane]);
-                            block(A.val + (int64_t)__builtin_amdgcn_readlane(il, u) * (BR * BC), xv, true);
-                        }
+                        for (int h = 0; h < VW; ++h) e[g * VW + h] = t[h];
                     }
+#pragma unroll
+                    for (int i = 0; i < BR; ++i)
+#pragma unroll
+                        for (int b = 0; b < BC; ++b) acc[i] += AT(TR ? e[b * BC + i] : e[i * BC + b]) * xv[b];
                 }
             }
-        }
-        if (lane < nrhs) {
-            const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
-            epi.template apply_m<BR>(out, lane, nrhs, acc, red);
-        }
+        };
+        walk(A.rptr[row], A.rptr[row + 1], A.col, (const int32_t *)nullptr, std::false_type{});
+        if constexpr (BR == BC)
+            if (A.lptr) walk(A.lptr[row], A.lptr[row + 1], A.lcol, A.lidx, std::true_type{});
     }
-    if (Epi::kReduce) {
-        lds[threadIdx.x] = red;
-        __syncthreads();
-        if (threadIdx.x < WAVE && threadIdx.x < nrhs) {
-            double t = 0.0;
-            for (int w = 0; w < wpb; ++w) t += lds[w * WAVE + threadIdx.x];
-            partials[lb * nrhs + threadIdx.x] = t;
+    double red = 0.0;
+    if (S == 1 && wpr == 1) {
+        if (live && j < nrhs) {
+            const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
+            epi.template apply_m<BR>(out, j, nrhs, acc, red);
         }
+        return;
+    }
+#pragma unroll
+    for (int o = C; o < WAVE; o <<= 1)
+#pragma unroll
+        for (int i = 0; i < BR; ++i) acc[i] += __shfl_xor(acc[i], o, WAVE);
+    if (slot == 0)
+#pragma unroll
+        for (int i = 0; i < BR; ++i) buf[(wv * BR + i) * C + j] = acc[i];
+    __syncthreads();
+    if (!live) return;
+    const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
+    for (int o = ws * WAVE + lane; o < BR * C; o += wpr * WAVE) {
+        const int i = o / C, jo = o % C;
+        if (jo >= nrhs) continue;
+        AT t[1] = {AT(0)};
+        for (int w = 0; w < wpr; ++w) t[0] += buf[((grp * wpr + w) * BR + i) * C + jo];
+        epi.template apply_m<1>(out * BR + i, jo, nrhs, t, red);
     }
 }
 
@@ -403,6 +432,35 @@ static inline int64_t sell_grid(const Sell &A, int nrhs, const Tune &t) {
 
 int sell_partials_count(const Sell &A, int nrhs) { return (int)sell_grid(A, nrhs, A.tune64); }
 
+// Waves per row of k_rowm: one where the rows alone fill the device (8192
+// waves, eight per SIMD), else doubled until they do, while each wave keeps at
+// least two steps of its slots (a restriction to 96 rows of 300 blocks at 64
+// columns takes 263 us with one wave per row).
+static int rowm_waves(const Sell &A, int slots) {
+    const int64_t blocks = A.sym() ? 2 * A.nnzb - A.nrows : A.nnzb;
+    const int64_t steps = blocks / (A.nrows * slots);
+    int w = 1;
+    while (w < 16 && A.nrows * w < 8192 && steps >= 4 * w) w *= 2;
+    return w;
+}
+
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
+static void launch_rowm(const Sell &A, const VT *val, const XT *x, const Epi &epi, int nrhs, int mwpb, hipStream_t s) {
+    auto go = [&](auto kern, int c) {
+        const int wpr = rowm_waves(A, WAVE / c);
+        const int waves = c == WAVE && wpr == 1 ? mwpb : std::max(4, wpr);
+        const int64_t g = (A.nrows + waves / wpr - 1) / (waves / wpr);
+        const size_t lds = c == WAVE && wpr == 1 ? 0 : (size_t)waves * BR * c * sizeof(AT);
+        hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(waves * WAVE), lds, s, rview(A, val), x, epi, nrhs, wpr);
+    };
+    if (nrhs <= 2) go(k_rowm<BR, BC, VT, XT, AT, Epi, 2>, 2);
+    else if (nrhs <= 4) go(k_rowm<BR, BC, VT, XT, AT, Epi, 4>, 4);
+    else if (nrhs <= 8) go(k_rowm<BR, BC, VT, XT, AT, Epi, 8>, 8);
+    else if (nrhs <= 16) go(k_rowm<BR, BC, VT, XT, AT, Epi, 16>, 16);
+    else go(k_rowm<BR, BC, VT, XT, AT, Epi, 64>, 64);
+    TE_CHECK_HIP(hipGetLastError());
+}
+
 template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
 static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, int nrhs, double *partials,
                      hipStream_t s) {
@@ -414,8 +472,10 @@ static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, 
     int64_t g = sell_grid(A, nrhs, t);
     if (g == 0) return;
     const dim3 blk(64 * (nrhs == 1 ? t.wpb : t.mwpb));
+    TE_REQUIRE(A.format == (BR == 6 ? FMT_ROWWAVE : FMT_SELL), TE_EINVAL, "no %dx%d-block operator in layout %d", BR,
+               BC, A.format);
     if (nrhs == 1) {
-        if (A.format == FMT_ROWWAVE) {
+        if constexpr (BR == 6) {
             if (t.nt)
                 hipLaunchKernelGGL((k_roww<BR, BC, VT, XT, AT, Epi, true>), dim3((unsigned)g), blk, 0, s,
                                    rview(A, val), x, epi, partials, t.spw, t.remap, t.xb);
@@ -430,9 +490,11 @@ static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, 
                 hipLaunchKernelGGL((k_sell1<BR, BC, VT, XT, AT, Epi, false>), dim3((unsigned)g), blk, 0, s,
                                    view(A, val), x, epi, partials, t.spw, t.remap);
         }
-    } else if (A.format == FMT_ROWWAVE) {
-        hipLaunchKernelGGL((k_rowwm<BR, BC, VT, XT, AT, Epi>), dim3((unsigned)g), blk, 0, s, rview(A, val), x, epi,
-                           nrhs, partials, t.mwpb);
+    } else if constexpr (BR == 6) {
+        // sums over the rows are formed on the mesh level only (3-row blocks)
+        if constexpr (!Epi::kReduce) launch_rowm<BR, BC, VT, XT, AT, Epi>(A, val, x, epi, nrhs, t.mwpb, s);
+        else TE_REQUIRE(false, TE_EINVAL, "no reducing product of %dx%d blocks for several columns", BR, BC);
+        return;
     } else {
         const int R = multi_rows(nrhs, t.mtile);
         if (R == 1) {
@@ -479,7 +541,6 @@ static void dispatch(const Sell &A, const T *x, const Epi &epi, int nrhs, double
         case 66: launch_t<6, 6, T, T, T>(A, val, x, epi, nrhs, partials, s); break;
         case 36: launch_t<3, 6, T, T, T>(A, val, x, epi, nrhs, partials, s); break;
         case 63: launch_t<6, 3, T, T, T>(A, val, x, epi, nrhs, partials, s); break;
-        case 11: launch_t<1, 1, T, T, T>(A, val, x, epi, nrhs, partials, s); break;
         default: TE_REQUIRE(false, TE_EINVAL, "unsupported block shape %dx%d", A.br, A.bc);
     }
 }
