@@ -23,6 +23,7 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <numeric>
 #include <thread>
 
 #include "te_amg.h"
@@ -549,7 +550,14 @@ static int fmt_for(int br) { return br >= 6 ? FMT_ROWWAVE : FMT_SELL; }
 // Storage order, packed operator and point diagonal of a level; dnat gets
 // the diagonal in natural numbering (device) for the prolongator smoothing.
 static void finish_level(Level &L, const DBsr &D, const amg_options &o, DBuf<double> &dnat, hipStream_t s) {
-    L.perm_h = window_sorted_order(L.Ah.ptr, 4096);
+    if (fmt_for(L.bs) == FMT_SELL) {
+        L.perm_h = window_sorted_order(L.Ah.ptr, 4096);
+    } else {
+        // one wave per row needs no rows of equal length side by side; the
+        // natural order keeps a row's neighbours in x close by
+        L.perm_h.resize(L.n);
+        std::iota(L.perm_h.begin(), L.perm_h.end(), 0);
+    }
     L.iperm_h.assign(L.n, 0);
     parallel_for(L.n, [&](int64_t lo, int64_t hi, int) {
         for (int64_t i = lo; i < hi; ++i) L.iperm_h[L.perm_h[i]] = (int32_t)i;
