@@ -223,9 +223,9 @@ void permute_scatter(const double *src, double *dst, const int32_t *map, int64_t
                      hipStream_t s);  // dst[map[i]] = src[i]
 int dot_nblocks(int64_t n);
 void dot_partials(const double *a, const double *b, int64_t n, int nrhs, double *partials, hipStream_t s);
-// out[j] = sum over b of partials[b*nrhs + j], in a fixed order.  Above 4096
-// parts the sum takes two passes whose chunk sums are written after the
-// input: the buffer must then hold (nparts + min(1024, nparts/64)) * nrhs.
+// out[j] = sum over b of partials[b*nrhs + j], in a fixed order.  Long tables
+// take two passes whose chunk sums are written after the input: the buffer
+// must then hold (nparts + min(512, nparts/64)) * nrhs.
 void reduce_partials(const double *partials, int nparts, int nrhs, double *out, hipStream_t s);
 
 // Block CG kernels (te_block.hip); block vectors [rows][m], m <= 64, small
@@ -242,15 +242,16 @@ void block_gram(const double *const *mats, int nmat, const int *li, const int *r
 void block_xr(int64_t rows, int m, const double *alpha, const double *P, const double *Q, double *X, double *R,
               double *partials, hipStream_t s);
 void block_p(int64_t rows, int m, const double *T1, const double *T2, const double *Z, double *P, hipStream_t s);
-void reduce_pairs(const double *partials, int nparts, int nrhs, double *out, hipStream_t s);
+// the same sums followed by the CG bookkeeping on the device scalars S (CgScalars):
+// alpha from (p, A p); beta and rz from the interleaved pairs of dot_rz; rz at the start
+void reduce_alpha(const double *partials, int nparts, int nrhs, void *S, hipStream_t s);
+void reduce_beta(const double *partials, int nparts, int nrhs, void *S, int flexible, hipStream_t s);
+void reduce_rz0(const double *partials, int nparts, int nrhs, void *S, hipStream_t s);
 void cg_update(double *u, double *r, double *r_old, const double *p, const double *q, const double *alpha,
                int64_t rows, int nrhs, double *partials, hipStream_t s);
 void dot_rz(const double *r, const double *z, const double *r_old, int64_t rows, int nrhs, double *partials,
             hipStream_t s);
 void p_update(double *p, const double *z, const double *beta, int64_t n, int nrhs, hipStream_t s);
-void cg_alpha(void *S, const double *pq_sum, int nrhs, hipStream_t s);
-void cg_beta(void *S, const double *rzf, int nrhs, int flexible, hipStream_t s);
-void cg_rz0(void *S, const double *rzf, int nrhs, hipStream_t s);
 size_t cg_scalars_bytes();
 void copy_cols(double *r, const double *t, const int32_t *sel, int64_t n, int nrhs, hipStream_t s);
 template <typename T>

@@ -726,36 +726,77 @@ void dot_partials(const double *a, const double *b, int64_t n, int nrhs, double 
     TE_CHECK_HIP(hipGetLastError());
 }
 
-// out[j] = sum_b partials[b*nrhs + j], fixed order (thread j, sequential b).
-__global__ void k_reduce_partials(const double *__restrict__ partials, int nparts, int nrhs, double *__restrict__ out) {
-    __shared__ double lds[BLK];
-    // each column j: threads split the parts in a fixed strided way, then tree
-    for (int j = 0; j < nrhs; ++j) {
-        double t = 0.0;
-        for (int b = threadIdx.x; b < nparts; b += BLK) t += partials[(int64_t)b * nrhs + j];
-        lds[threadIdx.x] = t;
-        __syncthreads();
-        for (int o = BLK / 2; o > 0; o >>= 1) {
-            if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[j] = lds[0];
+// Column sums of a [nparts][ncols] table of partials in a fixed order, the
+// scalar bookkeeping of the CG recurrence done by the same launch.
+//   RED_STORE  out[c] = sum
+//   RED_ALPHA  sum = (p, A p): alpha = active ? rz / pq : 0; flag if pq <= 0
+//   RED_BETA   sum pairs ((r, z), (z, r - r_old)): beta; rz = (r, z); flag if <= 0
+//   RED_RZ0    sum pairs: rz; flag if <= 0
+// One workgroup: thread (r, c) adds every Rth part of its column, R the
+// largest power of two of rows that fit 1024 threads, then a tree over r.  Long
+// tables are cut to G chunks first (k_reduce_chunks, coalesced).  The former
+// one-workgroup forms walked the columns one after the other, or the chunk
+// sums in one thread per column: at 64 columns 166 us ((r, z) pairs), 84 us
+// (|r|^2) and 233 us ((p, A p)) per launch, now 8 to 15 us.
+enum { RED_STORE = 0, RED_ALPHA = 1, RED_BETA = 2, RED_RZ0 = 3 };
+constexpr int RBLK = 1024;
+
+template <int FIN>
+__global__ void __launch_bounds__(RBLK) k_reduce(const double *__restrict__ partials, int nparts, int ncols, int R,
+                                                 double *__restrict__ out, CgScalars *S, int flexible) {
+    __shared__ double lds[RBLK];
+    const int r = threadIdx.x / ncols, c = threadIdx.x % ncols;
+    double t = 0.0;
+    if (r < R)
+#pragma unroll 8
+        for (int b = r; b < nparts; b += R) t += partials[(int64_t)b * ncols + c];
+    lds[threadIdx.x] = t;
+    __syncthreads();
+    for (int o = R / 2; o > 0; o >>= 1) {
+        if (r < o) lds[threadIdx.x] += lds[threadIdx.x + o * ncols];
         __syncthreads();
     }
+    const int j = threadIdx.x;
+    if (FIN == RED_STORE) {
+        if (j < ncols) out[j] = lds[j];
+    } else if (FIN == RED_ALPHA) {
+        if (j >= ncols) return;
+        const double pq = lds[j];
+        double a = 0.0;
+        if (S->active[j]) {
+            if (!(pq > 0.0)) S->flag[j] = (pq != pq) ? 3 : 1;
+            else a = S->rz[j] / pq;
+        }
+        S->pq[j] = pq;
+        S->alpha[j] = a;
+    } else {
+        if (2 * j >= ncols) return;
+        const double rzn = lds[2 * j], fl = lds[2 * j + 1];
+        const bool bad = S->active[j] && !(rzn > 0.0);
+        if (bad) S->flag[j] = (rzn != rzn) ? 3 : 2;
+        if (FIN == RED_BETA) {
+            double b = 0.0;
+            if (S->active[j] && !bad) {
+                b = flexible ? fl / S->rz[j] : rzn / S->rz[j];
+                S->rz[j] = rzn;
+            }
+            S->beta[j] = b;
+        } else {
+            S->rz[j] = rzn;
+        }
+    }
 }
-// Many partials (one per workgroup of a sparse product): two passes.  Pass 1:
-// workgroup g sums rows [g*chunk, (g+1)*chunk) of the [nparts][ncols] table,
-// thread (row offset, column) with coalesced reads, then the row offsets in
-// order; pass 2: one thread per column adds the G chunk sums in order.
-constexpr int REDUCE_ONE_PASS = 4096;
-__global__ void __launch_bounds__(BLK) k_reduce_cols1(const double *__restrict__ partials, int nparts, int ncols,
-                                                      int chunk, double *__restrict__ out2) {
+
+// chunk sums of a long table: workgroup g adds parts [g*chunk, (g+1)*chunk)
+__global__ void __launch_bounds__(BLK) k_reduce_chunks(const double *__restrict__ partials, int nparts, int ncols,
+                                                       int chunk, double *__restrict__ out2) {
     __shared__ double lds[BLK];
     const int R = BLK / ncols;  // rows per pass
     const int r = threadIdx.x / ncols, c = threadIdx.x % ncols;
     const int lo = blockIdx.x * chunk, hi = min(nparts, lo + chunk);
     double t = 0.0;
     if (r < R)
+#pragma unroll 4
         for (int b = lo + r; b < hi; b += R) t += partials[(int64_t)b * ncols + c];
     lds[threadIdx.x] = t;
     __syncthreads();
@@ -765,31 +806,38 @@ __global__ void __launch_bounds__(BLK) k_reduce_cols1(const double *__restrict__
         out2[(int64_t)blockIdx.x * ncols + threadIdx.x] = u;
     }
 }
-__global__ void __launch_bounds__(BLK) k_reduce_cols2(const double *__restrict__ out2, int G, int ncols,
-                                                      double *__restrict__ out) {
-    for (int c = threadIdx.x; c < ncols; c += BLK) {
-        double u = 0.0;
-        for (int g = 0; g < G; ++g) u += out2[(int64_t)g * ncols + c];
-        out[c] = u;
+
+// One pass up to 64 parts per thread; above, min(512, nparts / 64) chunk sums
+// go behind the table.
+template <int FIN>
+static void reduce_fin(const double *partials, int nparts, int ncols, double *out, CgScalars *S, int flexible,
+                       hipStream_t s) {
+    TE_REQUIRE(ncols >= 1 && ncols <= 128, TE_EINVAL, "reduction over %d columns", ncols);
+    int R = 1;
+    while (2 * R * ncols <= RBLK) R *= 2;
+    if ((int64_t)nparts > (int64_t)64 * R) {
+        const int G = std::min(512, std::max(1, nparts / 64));
+        const int chunk = (nparts + G - 1) / G;
+        double *out2 = const_cast<double *>(partials) + (int64_t)nparts * ncols;
+        hipLaunchKernelGGL(k_reduce_chunks, dim3(G), dim3(BLK), 0, s, partials, nparts, ncols, chunk, out2);
+        partials = out2;
+        nparts = G;
     }
-}
-static void reduce_cols(const double *partials, int nparts, int ncols, double *out, hipStream_t s) {
-    TE_REQUIRE(ncols >= 1 && ncols <= BLK, TE_EINVAL, "reduction over %d columns", ncols);
-    const int G = std::min(1024, std::max(1, nparts / 64));
-    const int chunk = (nparts + G - 1) / G;
-    double *out2 = const_cast<double *>(partials) + (int64_t)nparts * ncols;
-    hipLaunchKernelGGL(k_reduce_cols1, dim3(G), dim3(BLK), 0, s, partials, nparts, ncols, chunk, out2);
-    hipLaunchKernelGGL(k_reduce_cols2, dim3(1), dim3(BLK), 0, s, out2, G, ncols, out);
+    hipLaunchKernelGGL(k_reduce<FIN>, dim3(1), dim3(RBLK), 0, s, partials, nparts, ncols, R, out, S, flexible);
     TE_CHECK_HIP(hipGetLastError());
 }
 
 void reduce_partials(const double *partials, int nparts, int nrhs, double *out, hipStream_t s) {
-    if (nparts > REDUCE_ONE_PASS) {
-        reduce_cols(partials, nparts, nrhs, out, s);
-        return;
-    }
-    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(BLK), 0, s, partials, nparts, nrhs, out);
-    TE_CHECK_HIP(hipGetLastError());
+    reduce_fin<RED_STORE>(partials, nparts, nrhs, out, nullptr, 0, s);
+}
+void reduce_alpha(const double *partials, int nparts, int nrhs, void *S, hipStream_t s) {
+    reduce_fin<RED_ALPHA>(partials, nparts, nrhs, nullptr, (CgScalars *)S, 0, s);
+}
+void reduce_beta(const double *partials, int nparts, int nrhs, void *S, int flexible, hipStream_t s) {
+    reduce_fin<RED_BETA>(partials, nparts, 2 * nrhs, nullptr, (CgScalars *)S, flexible, s);
+}
+void reduce_rz0(const double *partials, int nparts, int nrhs, void *S, hipStream_t s) {
+    reduce_fin<RED_RZ0>(partials, nparts, 2 * nrhs, nullptr, (CgScalars *)S, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -905,83 +953,6 @@ void p_update(double *p, const double *z, const double *beta, int64_t n, int nrh
     TE_CHECK_HIP(hipGetLastError());
 }
 
-// Scalar bookkeeping of the CG recurrence, one thread per column.
-//   alpha: pq from partials -> alpha = active ? rz/pq : 0 ; flag if pq <= 0
-//   beta:  rz_new (+ flexible term) -> beta; rz = rz_new; flag if rz_new <= 0
-__global__ void k_cg_alpha(CgScalars *S, const double *__restrict__ pq_sum, int nrhs) {
-    int j = threadIdx.x;
-    if (j >= nrhs) return;
-    double pq = pq_sum[j];
-    S->pq[j] = pq;
-    double a = 0.0;
-    if (S->active[j]) {
-        if (!(pq > 0.0)) {
-            S->flag[j] = (pq != pq) ? 3 : 1;
-        } else {
-            a = S->rz[j] / pq;
-        }
-    }
-    S->alpha[j] = a;
-}
-__global__ void k_cg_beta(CgScalars *S, const double *__restrict__ rzf, int nrhs, int flexible) {
-    int j = threadIdx.x;
-    if (j >= nrhs) return;
-    double rzn = rzf[2 * j], fl = rzf[2 * j + 1];
-    double b = 0.0;
-    if (S->active[j]) {
-        if (!(rzn > 0.0)) {
-            S->flag[j] = (rzn != rzn) ? 3 : 2;
-        } else {
-            b = flexible ? fl / S->rz[j] : rzn / S->rz[j];
-            S->rz[j] = rzn;
-        }
-    }
-    S->beta[j] = b;
-}
-__global__ void k_cg_rz0(CgScalars *S, const double *__restrict__ rzf, int nrhs) {
-    int j = threadIdx.x;
-    if (j >= nrhs) return;
-    double rzn = rzf[2 * j];
-    if (S->active[j] && !(rzn > 0.0)) S->flag[j] = (rzn != rzn) ? 3 : 2;
-    S->rz[j] = rzn;
-}
-// reduce interleaved (rz, flex) partial pairs
-__global__ void k_reduce_pairs(const double *__restrict__ partials, int nparts, int nrhs, double *__restrict__ out) {
-    __shared__ double lds[BLK];
-    for (int jj = 0; jj < 2 * nrhs; ++jj) {
-        double t = 0.0;
-        for (int b = threadIdx.x; b < nparts; b += BLK) t += partials[(int64_t)b * 2 * nrhs + jj];
-        lds[threadIdx.x] = t;
-        __syncthreads();
-        for (int o = BLK / 2; o > 0; o >>= 1) {
-            if (threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[jj] = lds[0];
-        __syncthreads();
-    }
-}
-
-void cg_alpha(void *S, const double *pq_sum, int nrhs, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(64), 0, s, (CgScalars *)S, pq_sum, nrhs);
-    TE_CHECK_HIP(hipGetLastError());
-}
-void cg_beta(void *S, const double *rzf, int nrhs, int flexible, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(64), 0, s, (CgScalars *)S, rzf, nrhs, flexible);
-    TE_CHECK_HIP(hipGetLastError());
-}
-void cg_rz0(void *S, const double *rzf, int nrhs, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_rz0, dim3(1), dim3(64), 0, s, (CgScalars *)S, rzf, nrhs);
-    TE_CHECK_HIP(hipGetLastError());
-}
-void reduce_pairs(const double *partials, int nparts, int nrhs, double *out, hipStream_t s) {
-    if (nparts > REDUCE_ONE_PASS) {
-        reduce_cols(partials, nparts, 2 * nrhs, out, s);
-        return;
-    }
-    hipLaunchKernelGGL(k_reduce_pairs, dim3(1), dim3(BLK), 0, s, partials, nparts, nrhs, out);
-    TE_CHECK_HIP(hipGetLastError());
-}
 size_t cg_scalars_bytes() { return sizeof(CgScalars); }
 
 // Column select: r[:, j] = t[:, j] where sel[j] != 0

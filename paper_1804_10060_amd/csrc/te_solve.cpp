@@ -536,8 +536,7 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
         // zero-guess columns that are already converged stay untouched (alpha = 0)
         precondition(h, h->r.p, h->z.p, m, mixed, s);
         dot_rz(h->r.p, h->z.p, nullptr, rows, m, part, s);
-        reduce_pairs(part, dot_nblocks(rows), m, sums, s);
-        cg_rz0(S, sums, m, s);
+        reduce_rz0(part, dot_nblocks(rows), m, S, s);
         TE_CHECK_HIP(hipMemcpyAsync(h->p.p, h->z.p, nv * sizeof(double), hipMemcpyDeviceToDevice, s));
         TE_CHECK_HIP(hipMemcpyAsync(flags.data(), S->flag, 64 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
         TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -554,8 +553,7 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
         sell_dot(cg_operator(h), h->p.p, h->q.p, m, part, s);
         h->prof.end(TE_K_AP);
         h->prof.begin(TE_K_VECTOR);
-        reduce_partials(part, sell_partials_count(cg_operator(h), m), m, sums, s);
-        cg_alpha(S, sums, m, s);
+        reduce_alpha(part, sell_partials_count(cg_operator(h), m), m, S, s);
         cg_update(h->u.p, h->r.p, mixed ? h->r_old.p : nullptr, h->p.p, h->q.p, S->alpha, rows, m, part, s);
         reduce_partials(part, dot_nblocks(rows), m, sums, s);
         h->prof.end(TE_K_VECTOR);
@@ -611,8 +609,7 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
         precondition(h, h->r.p, h->z.p, m, mixed, s);
         h->prof.begin(TE_K_VECTOR);
         dot_rz(h->r.p, h->z.p, mixed ? h->r_old.p : nullptr, rows, m, part, s);
-        reduce_pairs(part, dot_nblocks(rows), m, sums, s);
-        cg_beta(S, sums, m, mixed ? 1 : 0, s);
+        reduce_beta(part, dot_nblocks(rows), m, S, mixed ? 1 : 0, s);
         p_update(h->p.p, h->z.p, S->beta, nv, m, s);
         h->prof.end(TE_K_VECTOR);
     }
