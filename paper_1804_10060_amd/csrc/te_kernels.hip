@@ -683,46 +683,74 @@ int dot_nblocks(int64_t n) {
     return (int)(g < 1 ? 1 : (g > DOT_BLOCKS ? DOT_BLOCKS : g));
 }
 
-// Single column: block b sums a contiguous chunk in a fixed order.
-__global__ void k_dot1(const double *__restrict__ a, const double *__restrict__ b, int64_t n,
-                       double *__restrict__ partials) {
-    __shared__ double lds[WPB];
-    const int64_t nb = gridDim.x;
-    const int64_t chunk = (n + nb - 1) / nb;
-    const int64_t lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double t = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += BLK) t += a[i] * b[i];
-    t = block_sum(t, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
-}
+// The vector kernels below give every workgroup a contiguous chunk of rows and
+// every thread entries of one column only: the first 256 / nrhs * nrhs threads
+// walk the chunk's entries in turn (column = thread % nrhs), so few columns
+// leave no lane without work (a lane per column measured 66 us for the CG
+// update at 5 columns on 287,000 rows, now 14), four entries in flight.
+// The threads of a column are then added in a fixed order.
+constexpr int VU = 4;
 
-// Several columns (layout [rows][nrhs]): lane = column, waves over rows.
-__global__ void k_dotm(const double *__restrict__ a, const double *__restrict__ b, int64_t rows, int nrhs,
-                       double *__restrict__ partials) {
-    __shared__ double lds[BLK];
-    const int64_t nb = gridDim.x;
-    const int64_t chunk = (rows + nb - 1) / nb;
-    const int64_t lo = blockIdx.x * chunk, hi = min(rows, lo + chunk);
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-    double t = 0.0;
-    if (lane < nrhs)
-        for (int64_t i = lo + w; i < hi; i += WPB) t += a[i * nrhs + lane] * b[i * nrhs + lane];
-    lds[threadIdx.x] = t;
+// sums of NV values per column over the workgroup, out[c * NV + v]
+template <int NV>
+__device__ __forceinline__ void column_sums(const double (&t)[NV], int nrhs, double *__restrict__ out) {
+    __shared__ double lds[NV][BLK];
+    if (nrhs == 1) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const double s = block_sum(t[v], lds[v]);
+            if (threadIdx.x == 0) out[v] = s;
+        }
+        return;
+    }
+    const int per = BLK / nrhs;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) lds[v][threadIdx.x] = t[v];
     __syncthreads();
-    if (threadIdx.x < nrhs) {
+    for (int e = threadIdx.x; e < NV * nrhs; e += BLK) {
+        const int c = e / NV, v = e % NV;
         double s = 0.0;
-        for (int k = 0; k < WPB; ++k) s += lds[k * WAVE + threadIdx.x];
-        partials[blockIdx.x * (int64_t)nrhs + threadIdx.x] = s;
+        for (int k = 0; k < per; ++k) s += lds[v][k * nrhs + c];
+        out[e] = s;
     }
 }
 
+// f(i, act, cnt): entries i, i + act, ... (cnt of them, VU or 1) of this
+// workgroup's chunk, in the thread's column
+template <class F>
+__device__ __forceinline__ void chunk_entries(int64_t rows, int nrhs, F f) {
+    const int64_t chunk = (rows + gridDim.x - 1) / gridDim.x;
+    const int64_t lo = blockIdx.x * chunk * nrhs, hi = min(rows, (blockIdx.x + 1) * chunk) * nrhs;
+    const int act = BLK / nrhs * nrhs;
+    if ((int)threadIdx.x >= act) return;
+    int64_t i = lo + threadIdx.x;
+    for (; i + (int64_t)(VU - 1) * act < hi; i += (int64_t)VU * act) f(i, act, VU);
+    for (; i < hi; i += act) f(i, act, 1);
+}
+
+__global__ void __launch_bounds__(BLK) k_dot(const double *__restrict__ a, const double *__restrict__ b, int64_t rows,
+                                             int nrhs, double *__restrict__ partials) {
+    double t[1] = {0.0};
+    chunk_entries(rows, nrhs, [&](int64_t i, int act, int cnt) {
+        if (cnt == VU) {
+            double x[VU], y[VU];
+#pragma unroll
+            for (int u = 0; u < VU; ++u) {
+                x[u] = a[i + (int64_t)u * act];
+                y[u] = b[i + (int64_t)u * act];
+            }
+#pragma unroll
+            for (int u = 0; u < VU; ++u) t[0] += x[u] * y[u];
+        } else {
+            t[0] += a[i] * b[i];
+        }
+    });
+    column_sums<1>(t, nrhs, partials + blockIdx.x * (int64_t)nrhs);
+}
+
 void dot_partials(const double *a, const double *b, int64_t n, int nrhs, double *partials, hipStream_t s) {
-    int64_t rows = n / nrhs;
-    int nb = dot_nblocks(rows);
-    if (nrhs == 1)
-        hipLaunchKernelGGL(k_dot1, dim3(nb), dim3(BLK), 0, s, a, b, n, partials);
-    else
-        hipLaunchKernelGGL(k_dotm, dim3(nb), dim3(BLK), 0, s, a, b, rows, nrhs, partials);
+    const int64_t rows = n / nrhs;
+    hipLaunchKernelGGL(k_dot, dim3(dot_nblocks(rows)), dim3(BLK), 0, s, a, b, rows, nrhs, partials);
     TE_CHECK_HIP(hipGetLastError());
 }
 
@@ -844,101 +872,80 @@ void reduce_rz0(const double *partials, int nparts, int nrhs, void *S, hipStream
 // CG vector updates (float64), per-column scalars on the device
 // ---------------------------------------------------------------------------
 // u += alpha_j p; r_old = r (if keep_old); r -= alpha_j q; red_j += r^2
-__global__ void k_cg_update(double *__restrict__ u, double *__restrict__ r, double *__restrict__ r_old,
-                            const double *__restrict__ p, const double *__restrict__ q, const double *__restrict__ alpha,
-                            int64_t rows, int nrhs, double *__restrict__ partials) {
-    __shared__ double lds[BLK];
-    const int64_t nb = gridDim.x;
-    const int64_t chunk = (rows + nb - 1) / nb;
-    const int64_t lo = blockIdx.x * chunk, hi = min(rows, lo + chunk);
-    if (nrhs == 1) {
-        const double a = alpha[0];
-        double t = 0.0;
-        for (int64_t i = lo + threadIdx.x; i < hi; i += BLK) {
-            u[i] += a * p[i];
-            double rv = r[i];
-            if (r_old) r_old[i] = rv;
-            rv -= a * q[i];
-            r[i] = rv;
-            t += rv * rv;
-        }
-        t = block_sum(t, lds);
-        if (threadIdx.x == 0) partials[blockIdx.x] = t;
-        return;
-    }
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-    double t = 0.0;
-    if (lane < nrhs) {
-        const double a = alpha[lane];
-        for (int64_t i = lo + w; i < hi; i += WPB) {
-            int64_t k = i * nrhs + lane;
-            u[k] += a * p[k];
-            double rv = r[k];
-            if (r_old) r_old[k] = rv;
-            rv -= a * q[k];
-            r[k] = rv;
-            t += rv * rv;
-        }
-    }
-    lds[threadIdx.x] = t;
-    __syncthreads();
-    if (threadIdx.x < nrhs) {
-        double s = 0.0;
-        for (int k = 0; k < WPB; ++k) s += lds[k * WAVE + threadIdx.x];
-        partials[blockIdx.x * (int64_t)nrhs + threadIdx.x] = s;
-    }
+template <bool OLD>
+__global__ void __launch_bounds__(BLK) k_cg_update(double *__restrict__ u, double *__restrict__ r,
+                                                   double *__restrict__ r_old, const double *__restrict__ p,
+                                                   const double *__restrict__ q, const double *__restrict__ alpha,
+                                                   int64_t rows, int nrhs, double *__restrict__ partials) {
+    double t[1] = {0.0};
+    const double a = alpha[nrhs == 1 ? 0 : threadIdx.x % nrhs];
+    chunk_entries(rows, nrhs, [&](int64_t i0, int act, int cnt) {
+        auto part = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            double uv[N], pv[N], rv[N], qv[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const int64_t i = i0 + (int64_t)k * act;
+                uv[k] = u[i];
+                pv[k] = p[i];
+                rv[k] = r[i];
+                qv[k] = q[i];
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const int64_t i = i0 + (int64_t)k * act;
+                u[i] = uv[k] + a * pv[k];
+                if (OLD) r_old[i] = rv[k];
+                const double rn = rv[k] - a * qv[k];
+                r[i] = rn;
+                t[0] += rn * rn;
+            }
+        };
+        if (cnt == VU) part(std::integral_constant<int, VU>{});
+        else part(std::integral_constant<int, 1>{});
+    });
+    column_sums<1>(t, nrhs, partials + blockIdx.x * (int64_t)nrhs);
 }
 void cg_update(double *u, double *r, double *r_old, const double *p, const double *q, const double *alpha,
                int64_t rows, int nrhs, double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(k_cg_update, dim3(dot_nblocks(rows)), dim3(BLK), 0, s, u, r, r_old, p, q, alpha, rows, nrhs,
+    auto kern = r_old ? k_cg_update<true> : k_cg_update<false>;
+    hipLaunchKernelGGL(kern, dim3(dot_nblocks(rows)), dim3(BLK), 0, s, u, r, r_old, p, q, alpha, rows, nrhs,
                        partials);
     TE_CHECK_HIP(hipGetLastError());
 }
 
 // (r, z) and, for the flexible variant, (z, r - r_old) per column
-__global__ void k_dot_rz(const double *__restrict__ r, const double *__restrict__ z, const double *__restrict__ r_old,
-                         int64_t rows, int nrhs, double *__restrict__ partials) {
-    __shared__ double lds[2 * BLK];
-    const int64_t nb = gridDim.x;
-    const int64_t chunk = (rows + nb - 1) / nb;
-    const int64_t lo = blockIdx.x * chunk, hi = min(rows, lo + chunk);
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-    double t = 0.0, f = 0.0;
-    if (nrhs == 1) {
-        for (int64_t i = lo + threadIdx.x; i < hi; i += BLK) {
-            t += r[i] * z[i];
-            if (r_old) f += z[i] * (r[i] - r_old[i]);
-        }
-        double a = block_sum(t, lds);
-        double b = block_sum(f, lds + WPB);
-        if (threadIdx.x == 0) {
-            partials[2 * blockIdx.x] = a;
-            partials[2 * blockIdx.x + 1] = b;
-        }
-        return;
-    }
-    if (lane < nrhs)
-        for (int64_t i = lo + w; i < hi; i += WPB) {
-            int64_t k = i * nrhs + lane;
-            t += r[k] * z[k];
-            if (r_old) f += z[k] * (r[k] - r_old[k]);
-        }
-    lds[threadIdx.x] = t;
-    lds[BLK + threadIdx.x] = f;
-    __syncthreads();
-    if (threadIdx.x < nrhs) {
-        double s1 = 0.0, s2 = 0.0;
-        for (int k = 0; k < WPB; ++k) {
-            s1 += lds[k * WAVE + threadIdx.x];
-            s2 += lds[BLK + k * WAVE + threadIdx.x];
-        }
-        partials[(blockIdx.x * (int64_t)nrhs + threadIdx.x) * 2] = s1;
-        partials[(blockIdx.x * (int64_t)nrhs + threadIdx.x) * 2 + 1] = s2;
-    }
+template <bool OLD>
+__global__ void __launch_bounds__(BLK) k_dot_rz(const double *__restrict__ r, const double *__restrict__ z,
+                                                const double *__restrict__ r_old, int64_t rows, int nrhs,
+                                                double *__restrict__ partials) {
+    double t[2] = {0.0, 0.0};
+    chunk_entries(rows, nrhs, [&](int64_t i0, int act, int cnt) {
+        auto part = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            double rv[N], zv[N], ov[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const int64_t i = i0 + (int64_t)k * act;
+                rv[k] = r[i];
+                zv[k] = z[i];
+                ov[k] = OLD ? r_old[i] : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                t[0] += rv[k] * zv[k];
+                if (OLD) t[1] += zv[k] * (rv[k] - ov[k]);
+            }
+        };
+        if (cnt == VU) part(std::integral_constant<int, VU>{});
+        else part(std::integral_constant<int, 1>{});
+    });
+    column_sums<2>(t, nrhs, partials + blockIdx.x * (int64_t)nrhs * 2);
 }
 void dot_rz(const double *r, const double *z, const double *r_old, int64_t rows, int nrhs, double *partials,
             hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_rz, dim3(dot_nblocks(rows)), dim3(BLK), 0, s, r, z, r_old, rows, nrhs, partials);
+    auto kern = r_old ? k_dot_rz<true> : k_dot_rz<false>;
+    hipLaunchKernelGGL(kern, dim3(dot_nblocks(rows)), dim3(BLK), 0, s, r, z, r_old, rows, nrhs, partials);
     TE_CHECK_HIP(hipGetLastError());
 }
 
@@ -969,29 +976,96 @@ void copy_cols(double *r, const double *t, const int32_t *sel, int64_t n, int nr
 // ---------------------------------------------------------------------------
 // Dense coarse solve: y = Ainv x (Ainv symmetric n x n, float64)
 // ---------------------------------------------------------------------------
+// One column: one wave per row, the row's entries in pairs (16-byte loads when
+// the rows start on 16 bytes: n even), four pairs per lane in flight (one entry
+// at a time: 17 us at n = 2800, now 11).
 template <typename T>
 __global__ void __launch_bounds__(BLK) k_dense_mv(const double *__restrict__ Ainv, const T *__restrict__ x,
-                                                  T *__restrict__ y, int n, int nrhs) {
+                                                  T *__restrict__ y, int n) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = (int64_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * WPB + threadIdx.x / WAVE));
     if (row >= n) return;
     const double *a = Ainv + row * (int64_t)n;
-    if (nrhs == 1) {
-        double t = 0.0;
-        for (int j = lane; j < n; j += WAVE) t += a[j] * double(x[j]);
-        t = wave_sum(t);
-        if (lane == 0) y[row] = T(t);
-        return;
-    }
-    if (lane >= nrhs) return;
+    typedef double d2 __attribute__((ext_vector_type(2)));
     double t = 0.0;
-    for (int j = 0; j < n; ++j) t += a[j] * double(x[(int64_t)j * nrhs + lane]);
-    y[row * nrhs + lane] = T(t);
+    if ((n & 1) == 0) {
+        const d2 *a2 = reinterpret_cast<const d2 *>(a);
+#pragma unroll 4
+        for (int j = lane; j < n / 2; j += WAVE) {
+            const d2 v = a2[j];
+            t += v[0] * double(x[2 * j]) + v[1] * double(x[2 * j + 1]);
+        }
+    } else {
+#pragma unroll 4
+        for (int j = lane; j < n; j += WAVE) t += a[j] * double(x[j]);
+    }
+    t = wave_sum(t);
+    if (lane == 0) y[row] = T(t);
+}
+
+// Several columns: y[16 rows][nrhs] per workgroup on the float64 matrix cores
+// (v_mfma_f64_16x16x4, column tiles of 16).  The eight waves take every eighth
+// step of eight inner indices (lane (q, i): entries 8 s + 2 q and + 1 of row i
+// and of column i's vector) and add their tiles in order through LDS.  One
+// wave per row with a lane per column walked n inner indices serially: 139 us
+// at n = 570 (64 columns), 32 us at n = 738 (5 columns); now 11 and 5 us.
+constexpr int DW = 8;   // waves
+template <typename T, int NT>
+__global__ void __launch_bounds__(DW *WAVE) k_dense_mm(const double *__restrict__ Ainv, const T *__restrict__ x,
+                                                       T *__restrict__ y, int n, int nrhs) {
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    __shared__ double part[DW][16][16 * NT];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, i = lane & 15, q = lane >> 4;
+    const int r0 = blockIdx.x * 16;
+    const double *a = Ainv + (int64_t)min(r0 + i, n - 1) * n;   // a spare row repeats the last, and is not stored
+    d4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int k0 = 8 * w; k0 < n; k0 += 8 * DW) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k0 + 2 * q + h;
+            const bool ok = k < n;
+            const int kk = ok ? k : n - 1;
+            const double av = a[kk];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const double xv = double(x[(int64_t)kk * nrhs + min(16 * t + i, nrhs - 1)]);
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ok ? av : 0.0, ok ? xv : 0.0, acc[t], 0, 0, 0);
+            }
+        }
+    }
+    // register r of lane (q, i) is row 4 r + q, column i of the tile
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[w][4 * r + q][16 * t + i] = acc[t][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * 16 * NT; e += DW * WAVE) {
+        const int r = e / (16 * NT), c = e % (16 * NT);
+        if (r0 + r >= n || c >= nrhs) continue;
+        double s = 0.0;
+#pragma unroll
+        for (int v = 0; v < DW; ++v) s += part[v][r][c];
+        y[(int64_t)(r0 + r) * nrhs + c] = T(s);
+    }
 }
 template <typename T>
 void dense_mv(const double *Ainv, const T *x, T *y, int n, int nrhs, hipStream_t s) {
     if (n == 0) return;
-    hipLaunchKernelGGL(k_dense_mv<T>, dim3((n + WPB - 1) / WPB), dim3(BLK), 0, s, Ainv, x, y, n, nrhs);
+    const dim3 g((n + 15) / 16), b(DW * WAVE);
+    TE_REQUIRE(nrhs >= 1 && nrhs <= 64, TE_EINVAL, "dense product with %d columns", nrhs);
+    if (nrhs == 1)
+        hipLaunchKernelGGL(k_dense_mv<T>, dim3((n + WPB - 1) / WPB), dim3(BLK), 0, s, Ainv, x, y, n);
+    else if (nrhs <= 16)
+        hipLaunchKernelGGL((k_dense_mm<T, 1>), g, b, 0, s, Ainv, x, y, n, nrhs);
+    else if (nrhs <= 32)
+        hipLaunchKernelGGL((k_dense_mm<T, 2>), g, b, 0, s, Ainv, x, y, n, nrhs);
+    else if (nrhs <= 48)
+        hipLaunchKernelGGL((k_dense_mm<T, 3>), g, b, 0, s, Ainv, x, y, n, nrhs);
+    else
+        hipLaunchKernelGGL((k_dense_mm<T, 4>), g, b, 0, s, Ainv, x, y, n, nrhs);
     TE_CHECK_HIP(hipGetLastError());
 }
 template void dense_mv<double>(const double *, const double *, double *, int, int, hipStream_t);
