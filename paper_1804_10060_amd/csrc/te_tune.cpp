@@ -152,6 +152,7 @@ void tune_one(Sell &A, Tune &slot, const char *dtype, const T *x, T *y, std::map
             return;
         }
     }
+    const Tune def = slot;   // the operator's untuned configuration
     Tune best;
     float best_t = INFINITY, def_t = 0.f;
     // the shared x entries exist for one wave per row (blocks no wider than tall)
@@ -164,7 +165,8 @@ void tune_one(Sell &A, Tune &slot, const char *dtype, const T *x, T *y, std::map
                         Tune c{wpb, spw, remap, nt};
                         c.xb = xb;
                         const float t = time_op<T>(A, slot, c, x, y, s, e0, e1);
-                        if (wpb == 4 && spw == 1 && remap == 1 && nt == 0 && xb == 0) def_t = t;
+                        if (wpb == def.wpb && spw == def.spw && remap == def.remap && nt == def.nt && xb == def.xb)
+                            def_t = t;
                         if (t < best_t) {
                             best_t = t;
                             best = c;
