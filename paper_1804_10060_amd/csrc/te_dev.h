@@ -153,6 +153,46 @@ __device__ __forceinline__ void sell1_body(const SellView<VT> &A, const XT *__re
     if (real) epi.template apply<BR>(out, acc, red, pre);
 }
 
+// One slice by W waves of a workgroup: wave w takes the entries w, w + W, ...
+// of every row, the partial sums meet in LDS (buf: [W][BR][64]) and wave 0 adds
+// them in wave order and runs the epilogue, whose inputs it has loaded before
+// the entries.  Every wave of the workgroup must call this.
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, bool NT = false>
+__device__ __forceinline__ void sell1_split(const SellView<VT> &A, const XT *__restrict__ x, const Epi &epi,
+                                            int64_t slice, int lane, int w, int W, AT *__restrict__ buf, double &red) {
+    const int64_t row = slice * WAVE + lane;
+    const int off = A.slice_off[slice];
+    const int width = A.slice_off[slice + 1] - off;
+    const int len = A.rowlen[row];
+    const int kmin = __builtin_amdgcn_readlane(len, WAVE - 1);
+    const bool real = row < A.nrows;
+    const int64_t out = real ? (A.rowmap ? (int64_t)A.rowmap[row] : row) : 0;
+    typename Epi::template Pre<BR> pre{};
+    if (real && w == 0) pre = epi.template load<BR>(out);
+    AT acc[BR];
+#pragma unroll
+    for (int i = 0; i < BR; ++i) acc[i] = AT(0);
+    const int32_t *cp = A.col + (int64_t)off * WAVE + lane;
+    const VT *vp = A.val + (int64_t)off * (BR * BC * WAVE);
+    int k = w;
+    for (; k + W < kmin; k += 2 * W) {
+        sell1_entry<BR, BC, VT, XT, AT, NT>(cp, vp, k, lane, x, acc);
+        sell1_entry<BR, BC, VT, XT, AT, NT>(cp, vp, k + W, lane, x, acc);
+    }
+    for (; k < width; k += W)
+        if (k < len) sell1_entry<BR, BC, VT, XT, AT, NT>(cp, vp, k, lane, x, acc);
+    if (w > 0)
+#pragma unroll
+        for (int i = 0; i < BR; ++i) buf[(w * BR + i) * WAVE + lane] = acc[i];
+    __syncthreads();
+    if (w == 0 && real) {
+        for (int v = 1; v < W; ++v)
+#pragma unroll
+            for (int i = 0; i < BR; ++i) acc[i] += buf[(v * BR + i) * WAVE + lane];
+        epi.template apply<BR>(out, acc, red, pre);
+    }
+}
+
 // One wave per stored row (format 1).  Lane = (block slot, row of the block):
 // with NB = 64 / BR slots, a wave consumes NB consecutive blocks per step,
 // i.e. one contiguous run of NB*BR*BC values, each lane reading the BC
@@ -208,16 +248,19 @@ __device__ __forceinline__ float lane_bperm(int src, float v) {
 // XB (BC <= BR): the first BC lanes of a slot load one x entry each of the
 // block column and pass them round by lane_bperm, instead of every lane
 // loading all BC (the same values, so the same result bit for bit).
-template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, bool NT = false, bool XB = false>
-__device__ __forceinline__ void roww_body(const RowView<VT> &A, const XT *__restrict__ x, const Epi &epi, int64_t row,
-                                          int lane, double &red, AT *__restrict__ wbuf) {
+// The sum of one lane's entries of a row; with W > 1 waves on the row, wave w
+// takes every Wth step of NB blocks.
+template <int BR, int BC, typename VT, typename XT, typename AT, bool NT = false, bool XB = false>
+__device__ __forceinline__ AT roww_sum(const RowView<VT> &A, const XT *__restrict__ x, int64_t row, int lane, int w = 0,
+                                       int W = 1) {
     static_assert(!XB || BC <= BR, "x exchange needs BC <= BR");
-    constexpr int NB = WAVE / BR, U = roww_batch<BC>();
+    constexpr int NB0 = WAVE / BR, U = roww_batch<BC>();
     const int slot = lane / BR, i = lane % BR;
+    const int NB = NB0 * W;   // blocks per step of all the row's waves
     AT acc = AT(0);
-    if (slot < NB) {
+    if (slot < NB0) {
         const int64_t hi = A.rptr[row + 1];
-        const int64_t k0 = A.rptr[row] + slot;
+        const int64_t k0 = A.rptr[row] + w * NB0 + slot;
         // an entry past the row reads the slot's first entry and is not added
         int64_t cc[U];
 #pragma unroll
@@ -263,7 +306,7 @@ __device__ __forceinline__ void roww_body(const RowView<VT> &A, const XT *__rest
                 // mirror; the (column, mirror) pairs of the next batch are
                 // loaded one batch ahead
                 const int64_t lhi = A.lptr[row + 1];
-                const int64_t q0 = A.lptr[row] + slot;
+                const int64_t q0 = A.lptr[row] + w * NB0 + slot;
                 int64_t lc[U], li[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -309,7 +352,14 @@ __device__ __forceinline__ void roww_body(const RowView<VT> &A, const XT *__rest
             }
         }
     }
-    wbuf[lane] = acc;
+    return acc;
+}
+
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, bool NT = false, bool XB = false>
+__device__ __forceinline__ void roww_body(const RowView<VT> &A, const XT *__restrict__ x, const Epi &epi, int64_t row,
+                                          int lane, double &red, AT *__restrict__ wbuf) {
+    constexpr int NB = WAVE / BR;
+    wbuf[lane] = roww_sum<BR, BC, VT, XT, AT, NT, XB>(A, x, row, lane);
     wave_lds_sync();
     if (lane < BR) {
         AT t[1] = {AT(0)};

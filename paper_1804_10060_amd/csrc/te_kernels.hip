@@ -46,6 +46,24 @@ __global__ void __launch_bounds__(512) k_sell1(SellView<VT> A, const XT *__restr
     }
 }
 
+// Single right-hand side on an operator of too few slices to fill the device
+// (sell_split): a workgroup of W waves per slice, XCD-contiguous.
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, bool NT>
+__global__ void __launch_bounds__(512) k_sell1s(SellView<VT> A, const XT *__restrict__ x, Epi epi,
+                                                double *__restrict__ partials) {
+    __shared__ AT buf[8 * BR * WAVE];
+    __shared__ double lds[16];
+    const int64_t slice = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int lane = threadIdx.x & (WAVE - 1), W = blockDim.x / WAVE;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    double red = 0.0;
+    sell1_split<BR, BC, VT, XT, AT, Epi, NT>(A, x, epi, slice, lane, w, W, buf, red);
+    if (Epi::kReduce) {
+        const double t = block_sum(red, lds);   // waves past the first add zero
+        if (threadIdx.x == 0) partials[slice] = t;
+    }
+}
+
 // Several right-hand sides on the SELL layout, one wave per block row with
 // the right-hand sides on the lanes (at most 64); the block values are
 // wave-uniform (scalar loads), the row's column indices come 64 at a time
@@ -270,6 +288,35 @@ __global__ void __launch_bounds__(512) k_roww(RowView<VT> A, const XT *__restric
     }
 }
 
+// Few long rows (roww_split): a workgroup of W waves per row, the partial sums
+// added slot by slot in wave order.
+template <int BR, int BC, typename VT, typename XT, typename AT, class Epi, bool NT>
+__global__ void __launch_bounds__(512) k_rowws(RowView<VT> A, const XT *__restrict__ x, Epi epi,
+                                               double *__restrict__ partials, int xb) {
+    constexpr int NB = WAVE / BR;
+    __shared__ AT wb[512];
+    __shared__ double rlds[16];
+    const int64_t row = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int lane = threadIdx.x & (WAVE - 1), W = blockDim.x / WAVE;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    wb[threadIdx.x] = xb ? roww_sum<BR, BC, VT, XT, AT, NT, true>(A, x, row, lane, w, W)
+                         : roww_sum<BR, BC, VT, XT, AT, NT>(A, x, row, lane, w, W);
+    __syncthreads();
+    double red = 0.0;
+    if (threadIdx.x < BR) {
+        AT t[1] = {AT(0)};
+        for (int v = 0; v < W; ++v)
+#pragma unroll
+            for (int sl = 0; sl < NB; ++sl) t[0] += wb[v * WAVE + sl * BR + threadIdx.x];
+        const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
+        epi.template apply<1>(out * BR + threadIdx.x, t, red);
+    }
+    if (Epi::kReduce) {
+        const double t = block_sum(red, rlds);
+        if (threadIdx.x == 0) partials[row] = t;
+    }
+}
+
 // Format 1 with several right-hand sides.  A wave takes S = 64 / C entries of
 // a row at once: lane (slot, column), C the power of two that holds the
 // columns (so up to 32 columns leave no lane without work); wpr waves share a
@@ -420,8 +467,27 @@ static inline int multi_cols(int nrhs, int mtile) {
     return s >= 4 ? 4 : (s >= 2 ? 2 : 1);
 }
 
+// Waves per slice (SELL) or row (one wave per row) of the single-RHS products.
+// An operator whose slices or rows leave the device's wave slots empty (4096
+// at four waves of the float64 product per SIMD) takes more waves for each,
+// while every wave keeps three entries of a lane's row, or two steps of its
+// row's blocks.  The operator alone decides, so the sums do not depend on the
+// tuned launch shape.  Products of 1115 slices of 27 blocks (the
+// 214,000-DOF P2 disc) 0.056 -> 0.027 ms, restriction to 155 rows of 122
+// blocks 9.6 -> 6.4 us, the 77 slices of the 14,739-DOF cube 8 -> 5 us.
+static int launch_split(const Sell &A) {
+    const int64_t units = A.format == FMT_SELL ? A.nslices : A.nrows;
+    if (units == 0) return 1;
+    const int64_t blocks = A.sym() ? 2 * A.nnzb - A.nrows : A.nnzb;
+    const int64_t steps = A.format == FMT_SELL ? blocks / (3 * A.nrows) : blocks / (2 * (WAVE / A.br) * A.nrows);
+    int w = 1;
+    while (w < 8 && units * w < 4096 && 2 * w <= steps) w *= 2;
+    return w;
+}
+
 static inline int64_t sell_grid(const Sell &A, int nrhs, const Tune &t) {
     if (nrhs == 1) {
+        if (launch_split(A) > 1) return A.format == FMT_SELL ? A.nslices : A.nrows;
         const int64_t units = A.format == FMT_SELL ? A.nslices : A.nrows;
         const int64_t per = (int64_t)t.wpb * t.spw;
         return (units + per - 1) / per;
@@ -474,7 +540,20 @@ static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, 
     const dim3 blk(64 * (nrhs == 1 ? t.wpb : t.mwpb));
     TE_REQUIRE(A.format == (BR == 6 ? FMT_ROWWAVE : FMT_SELL), TE_EINVAL, "no %dx%d-block operator in layout %d", BR,
                BC, A.format);
-    if (nrhs == 1) {
+    if (const int split = nrhs == 1 ? launch_split(A) : 1; split > 1) {
+        const dim3 gs((unsigned)g), bs(WAVE * split);
+        if constexpr (BR == 6) {
+            if (t.nt) hipLaunchKernelGGL((k_rowws<BR, BC, VT, XT, AT, Epi, true>), gs, bs, 0, s, rview(A, val), x, epi,
+                                         partials, t.xb);
+            else hipLaunchKernelGGL((k_rowws<BR, BC, VT, XT, AT, Epi, false>), gs, bs, 0, s, rview(A, val), x, epi,
+                                    partials, t.xb);
+        } else {
+            if (t.nt) hipLaunchKernelGGL((k_sell1s<BR, BC, VT, XT, AT, Epi, true>), gs, bs, 0, s, view(A, val), x,
+                                         epi, partials);
+            else hipLaunchKernelGGL((k_sell1s<BR, BC, VT, XT, AT, Epi, false>), gs, bs, 0, s, view(A, val), x, epi,
+                                    partials);
+        }
+    } else if (nrhs == 1) {
         if constexpr (BR == 6) {
             if (t.nt)
                 hipLaunchKernelGGL((k_roww<BR, BC, VT, XT, AT, Epi, true>), dim3((unsigned)g), blk, 0, s,
