@@ -10,10 +10,10 @@
 // Sparse products take two passes.  Symbolic: one wave per output row puts
 // the candidate columns into an open-addressing hash set in LDS, counts them,
 // and (second call) writes them sorted by rank.  Numeric: one wave per output
-// row maps column -> slot through the same kind of LDS table; lane e owns
-// entry e of every output block, and the contributions are added in the order
-// of A's row, then B's row.  Every output value is thus summed by one lane in
-// a fixed order: the result does not depend on the launch or on timing.
+// row (two for 6-row blocks) maps column -> slot through the same kind of LDS
+// table, and the contributions are added in the order of A's row, then B's row.
+// Every output value is thus summed by one wave in a fixed order: the result
+// does not depend on the launch or on timing.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -21,6 +21,7 @@
 
 #include "te_amg.h"
 #include "te_setup_gpu.h"
+#include "te_dev.h"
 
 namespace te {
 
@@ -145,13 +146,45 @@ __device__ __forceinline__ int lower_bound_col(const int32_t *__restrict__ col, 
     return lo;
 }
 
-// Numeric pass.  For each block k_a of A's row, the lanes first look up the
-// output slots of the whole B row k_a points to (lane l: entry l), then walk
-// that B row in order, the slot passed by a lane shuffle.  LACC: the row's
-// output blocks are accumulated in dynamic LDS (mcap blocks), else in place.
-// UP (a product known to be symmetric): only the blocks on and above the
-// diagonal are formed (contributions to columns left of the row are
-// skipped); k_mirror_lower fills the others from them afterwards.
+// Output slots of a row: columns col[0, m) -> their positions, hashed into LDS
+// by the NT threads of a block (2 m <= TB).
+template <int TB, int NT>
+__device__ __forceinline__ void slot_table(int32_t *key, int32_t *slot, const int32_t *__restrict__ col, int m,
+                                           int tid) {
+    for (int t = tid; t < TB; t += NT) key[t] = -1;
+    __syncthreads();
+    for (int x = tid; x < m; x += NT) {
+        const int32_t c = col[x];
+        uint32_t h = hslot<TB>(c);
+        for (int probe = 0; probe < TB; ++probe) {
+            if (atomicCAS(&key[h], -1, c) == -1) {
+                slot[h] = x;
+                break;
+            }
+            h = (h + 1) & (TB - 1);
+        }
+    }
+}
+// the position of column c, -1 if the row does not hold it
+template <int TB>
+__device__ __forceinline__ int slot_find(const int32_t *key, const int32_t *slot, int32_t c) {
+    uint32_t h = hslot<TB>(c);
+    int probe = 0;
+    while (probe < TB && key[h] != c) {
+        h = (h + 1) & (TB - 1);
+        ++probe;
+    }
+    return probe < TB ? slot[h] : -1;
+}
+
+// Numeric pass, one wave per row, for scalar blocks and for rows too long for
+// LDS.  For each block k_a of A's row, the lanes first look up the output slots
+// of the whole B row k_a points to (lane l: entry l), then walk that B row in
+// order, the slot passed by a lane shuffle.  LACC: the row's output blocks are
+// accumulated in dynamic LDS (mcap blocks), else in place.  UP (a product known
+// to be symmetric): only the blocks on and above the diagonal are formed
+// (contributions to columns left of the row are skipped); k_mirror_lower fills
+// the others from them afterwards.
 template <int BR, int BK, int BC, int TB, bool LACC, bool UP = false>
 __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict__ aptr,
                                             const int32_t *__restrict__ acol, const double *__restrict__ aval,
@@ -161,6 +194,7 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
                                             int32_t *__restrict__ flag, int mcap) {
     constexpr int BB = BR * BC;
     static_assert(BB <= 64, "output block larger than a wave");
+    static_assert(!LACC || BB == 1, "block rows in LDS are k_num_blk's");
     __shared__ int32_t key[TB];
     __shared__ int32_t slot[TB];
     __shared__ int64_t s_b0[64], s_b1[64];
@@ -179,19 +213,7 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
             if (lane == 0) atomicOr(flag, 4);
             continue;
         }
-        for (int t = lane; t < TB; t += 64) key[t] = -1;
-        __syncthreads();
-        for (int x = lane; x < m; x += 64) {
-            const int32_t c = ccol[c0 + x];
-            uint32_t h = hslot<TB>(c);
-            for (int probe = 0; probe < TB; ++probe) {
-                if (atomicCAS(&key[h], -1, c) == -1) {
-                    slot[h] = x;
-                    break;
-                }
-                h = (h + 1) & (TB - 1);
-            }
-        }
+        slot_table<TB, 64>(key, slot, ccol + c0, m, lane);
         double *acc = LACC ? s_acc : cval + c0 * BB;
         for (int64_t t = lane; t < (int64_t)m * BB; t += 64) acc[t] = 0.0;
         __syncthreads();
@@ -217,66 +239,20 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
                     int my = -1;
                     if (lane < nb) {
                         const int32_t c = bcol[kb0 + lane];
-                        if (UP && (int64_t)c < i) {
-                            my = -2;   // left of the diagonal: not formed
-                        } else {
-                            uint32_t h = hslot<TB>(c);
-                            int probe = 0;
-                            while (probe < TB && key[h] != c) {
-                                h = (h + 1) & (TB - 1);
-                                ++probe;
-                            }
-                            my = probe < TB ? slot[h] : -1;
-                        }
+                        my = UP && (int64_t)c < i ? -2   // left of the diagonal: not formed
+                                                  : slot_find<TB>(key, slot, c);
                     }
                     if (__any(lane < nb && my == -1)) {
                         if (lane == 0) atomicOr(flag, 8);
                         continue;
                     }
-                    if constexpr (LACC && BB == 1) {
+                    if constexpr (LACC) {
                         // scalar blocks: every lane updates its own entry's slot
                         // (the slots of one B row are distinct), each slot still
                         // receiving its updates in A-row order
                         if (lane < nb && my >= 0) {
                             const double t1 = __dmul_rn(aval[ka], bval[kb0 + lane]);
                             acc[my] = __dadd_rn(acc[my], t1);
-                        }
-                        continue;
-                    } else if constexpr (LACC && 2 * BB <= 64) {
-                        // G groups of BB lanes take G entries of the B row at once
-                        // (distinct slots); per output element the products and
-                        // the accumulation run in the same order as with one group
-                        constexpr int G = 64 / BB, UG = (8 + G - 1) / G;
-                        const int g = lane / BB, e = lane - (lane / BB) * BB;
-                        const bool gon = g < G;
-                        const int gp = gon ? e / BC : 0, gq = gon ? e % BC : 0;
-                        double ag[BK];
-                        const double *a2 = aval + ka * (BR * BK) + gp * BK;
-#pragma unroll
-                        for (int r = 0; r < BK; ++r) ag[r] = gon ? a2[r] : 0.0;
-                        for (int ub = 0; ub < nb; ub += G * UG) {
-                            int sl[UG];
-                            double t[UG], old[UG];
-                            bool ok[UG];
-#pragma unroll
-                            for (int uu = 0; uu < UG; ++uu) {
-                                const int u = ub + uu * G + g;
-                                const int uc = u < nb ? u : nb - 1;
-                                sl[uu] = __shfl(my, uc);
-                                ok[uu] = gon && u < nb && sl[uu] >= 0;
-                                t[uu] = 0.0;
-                                if (ok[uu]) {
-                                    const double *b = bval + (kb0 + uc) * (BK * BC) + gq;
-#pragma unroll
-                                    for (int r = 0; r < BK; ++r) t[uu] += ag[r] * b[r * BC];
-                                }
-                            }
-#pragma unroll
-                            for (int uu = 0; uu < UG; ++uu)
-                                if (ok[uu]) old[uu] = acc[sl[uu] * BB + e];
-#pragma unroll
-                            for (int uu = 0; uu < UG; ++uu)
-                                if (ok[uu]) acc[sl[uu] * BB + e] = old[uu] + t[uu];
                         }
                         continue;
                     }
@@ -313,6 +289,164 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
         __syncthreads();
         if (LACC)
             for (int64_t t = lane; t < (int64_t)m * BB; t += 64) cval[c0 * BB + t] = s_acc[t];
+        __syncthreads();
+    }
+}
+
+// acc += v on an LDS double.  The LDS operations of one wave complete in the
+// order it issues them, so an element that only one wave adds to, one lane per
+// instruction, is summed in program order without waiting for any addition.
+__device__ __forceinline__ void lds_add(double *acc, double v) {
+    __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double *)acc, v);
+}
+
+// Numeric pass of block rows whose output fits in LDS: BR / 3 waves per row,
+// wave w forms the rows [3 w, 3 w + 3) of every output block.  The pairs
+// (A block, B block) of a row are taken as one list in A-row order: the lanes
+// look up a pair each (B column, output slot; pairs left of the diagonal are
+// dropped with UP), the kept ones are packed into a list in LDS, and then 64 /
+// BC pairs at a time are multiplied, lane (g, q) forming three elements of
+// column q of pair g's product and adding them to the accumulators.  Pairs of
+// the same A block have distinct slots and are added by one instruction; those
+// of different A blocks one A block after the other, so each element receives
+// its terms in A-row order.
+//   Bound by the latency of the dependent steps (B row bounds, column, slot,
+// values).  One A block at a time, lane e updating entry e of one output block
+// after the other by a read and a write, took 20.4 ms for the Galerkin product
+// of a 524,576-node P2 disc (R 2.8 M blocks, A P 10.4 M) and 7.3 ms for its A P;
+// now 3.0 and 3.4 ms (the next level's: 3.4 -> 0.84 and 4.2 -> 2.0 ms).
+template <int BR, int BK, int BC, int TB, bool UP>
+__global__ void __launch_bounds__(64 * (BR / 3))
+    k_num_blk(int64_t n, const int64_t *__restrict__ aptr, const int32_t *__restrict__ acol,
+              const double *__restrict__ aval, const int64_t *__restrict__ bptr, const int32_t *__restrict__ bcol,
+              const double *__restrict__ bval, const int64_t *__restrict__ cptr, const int32_t *__restrict__ ccol,
+              double *__restrict__ cval, int32_t *__restrict__ flag, int mcap) {
+    constexpr int W = BR / 3, NT = 64 * W, BB = BR * BC, NG = 64 / BC, UB = 2, LIST = 2 * NT;
+    __shared__ int32_t key[TB];
+    __shared__ int32_t slot[TB];
+    __shared__ int64_t s_b0[64];
+    __shared__ int32_t s_pre[64];
+    __shared__ int64_t l_kb[LIST];      // kept pairs: B block
+    __shared__ int32_t l_us[LIST];      //             A block (of 64) << 16 | slot
+    __shared__ int32_t s_kept[W];
+    extern __shared__ double s_acc[];   // [mcap][BB]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int g = lane / BC, q = lane - g * BC, p0 = 3 * w;
+    for (int64_t i = xcd_logical_block(blockIdx.x, gridDim.x); i < n; i += gridDim.x) {
+        const int64_t cs = cptr[i];
+        const int mf = (int)(cptr[i + 1] - cs);
+        const int u0 = UP ? lower_bound_col(ccol + cs, mf, i) : 0;   // UP: the columns >= i, a suffix of the row
+        const int64_t c0 = cs + u0;
+        const int m = mf - u0;
+        if (2 * m > TB || m > mcap) {  // uniform over the block
+            if (tid == 0) atomicOr(flag, 4);
+            continue;
+        }
+        slot_table<TB, NT>(key, slot, ccol + c0, m, tid);
+        for (int t = tid; t < m * BB; t += NT) s_acc[t] = 0.0;
+        const int64_t a0 = aptr[i], a1 = aptr[i + 1];
+        for (int64_t kc = a0; kc < a1; kc += 64) {
+            const int na = (int)((a1 - kc) < 64 ? (a1 - kc) : 64);
+            int64_t b0 = 0;
+            int len = 0;
+            if (lane < na) {
+                const int32_t jj = acol[kc + lane];
+                b0 = bptr[jj];
+                len = (int)(bptr[jj + 1] - b0);
+            }
+            int pre = len;   // inclusive prefix sum over the lanes
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(pre, o, 64);
+                if (lane >= o) pre += t;
+            }
+            const int total = __shfl(pre, 63, 64);
+            if (w == 0) {
+                s_b0[lane] = b0 - (pre - len);   // pair f of entry u is B block s_b0[u] + f
+                s_pre[lane] = pre;
+            }
+            __syncthreads();   // also the slots and the zeros
+            int cnt = 0;       // pairs in the list
+            for (int f0 = 0; f0 < total; f0 += NT) {
+                const int f = f0 + tid;
+                int sl = -2, lo = 0;
+                int64_t kb = 0;
+                if (f < total) {
+                    int hi = na - 1;   // the entry whose part of the list holds f
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (s_pre[mid] <= f) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    kb = s_b0[lo] + f;
+                    const int32_t c = bcol[kb];
+                    if (!UP || (int64_t)c >= i) {
+                        sl = slot_find<TB>(key, slot, c);
+                        if (sl < 0) atomicOr(flag, 8);
+                    }
+                }
+                const uint64_t keep = __ballot(sl >= 0);
+                int at = cnt + __popcll(keep & ((1ull << lane) - 1));
+                if constexpr (W > 1) {
+                    if (lane == 0) s_kept[w] = __popcll(keep);
+                    __syncthreads();
+#pragma unroll
+                    for (int v = 0; v < W; ++v) {
+                        if (v < w) at += s_kept[v];
+                        cnt += s_kept[v];
+                    }
+                } else {
+                    cnt += __popcll(keep);
+                }
+                if (sl >= 0) {
+                    l_kb[at] = kb;
+                    l_us[at] = lo << 16 | sl;
+                }
+                __syncthreads();
+                // another pass over the lanes may still fit into the list
+                if (f0 + NT < total && cnt + NT <= LIST) continue;
+                for (int x0 = 0; x0 < cnt; x0 += UB * NG) {
+                    double t[UB][3];
+                    int us[UB];
+                    bool ok[UB];
+#pragma unroll
+                    for (int v = 0; v < UB; ++v) {
+                        const int x = x0 + v * NG + g;
+                        ok[v] = g < NG && x < cnt;
+                        const int xi = ok[v] ? x : cnt - 1;
+                        us[v] = l_us[xi];
+                        const double *a = aval + (kc + (us[v] >> 16)) * (BR * BK) + p0 * BK;
+                        const double *b = bval + l_kb[xi] * (BK * BC) + q;
+                        double br[BK];
+#pragma unroll
+                        for (int r = 0; r < BK; ++r) br[r] = b[r * BC];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            t[v][p] = 0.0;
+#pragma unroll
+                            for (int r = 0; r < BK; ++r) t[v][p] += a[p * BK + r] * br[r];
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < UB; ++v) {
+                        uint64_t rem = __ballot(ok[v]);
+                        while (rem) {   // one A block after the other
+                            const int u = __shfl(us[v] >> 16, __builtin_ctzll(rem), 64);
+                            const bool now = ok[v] && (us[v] >> 16) == u;
+                            if (now) {
+                                double *acc = s_acc + (us[v] & 0xffff) * BB + p0 * BC + q;
+#pragma unroll
+                                for (int p = 0; p < 3; ++p) lds_add(acc + p * BC, t[v][p]);
+                            }
+                            rem &= ~__ballot(now);
+                        }
+                    }
+                }
+                cnt = 0;
+                __syncthreads();   // the list is refilled
+            }
+        }
+        __syncthreads();
+        for (int t = tid; t < m * BB; t += NT) cval[c0 * BB + t] = s_acc[t];
         __syncthreads();
     }
 }
@@ -801,14 +935,19 @@ void launch_num(int tb, int64_t mx, const DBsr &A, const DBsr &B, DBsr &C, int32
     const size_t lds = (size_t)std::max<int64_t>(mx, 1) * BR * BC * sizeof(double);
     const bool lacc = lds <= ((size_t)32 << 10);
     const int mcap = (int)std::max<int64_t>(mx, 1);
-#define TE_NUM(TBV)                                                                                                \
-    case TBV:                                                                                                      \
-        if (lacc)                                                                                                  \
-            hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, true, UP>), g, b, lds, s, A.nr, A.ptr, A.col, A.val, B.ptr, \
-                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                               \
-        else                                                                                                       \
-            hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, false, UP>), g, b, 0, s, A.nr, A.ptr, A.col, A.val, B.ptr,  \
-                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                               \
+#define TE_NUM(TBV)                                                                                                  \
+    case TBV:                                                                                                        \
+        if constexpr (BR * BC == 1) {                                                                                \
+            if (lacc)                                                                                                \
+                hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, true, UP>), g, b, lds, s, A.nr, A.ptr, A.col, A.val,      \
+                                   B.ptr, B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                      \
+        } else if (lacc) {                                                                                           \
+            hipLaunchKernelGGL((k_num_blk<BR, BK, BC, TBV, UP>), g, dim3(64 * (BR / 3)), lds, s, A.nr, A.ptr, A.col, \
+                               A.val, B.ptr, B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                   \
+        }                                                                                                            \
+        if (!lacc)                                                                                                   \
+            hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, false, UP>), g, b, 0, s, A.nr, A.ptr, A.col, A.val, B.ptr,    \
+                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                                 \
         break;
     switch (tb) {
         TE_NUM(64)
