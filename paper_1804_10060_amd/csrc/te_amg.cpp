@@ -829,35 +829,17 @@ int setup_impl(const te_bsr *A, const double *coords, const uint8_t *dir_mask, c
                 }
             }
         }
-        // this level is the coarsest: its values on the host for the dense factor
         TE_REQUIRE(ndof <= 12000, TE_EINVAL, "coarsest level has %lld DOF, too many for the dense factor",
                    (long long)ndof);
-        dev_to_host(*cur, L.Ah, s);
+        dev_pattern_to_host(*cur, L.Ah, s);
         L.dstore.release();
+        // dense inverse of (A + A^T)/2 in storage order
+        L.lam = 0.0;
+        dev_dense_inverse_spd(*cur, L.iperm_h, h->Ainv, s);
+        h->nc = (int)ndof;
         break;
     }
     owned.release();
-    // coarsest level: dense inverse of (A + A^T)/2 in storage order
-    {
-        Level &C = h->L.back();
-        C.lam = 0.0;
-        const int64_t nc = C.n * C.bs;
-        std::vector<double> M((size_t)nc * nc, 0.0);
-        const int b = C.bs;
-        for (int64_t i = 0; i < C.n; ++i)
-            for (int64_t kk = C.Ah.ptr[i]; kk < C.Ah.ptr[i + 1]; ++kk) {
-                const int64_t j = C.Ah.col[kk];
-                const int64_t si = C.iperm_h[i], sj = C.iperm_h[j];
-                for (int p = 0; p < b; ++p)
-                    for (int q = 0; q < b; ++q) {
-                        double v = 0.5 * C.Ah.val[(size_t)kk * b * b + p * b + q];
-                        M[(size_t)(si * b + p) * nc + sj * b + q] += v;
-                        M[(size_t)(sj * b + q) * nc + si * b + p] += v;
-                    }
-            }
-        dev_dense_inverse_spd(M, (int)nc, h->Ainv, s);
-        h->nc = (int)nc;
-    }
     note("coarse factor", (int)h->L.size() - 1, h->nc, 0);
     alloc_work(h.get(), s);
     TE_CHECK_HIP(hipStreamSynchronize(s));

@@ -70,10 +70,10 @@ void dev_pack(Sell &S, const DBsr &M, const std::vector<int64_t> &hptr, const st
               const std::vector<int32_t> &col_map, const std::vector<int32_t> *out_map, bool fp32, hipStream_t s,
               int format, bool sym = false);
 
-// inv = M^-1 for a symmetric positive definite n x n matrix M (host,
-// row-major), computed on the device by n symmetric sweeps; TE_ECHOL if a
-// pivot is not positive.
-void dev_dense_inverse_spd(const std::vector<double> &M, int n, DBuf<double> &inv, hipStream_t s);
+// inv = ((M + M^T) / 2)^-1 (dense, row-major) for a symmetric positive definite
+// M with distinct columns in each row, its block rows and columns moved to
+// pos[i]; TE_ECHOL if a pivot is not positive.
+void dev_dense_inverse_spd(const DBsr &M, const std::vector<int32_t> &pos, DBuf<double> &inv, hipStream_t s);
 
 // Parallel aggregation of a level (square A with a symmetric pattern, s from
 // dev_strength): the strong graph made symmetric (block k = (i, j) strong if

@@ -777,34 +777,180 @@ __global__ void k_pack_upper(int64_t nup, int bb, const int64_t *__restrict__ sr
 }
 
 // ---- dense inverse of the coarsest operator ----------------------------------------------
-// Symmetric sweep operator on pivot j (Goodnight 1979): with d = a_jj,
-//   a_jj <- -1/d,  a_ij <- a_ij/d,  a_jk <- a_jk/d,  a_ik <- a_ik - a_ij a_jk/d  (i, k != j);
-// after sweeping every pivot the matrix holds -A^-1.  On a symmetric positive
-// definite matrix each pivot is a Schur complement entry, hence positive;
-// a pivot <= 0 (or NaN) is reported.  Reads `in`, writes `out` (ping-pong).
-__global__ void k_sweep(int n, int j, const double *__restrict__ in, double *__restrict__ out,
-                        int32_t *__restrict__ bad) {
-    const double d = in[(int64_t)j * n + j];
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const double ajk = in[(int64_t)j * n + k];
-    for (int i = blockIdx.y; i < n; i += gridDim.y) {
-        const int64_t t = (int64_t)i * n + k;
-        double v;
-        if (i == j && k == j) {
-            v = -1.0 / d;
-            if (!(d > 0.0)) *bad = 1;
-        } else if (i == j || k == j) {
-            v = in[t] / d;
-        } else {
-            v = in[t] - in[(int64_t)i * n + j] * ajk / d;
+// Symmetric sweep operator (Goodnight 1979) on a block J of NB pivots at a
+// time: with P = A_JJ^-1,
+//   A_JJ <- -P,  A_Jk <- P A_Jk,  A_iJ <- A_iJ P,  A_ik <- A_ik - A_iJ P A_Jk  (i, k not in J);
+// after sweeping every block the matrix holds -A^-1.  On a symmetric positive
+// definite matrix each pivot is a Schur complement entry, hence positive; a
+// pivot <= 0 (or NaN) is reported.
+//   Per block three launches: the NB x NB pivot block in one workgroup, the
+// panel T = P A_J, and the update of the tiles on and above the diagonal,
+// which writes their mirrors too.  The products run on the float64 matrix
+// cores: their rate is the vector units', but a wave reads four operands from
+// LDS for four 16 x 16 x 4 products.  At about 2,300 unknowns: one pivot at a
+// time, each a pass over the matrix, 37 ms; now 37 x (31 + 15 + 26) us = 2.7 ms,
+// of which the serial pivot block takes the most.
+constexpr int NB = 64;          // pivots per step, and the tile size
+constexpr int NBK = 32;         // depth of a product's LDS stage
+constexpr int NBS = NB + 16;    // LDS row stride: lanes (l / 16, l % 16) touch every bank twice
+
+// -> P: thread (r, c0) holds entries c0 .. c0 + 15 of row r.  The matrix stays
+// symmetric, so pivot row j is all that a step needs: its owners write it with
+// a_jj replaced by 1 and the reciprocal of the pivot, and with a_rj set to 0
+// first every other row takes a_rk - a_rj a_jk / d also in column j (which
+// becomes -a_rj / d, the negated form of the sweep: P itself at the end).
+__global__ void __launch_bounds__(256) k_pivot_block(int64_t np, int64_t j0, const double *__restrict__ A,
+                                                     double *__restrict__ P, int32_t *__restrict__ bad) {
+    __shared__ __align__(16) double row[2][NB];
+    __shared__ double pinv[2];
+    const int r = threadIdx.x >> 2, c0 = (threadIdx.x & 3) * 16;
+    double a[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = A[(j0 + r) * np + j0 + c0 + c];
+    for (int jc = 0; jc < NB; jc += 16) {
+#pragma unroll
+        for (int jj = 0; jj < 16; ++jj) {
+            double *rj = row[jj & 1];
+            const bool own = c0 == jc;   // this thread's entries hold column j
+            if (r == jc + jj) {
+                if (own) {
+                    if (!(a[jj] > 0.0)) *bad = 1;
+                    pinv[jj & 1] = 1.0 / a[jj];
+                    a[jj] = 1.0;
+                }
+#pragma unroll
+                for (int c = 0; c < 16; ++c) rj[c0 + c] = a[c];
+            }
+            __syncthreads();
+            const double inv = pinv[jj & 1];
+            // a_rj = +- a_jr: rows already swept hold it with the other sign
+            const double arj = r < jc + jj ? -rj[r] : rj[r];
+            if (r == jc + jj) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) a[c] *= inv;
+            } else {
+                const double f = -arj * inv;
+                a[jj] = own ? 0.0 : a[jj];
+#pragma unroll
+                for (int c = 0; c < 16; ++c) a[c] += f * rj[c0 + c];
+            }
         }
-        out[t] = v;
+    }
+#pragma unroll
+    for (int c = 0; c < 16; ++c) P[r * NB + c0 + c] = a[c];
+}
+
+using f64x4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
+
+// acc += X[:, i0 .. i0 + NB)^T Y[:, c0 .. c0 + NB), X and Y of NB rows: wave w
+// of four forms the quarter (w / 2, w % 2) as 2 x 2 tiles of 16 x 16.
+__device__ __forceinline__ void tile_xty(const double *__restrict__ X, int64_t ldx, int64_t i0,
+                                         const double *__restrict__ Y, int64_t ldy, int64_t c0, double (*sx)[NBS],
+                                         double (*sy)[NBS], f64x4 (&acc)[2][2]) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int wi = (w >> 1) * 32 + (lane & 15), wc = (w & 1) * 32 + (lane & 15), lk = lane >> 4;
+    for (int k0 = 0; k0 < NB; k0 += NBK) {
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NBK * NB / 256; ++t) {
+            const int e = tid + t * 256, k = e / NB, c = e % NB;
+            sx[k][c] = X[(k0 + k) * ldx + i0 + c];
+            sy[k][c] = Y[(k0 + k) * ldy + c0 + c];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NBK; k += 4) {
+            const double x0 = sx[k + lk][wi], x1 = sx[k + lk][wi + 16];
+            const double y0 = sy[k + lk][wc], y1 = sy[k + lk][wc + 16];
+            acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
+            acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
+            acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
+            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
+        }
     }
 }
-__global__ void k_negate(int64_t nn, const double *__restrict__ in, double *__restrict__ out) {
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nn; t += (int64_t)gridDim.x * blockDim.x)
-        out[t] = -in[t];
+// element (row, column) of the tile that register r of acc[x][y] holds
+__device__ __forceinline__ int tile_row(int x, int r) {
+    return ((threadIdx.x >> 7) * 2 + x) * 16 + 4 * r + ((threadIdx.x & 63) >> 4);
+}
+__device__ __forceinline__ int tile_col(int y) {
+    return (((threadIdx.x >> 6) & 1) * 2 + y) * 16 + (threadIdx.x & 15);
+}
+
+// W = rows J of A, T = P W: one workgroup per tile of NB columns
+__global__ void __launch_bounds__(256) k_panel(int64_t np, int64_t j0, const double *__restrict__ A,
+                                               const double *__restrict__ P, double *__restrict__ W,
+                                               double *__restrict__ T) {
+    __shared__ double sx[NBK][NBS], sy[NBK][NBS];
+    const int64_t c0 = (int64_t)blockIdx.x * NB;
+    const double *AJ = A + j0 * np;
+    f64x4 acc[2][2] = {};
+    tile_xty(P, NB, 0, AJ, np, c0, sx, sy, acc);
+    for (int e = threadIdx.x; e < NB * NB; e += 256) W[(e / NB) * np + c0 + e % NB] = AJ[(e / NB) * np + c0 + e % NB];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) T[tile_row(x, r) * np + c0 + tile_col(y)] = acc[x][y][r];
+}
+
+// The rest of the step, in place (out = A, ld = np, sign = 1) or, for the last
+// block, negated into the first n rows and columns of out.
+__global__ void __launch_bounds__(256) k_block_update(int64_t np, int64_t j0, const double *__restrict__ P,
+                                                      const double *__restrict__ W, const double *__restrict__ T,
+                                                      const double *A, double *out, int64_t n, int64_t ld,
+                                                      double sign) {
+    __shared__ double sx[NBK][NBS], sy[NBK][NBS];
+    const int64_t I = blockIdx.y, K = blockIdx.x, i0 = I * NB, c0 = K * NB;
+    if (I > K) return;   // the mirrors are written by (K, I)
+    f64x4 acc[2][2] = {};
+    const bool pi = i0 == j0, pk = c0 == j0;
+    if (!pi && !pk) tile_xty(W, np, i0, T, np, c0, sx, sy, acc);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int ti = tile_row(x, r), tc = tile_col(y);
+                const int64_t i = i0 + ti, c = c0 + tc;
+                if (i > c || c >= n) continue;   // i <= c < n
+                double v;
+                if (pi && pk) v = -P[ti * NB + tc];
+                else if (pi) v = T[ti * np + c];
+                else if (pk) v = T[tc * np + i];
+                else v = A[i * np + c] - acc[x][y][r];
+                out[i * ld + c] = sign * v;
+                out[c * ld + i] = sign * v;
+            }
+}
+
+// the blocks of A (block size b, rows and columns moved by pos) into the dense
+// np x np matrix D, which holds zeros
+__global__ void __launch_bounds__(64) k_dense_scatter(int64_t n, int b, const int64_t *__restrict__ ptr,
+                                                      const int32_t *__restrict__ col,
+                                                      const double *__restrict__ val,
+                                                      const int32_t *__restrict__ pos, int64_t np,
+                                                      double *__restrict__ D) {
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const int64_t k0 = ptr[i], m = (ptr[i + 1] - k0) * b * b, r0 = (int64_t)pos[i] * b;
+        for (int64_t t = threadIdx.x; t < m; t += 64) {
+            const int64_t k = k0 + t / (b * b);
+            const int e = (int)(t % (b * b));
+            D[(r0 + e / b) * np + (int64_t)pos[col[k]] * b + e % b] = val[k0 * b * b + t];
+        }
+    }
+}
+// D <- (D + D^T) / 2, the identity beyond n
+__global__ void k_symmetrise(int64_t n, int64_t np, double *__restrict__ D) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < np * np; t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t i = t / np, k = t - i * np;
+        if (i > k) continue;
+        const double v = k < n ? 0.5 * D[t] + 0.5 * D[k * np + i] : i == k ? 1.0 : 0.0;
+        D[t] = v;
+        D[k * np + i] = v;
+    }
 }
 
 inline unsigned grid_for(int64_t n, int b = 256) {
@@ -1362,26 +1508,28 @@ void dev_pack(Sell &S, const DBsr &M, const std::vector<int64_t> &hptr, const st
     TE_CHECK_HIP(hipStreamSynchronize(s));
 }
 
-void dev_dense_inverse_spd(const std::vector<double> &M, int n, DBuf<double> &inv, hipStream_t s) {
-    const int64_t nn = (int64_t)n * n;
-    TE_REQUIRE((int64_t)M.size() == nn && n > 0, TE_EINVAL, "dense inverse: bad size");
-    DBuf<double> a, b;
-    upload(a, M, s);
-    b.alloc(nn);
-    DBuf<int32_t> bad(1);
+void dev_dense_inverse_spd(const DBsr &M, const std::vector<int32_t> &pos, DBuf<double> &inv, hipStream_t s) {
+    TE_REQUIRE(M.nr == M.nc && M.br == M.bc && M.nr > 0 && (int64_t)pos.size() == M.nr, TE_EINVAL,
+               "dense inverse: bad size");
+    const int64_t n = M.nr * M.br, nt = (n + NB - 1) / NB, np = nt * NB;
+    DBuf<double> A(np * np), P(NB * NB), W(NB * np), T(NB * np);
+    DBuf<int32_t> bad(1), dpos;
+    upload(dpos, pos, s);
     TE_CHECK_HIP(hipMemsetAsync(bad.p, 0, sizeof(int32_t), s));
-    const unsigned g = grid_for(nn);
-    const dim3 gs((n + 255) / 256, std::min(n, 4096));
-    for (int j = 0; j < n; ++j) {
-        hipLaunchKernelGGL(k_sweep, gs, dim3(256), 0, s, n, j, a.p, b.p, bad.p);
-        std::swap(a.p, b.p);
+    TE_CHECK_HIP(hipMemsetAsync(A.p, 0, np * np * sizeof(double), s));
+    hipLaunchKernelGGL(k_dense_scatter, dim3(wave_grid(M.nr)), dim3(64), 0, s, M.nr, M.br, M.ptr, M.col, M.val, dpos.p,
+                       np, A.p);
+    hipLaunchKernelGGL(k_symmetrise, dim3(grid_for(np * np)), dim3(256), 0, s, n, np, A.p);
+    inv.alloc(n * n);
+    for (int64_t j = 0; j < nt; ++j) {
+        const bool last = j == nt - 1;
+        hipLaunchKernelGGL(k_pivot_block, dim3(1), dim3(256), 0, s, np, j * NB, A.p, P.p, bad.p);
+        hipLaunchKernelGGL(k_panel, dim3(nt), dim3(256), 0, s, np, j * NB, A.p, P.p, W.p, T.p);
+        hipLaunchKernelGGL(k_block_update, dim3(nt, nt), dim3(256), 0, s, np, j * NB, P.p, W.p, T.p, A.p,
+                           last ? inv.p : A.p, last ? n : np, last ? n : np, last ? -1.0 : 1.0);
     }
     TE_CHECK_HIP(hipGetLastError());
     TE_REQUIRE(read_flag(bad, s) == 0, TE_ECHOL, "coarse factor: a pivot of the coarsest operator is not positive");
-    inv.alloc(nn);
-    hipLaunchKernelGGL(k_negate, dim3(g), dim3(256), 0, s, nn, a.p, inv.p);
-    TE_CHECK_HIP(hipGetLastError());
-    TE_CHECK_HIP(hipStreamSynchronize(s));
 }
 
 // ---------------------------------------------------------------------------

@@ -78,3 +78,30 @@ def test_products_match_oracle(case):
         err = abs(D).max() if D.nnz else 0.0
         assert err <= 1e-11 * np.abs(lv.A.data).max(), (l, err)
         assert np.array_equal(val, hs[1].level_matrix(l)[2])   # and run to run the same bits
+
+
+@pytest.mark.parametrize("n", [1, 21, 22, 64, 65, 130, 900])
+def test_dense_coarsest_inverse(n):
+    """A one-level hierarchy applies the explicit inverse: 3, 63, 66, 192, 195, 390
+    and 2700 unknowns (blocks of 64 pivots, full and padded).  The residual of a
+    Cholesky-like inverse is at most a few n kappa u |b|; kappa <= 1e4 here."""
+    import paper_1804_10060_amd as te
+    torch = torch_cuda()
+    A, X = _spring_network(n, _random(n, 6, 1) if n > 4 else (np.zeros(0, int), np.zeros(0, int)), seed=2)
+    mask = np.zeros((n, 3), dtype=np.uint8)
+    say("dense inverse", 3 * n)
+    h = te.AMG(oracle_bsr_to_device(A), dev(X, torch.float64), dev(mask), coarse_max=3000)
+    assert h.info()["n_levels"] == 1
+    b = np.random.default_rng(0).standard_normal(3 * n)
+    x = h.apply(0, te.TE_OP_VCYCLE, dev(b, torch.float64)).cpu().numpy()
+    assert np.linalg.norm(A @ x - b) <= 3 * n * 1e4 * 2.0 ** -53 * np.linalg.norm(b)
+
+
+def test_dense_coarsest_inverse_rejects_indefinite():
+    import paper_1804_10060_amd as te
+    torch = torch_cuda()
+    A, X = _spring_network(100, _random(100, 6, 1), seed=2)
+    A = A.tocsr()
+    A[220, 220] = -5.0   # a pivot in the last, padded block
+    with pytest.raises(te.TeError):
+        te.AMG(oracle_bsr_to_device(A.tobsr((3, 3))), dev(X, torch.float64), dev(np.zeros((100, 3), np.uint8)))
