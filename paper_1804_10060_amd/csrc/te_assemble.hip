@@ -9,9 +9,8 @@
 // element blocks of a chunk of cells go through LDS and each lane adds them
 // to the row blocks it owns, which are written once.  The load vectors take
 // one thread per node, several load cases at a time.  Element integrals:
-//   stiffness  P1: constant gradients (one-point exact); P2: degree-2
-//              integrand, 4-point rule (a,b,b,b), a = (5+3 sqrt5)/20,
-//              b = (5-sqrt5)/20, weights 1/4 (exact for degree 2);
+//   stiffness  P1: constant gradients; P2: degree-2 integrand, the integrals
+//              of the products of barycentric coordinates in closed form;
 //   thermal    P1: centroid rule (degree 1 exact); P2: degree-3 integrand,
 //              5-point rule with barycentric points (1/4,...) weight -4/5 and
 //              the permutations of (1/2,1/6,1/6,1/6) weight 9/20 (exact for
@@ -24,6 +23,7 @@
 #include <algorithm>
 #include <numeric>
 
+#include "te_dev.h"
 #include "te_internal.h"
 #include "te_thermal.h"
 
@@ -37,40 +37,66 @@ __constant__ int c_edge[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}}
 // ---------------------------------------------------------------------------
 // node -> (cell, local index) incidence
 // ---------------------------------------------------------------------------
+// bad: the first entry that is no node (initially all ones)
 __global__ void k_check_cells(const int32_t *__restrict__ cells, int64_t n_entries, int64_t n_nodes,
-                              int32_t *__restrict__ bad) {
+                              unsigned long long *__restrict__ bad) {
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n_entries; t += (int64_t)gridDim.x * blockDim.x) {
         int32_t v = cells[t];
-        if (v < 0 || v >= n_nodes) *bad = 1;
+        if (v < 0 || v >= n_nodes) atomicMin(bad, (unsigned long long)t);
     }
 }
 
-__global__ void k_inc_count(const int32_t *__restrict__ cells, int64_t n_entries, int32_t *__restrict__ cnt) {
+// entries t = cell * npe + local node, local nodes below a0 left out
+__global__ void k_inc_count(const int32_t *__restrict__ cells, int64_t n_entries, int npe, int a0,
+                            int32_t *__restrict__ cnt) {
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n_entries; t += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&cnt[cells[t]], 1);
+        if (a0 == 0 || t % npe >= a0) atomicAdd(&cnt[cells[t]], 1);
 }
 
-__global__ void k_inc_fill(const int32_t *__restrict__ cells, int64_t n_entries, const int64_t *__restrict__ start,
-                           int32_t *__restrict__ fill, int64_t *__restrict__ inc) {
+__global__ void k_inc_fill(const int32_t *__restrict__ cells, int64_t n_entries, int npe, int a0,
+                           const int64_t *__restrict__ start, int32_t *__restrict__ fill, int64_t *__restrict__ inc) {
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n_entries; t += (int64_t)gridDim.x * blockDim.x) {
+        if (a0 != 0 && t % npe < a0) continue;
         int32_t v = cells[t];
         int32_t k = atomicAdd(&fill[v], 1);
-        inc[start[v] + k] = t;  // t = cell * npe + local
+        inc[start[v] + k] = t;
     }
 }
 
-// per node: sort its incidence entries ascending (insertion sort, short lists)
+// Per node: its entries in ascending order.  Lists of at most CAP entries go
+// through registers, every entry placed by the number of smaller ones; longer
+// ones are sorted by insertion.  524,576 P2 nodes: insertion alone 0.169 ms
+// (a serial chain of loads and stores), now 0.040.
+template <int CAP>
+__device__ __forceinline__ void sort_list(int64_t *__restrict__ inc, int64_t lo, int len) {
+    int64_t v[CAP];
+#pragma unroll
+    for (int a = 0; a < CAP; ++a) v[a] = a < len ? inc[lo + a] : INT64_MAX;
+#pragma unroll
+    for (int a = 0; a < CAP; ++a) {
+        int r = 0;
+#pragma unroll
+        for (int b = 0; b < CAP; ++b) r += v[b] < v[a] ? 1 : 0;
+        if (a < len) inc[lo + r] = v[a];
+    }
+}
 __global__ void k_inc_sort(const int64_t *__restrict__ start, int64_t *__restrict__ inc, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t lo = start[i], hi = start[i + 1];
-        for (int64_t a = lo + 1; a < hi; ++a) {
-            int64_t v = inc[a];
-            int64_t b = a - 1;
-            while (b >= lo && inc[b] > v) {
-                inc[b + 1] = inc[b];
-                --b;
+        const int64_t lo = start[i], hi = start[i + 1];
+        if (hi - lo <= 8) {
+            sort_list<8>(inc, lo, (int)(hi - lo));
+        } else if (hi - lo <= 24) {
+            sort_list<24>(inc, lo, (int)(hi - lo));
+        } else {
+            for (int64_t a = lo + 1; a < hi; ++a) {
+                int64_t v = inc[a];
+                int64_t b = a - 1;
+                while (b >= lo && inc[b] > v) {
+                    inc[b + 1] = inc[b];
+                    --b;
+                }
+                inc[b + 1] = v;
             }
-            inc[b + 1] = v;
         }
     }
 }
@@ -93,111 +119,174 @@ __global__ void k_scan_block(const int32_t *__restrict__ in, int64_t *__restrict
     if (i < n) out[i + 1] = s[threadIdx.x];  // inclusive -> shifted
     if (threadIdx.x == 1023) block_sums[blockIdx.x] = s[1023];
 }
+// exclusive prefix sums of the block sums, in place: one workgroup
+__global__ void __launch_bounds__(1024) k_scan_sums(int64_t nb, int64_t *__restrict__ bs) {
+    __shared__ int64_t s[1024];
+    int64_t base = 0;
+    for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
+        const int64_t i = b0 + threadIdx.x;
+        const int64_t own = i < nb ? bs[i] : 0;
+        s[threadIdx.x] = own;
+        __syncthreads();
+        for (int o = 1; o < 1024; o <<= 1) {
+            const int64_t v = (threadIdx.x >= (unsigned)o) ? s[threadIdx.x - o] : 0;
+            __syncthreads();
+            s[threadIdx.x] += v;
+            __syncthreads();
+        }
+        if (i < nb) bs[i] = base + s[threadIdx.x] - own;
+        base += s[1023];
+        __syncthreads();
+    }
+}
 __global__ void k_scan_add(int64_t *__restrict__ out, int64_t n, const int64_t *__restrict__ block_off) {
     int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
     if (i < n) out[i + 1] += block_off[blockIdx.x];
     if (i == 0) out[0] = 0;
 }
 
-static void scan_counts(const int32_t *cnt, int64_t *out, int64_t n, hipStream_t s) {
-    int64_t nb = (n + 1023) / 1024;
-    DBuf<int64_t> bs(std::max<int64_t>(nb, 1));
-    if (n > 0) {
-        hipLaunchKernelGGL(k_scan_block, dim3((unsigned)nb), dim3(1024), 0, s, cnt, out, n, bs.p);
-        TE_CHECK_HIP(hipGetLastError());
-    }
-    std::vector<int64_t> h;
-    download(h, bs.p, (size_t)nb, s);
-    std::vector<int64_t> off(nb, 0);
-    for (int64_t b = 1; b < nb; ++b) off[b] = off[b - 1] + h[b - 1];
-    DBuf<int64_t> doff;
-    upload(doff, off, s);
-    if (n > 0) {
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(1024), 0, s, out, n, doff.p);
-        TE_CHECK_HIP(hipGetLastError());
-    } else {
-        TE_CHECK_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), s));
-    }
-    TE_CHECK_HIP(hipStreamSynchronize(s));
+// bs: scratch of (n + 1023) / 1024 sums, kept by the caller until the stream has run
+static void scan_counts(const int32_t *cnt, int64_t *out, int64_t n, DBuf<int64_t> &bs, hipStream_t s) {
+    const int64_t nb = (n + 1023) / 1024;   // n > 0
+    bs.alloc(nb);
+    hipLaunchKernelGGL(k_scan_block, dim3((unsigned)nb), dim3(1024), 0, s, cnt, out, n, bs.p);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, nb, bs.p);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(1024), 0, s, out, n, bs.p);
+    TE_CHECK_HIP(hipGetLastError());
 }
 
-static void build_incidence(const te_mesh *m, int npe, Incidence &I, hipStream_t s) {
-    const int64_t n = m->n_nodes, ne = m->n_cells * (int64_t)npe;
-    DBuf<int32_t> bad(1);
-    TE_CHECK_HIP(hipMemsetAsync(bad.p, 0, sizeof(int32_t), s));
-    unsigned g = (unsigned)std::min<int64_t>((ne + 255) / 256 + 1, 1 << 20);
-    hipLaunchKernelGGL(k_check_cells, dim3(g), dim3(256), 0, s, m->cells, ne, n, bad.p);
+// the first of n_entries node numbers outside [0, n_nodes), -1 if there is none
+static int64_t first_bad_node(const int32_t *nodes, int64_t n_entries, int64_t n_nodes, hipStream_t s) {
+    DBuf<unsigned long long> bad(1);
+    TE_CHECK_HIP(hipMemsetAsync(bad.p, 0xFF, sizeof(unsigned long long), s));
+    const unsigned g = (unsigned)std::min<int64_t>((n_entries + 255) / 256 + 1, 1 << 20);
+    hipLaunchKernelGGL(k_check_cells, dim3(g), dim3(256), 0, s, nodes, n_entries, n_nodes, bad.p);
     TE_CHECK_HIP(hipGetLastError());
-    int32_t hb = 0;
-    TE_CHECK_HIP(hipMemcpyAsync(&hb, bad.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    int64_t hb = -1;
+    TE_CHECK_HIP(hipMemcpyAsync(&hb, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     TE_CHECK_HIP(hipStreamSynchronize(s));
-    TE_REQUIRE(hb == 0, TE_EINVAL, "cells reference a node index outside [0, n_nodes)");
-    DBuf<int32_t> cnt(n);
-    TE_CHECK_HIP(hipMemsetAsync(cnt.p, 0, n * sizeof(int32_t), s));
-    hipLaunchKernelGGL(k_inc_count, dim3(g), dim3(256), 0, s, m->cells, ne, cnt.p);
-    TE_CHECK_HIP(hipGetLastError());
+    return hb;
+}
+
+// node -> entries of `cells` (n_cells x npe node numbers, checked) whose local
+// node is a0 or above, ascending if `sorted`.  Returns after the launches; cnt and bs are
+// scratch that the caller keeps until the stream has run.
+static void entry_lists(const int32_t *cells, int64_t n_cells, int npe, int a0, int64_t n, bool sorted,
+                        Incidence &I, DBuf<int32_t> &cnt, DBuf<int64_t> &bs, hipStream_t s) {
+    const int64_t ne = n_cells * (int64_t)npe;
+    const unsigned g = (unsigned)std::min<int64_t>((ne + 255) / 256 + 1, 1 << 20);
+    cnt.alloc(n);
     I.start.alloc(n + 1);
-    scan_counts(cnt.p, I.start.p, n, s);
-    TE_CHECK_HIP(hipMemsetAsync(cnt.p, 0, n * sizeof(int32_t), s));
     I.inc.alloc(std::max<int64_t>(ne, 1));
-    hipLaunchKernelGGL(k_inc_fill, dim3(g), dim3(256), 0, s, m->cells, ne, I.start.p, cnt.p, I.inc.p);
-    TE_CHECK_HIP(hipGetLastError());
+    TE_CHECK_HIP(hipMemsetAsync(cnt.p, 0, n * sizeof(int32_t), s));
+    hipLaunchKernelGGL(k_inc_count, dim3(g), dim3(256), 0, s, cells, ne, npe, a0, cnt.p);
+    scan_counts(cnt.p, I.start.p, n, bs, s);
+    TE_CHECK_HIP(hipMemsetAsync(cnt.p, 0, n * sizeof(int32_t), s));
+    hipLaunchKernelGGL(k_inc_fill, dim3(g), dim3(256), 0, s, cells, ne, npe, a0, I.start.p, cnt.p, I.inc.p);
     unsigned gn = (unsigned)std::min<int64_t>((n + 255) / 256 + 1, 1 << 20);
-    hipLaunchKernelGGL(k_inc_sort, dim3(gn), dim3(256), 0, s, I.start.p, I.inc.p, n);
+    if (sorted) hipLaunchKernelGGL(k_inc_sort, dim3(gn), dim3(256), 0, s, I.start.p, I.inc.p, n);
     TE_CHECK_HIP(hipGetLastError());
+}
+
+// (a pattern needs the cells of a node in no particular order)
+static void build_incidence(const te_mesh *m, int npe, Incidence &I, hipStream_t s, bool sorted = true) {
+    const int64_t n = m->n_nodes, ne = m->n_cells * (int64_t)npe;
+    TE_REQUIRE(first_bad_node(m->cells, ne, n, s) < 0, TE_EINVAL,
+               "cells reference a node index outside [0, n_nodes)");
+    DBuf<int32_t> cnt;
+    DBuf<int64_t> bs;
+    entry_lists(m->cells, m->n_cells, npe, 0, n, sorted, I, cnt, bs, s);
+    TE_CHECK_HIP(hipStreamSynchronize(s));
 }
 
 // ---------------------------------------------------------------------------
 // sparsity pattern
 // ---------------------------------------------------------------------------
-// Sorted distinct neighbours of node i in an LDS list (thread-private slice).
-// mode 0: write count to cnt[i]; mode 1: write the list to col[row_ptr[i]..].
-__global__ void __launch_bounds__(ABLK) k_pattern(const int32_t *__restrict__ cells, int npe,
-                                                  const int64_t *__restrict__ start, const int64_t *__restrict__ inc,
-                                                  int64_t n, int mode, int32_t *__restrict__ cnt,
-                                                  const int64_t *__restrict__ row_ptr, int32_t *__restrict__ col,
-                                                  int32_t *__restrict__ overflow) {
-    __shared__ int32_t lst[ABLK * PCAP];
-    int64_t i = (int64_t)blockIdx.x * ABLK + threadIdx.x;
-    if (i >= n) return;
-    int32_t *L = lst + threadIdx.x;  // strided by ABLK to spread banks
-    int len = 0;
-    bool over = false;
-    for (int64_t e = start[i]; e < start[i + 1] && !over; ++e) {
-        const int64_t cell = inc[e] / npe;
-        for (int b = 0; b < npe; ++b) {
-            int32_t v = cells[cell * npe + b];
-            // binary search for v in L[0..len)
-            int lo = 0, hi = len;
-            while (lo < hi) {
-                int mid = (lo + hi) >> 1;
-                if (L[mid * ABLK] < v) lo = mid + 1;
-                else hi = mid;
-            }
-            if (lo < len && L[lo * ABLK] == v) continue;
-            if (len == PCAP) {
-                over = true;
-                break;
-            }
-            for (int k = len; k > lo; --k) L[k * ABLK] = L[(k - 1) * ABLK];
-            L[lo * ABLK] = v;
-            ++len;
+// The distinct nodes of one node's cells, found by one wave: hashed into LDS
+// with linear probing, then each one's rank among them by counting.
+constexpr int PTAB = 256;  // slots, more than PCAP
+struct RowSet {
+    int32_t key[PTAB];     // node, -1 = empty
+    int16_t pos[PTAB];     // its position in the ascending row (after rank)
+    union {
+        struct {
+            int32_t lst[PTAB];   // the nodes in the order of their arrival
+            int16_t at[PTAB];    // and their slots
+        };
+        unsigned long long hit[PCAP];   // k_stiff, once the ranks are known
+    };
+    int32_t num, over;
+};
+__device__ __forceinline__ uint32_t row_hash(int32_t v) { return ((uint32_t)v * 2654435761u) >> 24; }
+
+// the slot of a node, which the set has to hold
+__device__ __forceinline__ int row_find(const RowSet &R, int32_t v) {
+    uint32_t h = row_hash(v);
+    for (int probe = 0; probe < PTAB && R.key[h] != v; ++probe) h = (h + 1) & (PTAB - 1);
+    return (int)h;
+}
+__device__ __forceinline__ void row_clear(RowSet &R) {
+    for (int t = threadIdx.x; t < PTAB; t += 64) R.key[t] = -1;
+    if (threadIdx.x == 0) R.num = R.over = 0;
+    __syncthreads();
+}
+// puts a node into the set -> its slot
+__device__ __forceinline__ int row_insert(RowSet &R, int32_t v) {
+    uint32_t h = row_hash(v);
+    for (int probe = 0; probe < PTAB; ++probe) {
+        const int32_t old = atomicCAS(&R.key[h], -1, v);
+        if (old == -1) {
+            const int k = atomicAdd(&R.num, 1);
+            R.lst[k] = v;
+            R.at[k] = (int16_t)h;
         }
+        if (old == -1 || old == v) return (int)h;
+        h = (h + 1) & (PTAB - 1);
     }
-    if (over) {
-        *overflow = 1;
-        return;
-    }
-    if (mode == 0) {
-        cnt[i] = len;
-    } else {
-        // row_ptr comes from the caller: never write past its row
-        if (row_ptr[i + 1] - row_ptr[i] != len) {
-            *overflow = 2;
-            return;
+    R.over = 1;
+    return 0;
+}
+// -> the number of distinct nodes, PCAP + 1 if there are more than PCAP
+__device__ __forceinline__ int row_count(const RowSet &R) {
+    __syncthreads();
+    return R.over || R.num > PCAP ? PCAP + 1 : R.num;
+}
+// Sorted distinct neighbours of a node, one wave per node.  col null: their
+// number to cnt[i]; otherwise the list to col[row_ptr[i] ..].
+//   An insertion into a sorted list of one thread per node (48 KB of LDS for 64
+// nodes) took 1.19 ms on 524,576 P2 nodes; now 0.151 ms.
+__global__ void __launch_bounds__(64) k_pattern(const int32_t *__restrict__ cells, int npe,
+                                                const int64_t *__restrict__ start, const int64_t *__restrict__ inc,
+                                                int64_t n, int32_t *__restrict__ cnt,
+                                                const int64_t *__restrict__ row_ptr, int32_t *__restrict__ col,
+                                                int32_t *__restrict__ overflow) {
+    __shared__ RowSet R;
+    const int lane = threadIdx.x;
+    for (int64_t i = xcd_logical_block(blockIdx.x, gridDim.x); i < n; i += gridDim.x) {
+        const int64_t e0 = start[i];
+        const int total = (int)(start[i + 1] - e0) * npe;
+        row_clear(R);
+        for (int t = lane; t < total; t += 64) {
+            const int e = t / npe;
+            row_insert(R, cells[inc[e0 + e] / npe * npe + (t - e * npe)]);
         }
-        int32_t *o = col + row_ptr[i];
-        for (int k = 0; k < len; ++k) o[k] = L[k * ABLK];
+        const int m = row_count(R);
+        if (m > PCAP) {
+            if (lane == 0) *overflow = 1;
+        } else if (!col) {
+            if (lane == 0) cnt[i] = m;
+        } else if (row_ptr[i + 1] - row_ptr[i] != m) {
+            // row_ptr comes from the caller: never write past its row
+            if (lane == 0) *overflow = 2;
+        } else {
+            for (int x = lane; x < m; x += 64) {
+                const int32_t v = R.lst[x];
+                int r = 0;
+                for (int y = 0; y < m; ++y) r += R.lst[y] < v ? 1 : 0;
+                col[row_ptr[i] + r] = v;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -209,11 +298,11 @@ struct Geo {
     double vol;
 };
 
-__device__ __forceinline__ Geo cell_geo(const double *__restrict__ X, const int32_t *__restrict__ cv) {
-    double x0[3], J[3][3];
-    for (int c = 0; c < 3; ++c) x0[c] = X[(int64_t)cv[0] * 3 + c];
+// x: the four vertices
+__device__ __forceinline__ Geo vertex_geo(const double *x) {
+    double J[3][3];
     for (int k = 0; k < 3; ++k)
-        for (int c = 0; c < 3; ++c) J[c][k] = X[(int64_t)cv[k + 1] * 3 + c] - x0[c];  // columns = edges
+        for (int c = 0; c < 3; ++c) J[c][k] = x[(k + 1) * 3 + c] - x[c];  // columns = edges
     // inverse via cofactors: rows of J^-1 are the gradients of l1..l3
     double det = J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) - J[0][1] * (J[1][0] * J[2][2] - J[1][2] * J[2][0]) +
                  J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
@@ -231,6 +320,12 @@ __device__ __forceinline__ Geo cell_geo(const double *__restrict__ X, const int3
     for (int c = 0; c < 3; ++c) g.G[0][c] = -(g.G[1][c] + g.G[2][c] + g.G[3][c]);
     g.vol = fabs(det) / 6.0;
     return g;
+}
+__device__ __forceinline__ Geo cell_geo(const double *__restrict__ X, const int32_t *__restrict__ cv) {
+    double x[12];
+    for (int k = 0; k < 4; ++k)
+        for (int c = 0; c < 3; ++c) x[k * 3 + c] = X[(int64_t)cv[k] * 3 + c];
+    return vertex_geo(x);
 }
 
 // Element tables are indexed by runtime node numbers; to keep them out of
@@ -287,8 +382,8 @@ struct AsmArgs {
     const double *T;   // [nrhs][N]
     const double *f;   // [nrhs][N][3] or null
     const int64_t *row_ptr;
-    const int32_t *col;
-    double *val;       // stiffness values (k_stiff)
+    int32_t *col;      // columns and values of the stiffness (k_stiff)
+    double *val;
     double *b;         // [N][3][nrhs]
     int nrhs;
 };
@@ -422,142 +517,238 @@ static void launch_load(const AsmArgs &a, int degree, hipStream_t s) {
     TE_CHECK_HIP(hipGetLastError());
 }
 
-// Stiffness rows, one wave per node row.  The row's incident cells are taken
-// in chunks of SCH: lanes compute the chunk's cell geometries, then the
-// element blocks K_e[a][b] of all (cell, b) pairs with the position of block
-// b in the row; lane q owns blocks q, q + 64, q + 128 of the row (at most
-// PCAP) and adds the chunk's blocks to them in cell order.
-constexpr int SCH = 16;
+// coefficients of the integral of grad phi_a (x) grad phi_b over a P2 cell,
+// divided by its volume.  A basis gradient is 4 l_m1 G_k1 + 4 l_m2 G_k2 for an
+// edge (k1, k2) = (m2, m1), and (4 l_a - 1) G_a for a vertex; with
+// int l_i l_j = (1 + d_ij) |K| / 20 and int l_i = |K| / 4.
+struct P2Grad {
+    int k1, k2, m1, m2;
+    double c, w;   // the constant term of G_k1 and whether there is a G_k2 term
+};
+__device__ __forceinline__ P2Grad p2_terms(int a) {
+    // the six edges (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), four bits each
+    const int e = 4 * (a < 4 ? 0 : a - 4), i = (0x211000 >> e) & 15, j = (0x332321 >> e) & 15;
+    if (a < 4) return {a, a, a, a, -1.0, 0.0};
+    return {i, j, j, i, 0.0, 1.0};
+}
 
+// Stiffness rows and their columns, one wave per node row.  The distinct nodes
+// of the row's cells are its columns.  The cells are then taken CH
+// at a time: lanes compute their geometries, then one lane per (cell, b) the
+// element block K_e[a][b]; the chunk's cells that meet a row block, and the b of
+// each, are gathered in four bits per cell.  Lane q owns blocks q, q + 64,
+// q + 128 of the row (at most PCAP) and adds the chunk's blocks to them in cell
+// order: block q in registers, the others, which few rows have, in place.
+//   Bound by the latency of the dependent steps (cells of the row, their nodes,
+// coordinates, blocks), so by the waves in flight: CH is what one pass over the
+// lanes takes.  With the columns written by a kernel before, 16 cells in LDS,
+// every block looked for in every cell and P2 integrals by quadrature: 3.03 +
+// 1.19 ms on 524,576 P2 nodes; now 1.41 ms for both, half of it the issue of 810
+// vector instructions per row.
 template <int DEG>
-__global__ void __launch_bounds__(64) k_stiff(AsmArgs A) {
-    constexpr int NPE = DEG == 1 ? 4 : 10;
-    static_assert(NPE % 2 == 0, "cell entries are read in pairs");
-    __shared__ double s_geo[SCH][15];  // gradients of the 4 barycentric coordinates, volume, lam, mu
-    __shared__ int32_t s_cv[SCH][NPE];
-    __shared__ int32_t s_a[SCH];
-    __shared__ double s_k[SCH * NPE][9];
-    __shared__ __align__(8) int32_t s_pos[SCH * NPE];  // NPE is even: a cell's entries read as int2
-    __shared__ int32_t s_col[PCAP];                    // the row's columns, searched in LDS
-    const int lane = threadIdx.x;
-    for (int64_t i = blockIdx.x; i < A.n; i += gridDim.x) {
+__global__ void __launch_bounds__(64, 4) k_stiff(AsmArgs A, int64_t nnzb, int32_t *__restrict__ overflow) {
+    constexpr int NPE = DEG == 1 ? 4 : 10, CH = 64 / NPE;
+    static_assert(CH <= 16, "four bits per cell");
+    __shared__ RowSet R;
+    __shared__ double s_geo[CH][15];  // the vertices, then the gradients of the 4 barycentric coordinates, volume, lam, mu
+    __shared__ double s_k[64][9];
+    __shared__ int32_t s_dup;
+    const int lane = threadIdx.x, c = lane / NPE, bb = lane - c * NPE;   // lane (c, bb): cell, local node
+    for (int64_t i = xcd_logical_block(blockIdx.x, gridDim.x); i < A.n; i += gridDim.x) {
         const int64_t r0 = A.row_ptr[i], r1 = A.row_ptr[i + 1];
-        const int len = (int)(r1 - r0);
-        for (int t = lane; t < len; t += 64) s_col[t] = A.col[r0 + t];
-        double acc[3][9];
+        const int64_t e0 = A.start[i];
+        const int ne = (int)(A.start[i + 1] - e0);
+        int64_t ent = 0;   // of the lane's cell in the current chunk
+        int32_t v = 0;     // the node and its coordinates
+        double x[3] = {0.0, 0.0, 0.0};
+        int slot = 0;
+        auto fetch = [&](int cb) {
+            if (c < CH && cb + c < ne) {
+                ent = A.inc[e0 + cb + c];
+                v = A.cells[ent / NPE * NPE + bb];
+            }
+        };
+        auto fetch_x = [&](int cb) {
+            if (c < CH && cb + c < ne && bb < 4)
+                for (int k = 0; k < 3; ++k) x[k] = A.X[(int64_t)v * 3 + k];
+        };
+        row_clear(R);
+        // the first chunk last: what it fetched is what the loop below starts with
+        for (int cb = ne > 0 ? (ne - 1) / CH * CH : -1; cb >= 0; cb -= CH) {
+            fetch(cb);
+            if (cb == 0) fetch_x(0);
+            if (c < CH && cb + c < ne) slot = row_insert(R, v);
+        }
+        const int len = row_count(R);
+        // row_ptr comes from the caller: never write past its row
+        const int bad = len > PCAP ? 1 : r1 - r0 != len || r0 < 0 || r1 > nnzb ? 2 : 0;
+        if (bad) {
+            if (lane == 0) *overflow = bad;
+            __syncthreads();
+            continue;
+        }
+        for (int y0 = lane; y0 < len; y0 += 64) {
+            const int32_t w = R.lst[y0];
+            int r = 0;
+            for (int y = 0; y < len; ++y) r += R.lst[y] < w ? 1 : 0;
+            A.col[r0 + r] = w;
+            R.pos[R.at[y0]] = (int16_t)r;
+        }
+        if (lane == 0) s_dup = 0;
+        double acc[9];
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int k = 0; k < 9; ++k) acc[q][k] = 0.0;
-        const int64_t e0 = A.start[i], e1 = A.start[i + 1];
-        for (int64_t cb = e0; cb < e1; cb += SCH) {
-            const int nc = (int)((e1 - cb) < SCH ? (e1 - cb) : SCH);
+        for (int k = 0; k < 9; ++k) acc[k] = 0.0;
+        for (int cb = 0; cb < ne; cb += CH) {
+            const int nc = ne - cb < CH ? ne - cb : CH;
+            const int a = (int)(ent % NPE);
+            __syncthreads();   // the ranks are taken, the last chunk is added
+            for (int t = lane; t < len; t += 64) R.hit[t] = 0;
+            if (c < nc && bb < 4)
+                for (int k = 0; k < 3; ++k) s_geo[c][bb * 3 + k] = x[k];
+            if (c < nc && bb < 2) {
+                const int64_t cell = ent / NPE;
+                s_geo[c][13 + bb] = A.coef ? A.coef[cell * 3 + bb] : bb ? A.mu : A.lam;
+            }
+            if (cb > 0 && c < nc) slot = row_find(R, v);
+            int p = R.pos[slot];
+            if (cb + CH < ne) {   // the next chunk's nodes meanwhile
+                fetch(cb + CH);
+                fetch_x(cb + CH);
+            }
+            __syncthreads();
             if (lane < nc) {
-                const int64_t ent = A.inc[cb + lane];
-                const int32_t *cv = A.cells + (ent / NPE) * NPE;
-                s_a[lane] = (int)(ent % NPE);
-                for (int b = 0; b < NPE; ++b) s_cv[lane][b] = cv[b];
-                const Geo g = cell_geo(A.X, cv);
+                const Geo g = vertex_geo(s_geo[lane]);
                 for (int k = 0; k < 4; ++k)
-                    for (int c = 0; c < 3; ++c) s_geo[lane][k * 3 + c] = g.G[k][c];
+                    for (int d = 0; d < 3; ++d) s_geo[lane][k * 3 + d] = g.G[k][d];
                 s_geo[lane][12] = g.vol;
-                s_geo[lane][13] = A.coef ? A.coef[(ent / NPE) * 3] : A.lam;
-                s_geo[lane][14] = A.coef ? A.coef[(ent / NPE) * 3 + 1] : A.mu;
             }
             __syncthreads();
-            for (int t = lane; t < nc * NPE; t += 64) {
-                const int c = t / NPE, bb = t % NPE, a = s_a[c];
+            if (c < nc) {
                 const double *G = s_geo[c];
-                const double vol = s_geo[c][12], lam = s_geo[c][13], mu = s_geo[c][14];
-                double K[9];
+                const double vol = G[12], lam = G[13], mu = G[14];
+                double H[3][3];   // int grad phi_a (x) grad phi_b / |K|
                 if (DEG == 1) {
-                    const double *ga = G + a * 3, *gb = G + bb * 3;
-                    const double dot = ga[0] * gb[0] + ga[1] * gb[1] + ga[2] * gb[2];
-                    for (int p = 0; p < 3; ++p)
-                        for (int q = 0; q < 3; ++q)
-                            K[p * 3 + q] =
-                                vol * (lam * ga[p] * gb[q] + mu * ga[q] * gb[p] + (p == q ? mu * dot : 0.0));
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+#pragma unroll
+                        for (int y = 0; y < 3; ++y) H[d][y] = G[a * 3 + d] * G[bb * 3 + y];
                 } else {
-                    // degree-2 integrand: 4-point rule (a,b,b,b), weights |K|/4
-                    const double qa = 0.5854101966249685, qb = 0.1381966011250105;
-                    for (int k = 0; k < 9; ++k) K[k] = 0.0;
-                    for (int qp = 0; qp < 4; ++qp) {
-                        const double l0 = qp == 0 ? qa : qb, l1 = qp == 1 ? qa : qb, l2 = qp == 2 ? qa : qb,
-                                     l3 = qp == 3 ? qa : qb;
-                        double ga[3], gb[3];
-                        p2_grad(a, l0, l1, l2, l3, G, ga);
-                        p2_grad(bb, l0, l1, l2, l3, G, gb);
-                        const double dot = ga[0] * gb[0] + ga[1] * gb[1] + ga[2] * gb[2];
-                        for (int p = 0; p < 3; ++p)
-                            for (int q = 0; q < 3; ++q)
-                                K[p * 3 + q] += lam * ga[p] * gb[q] + mu * ga[q] * gb[p] + (p == q ? mu * dot : 0.0);
+                    const P2Grad u = p2_terms(a), w = p2_terms(bb);
+                    auto mass = [](int x, int y) { return x == y ? 1.6 : 0.8; };   // 16 int l_x l_y / |K|
+                    const double m11 = mass(u.m1, w.m1) + u.c + w.c + u.c * w.c, m12 = w.w * (mass(u.m1, w.m2) + u.c);
+                    const double m21 = u.w * (mass(u.m2, w.m1) + w.c), m22 = u.w * w.w * mass(u.m2, w.m2);
+#pragma unroll
+                    for (int y = 0; y < 3; ++y) {
+                        const double b1 = G[w.k1 * 3 + y], b2 = G[w.k2 * 3 + y];
+                        const double h1 = m11 * b1 + m12 * b2, h2 = m21 * b1 + m22 * b2;
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) H[d][y] = G[u.k1 * 3 + d] * h1 + G[u.k2 * 3 + d] * h2;
                     }
-                    const double w = 0.25 * vol;
-                    for (int k = 0; k < 9; ++k) K[k] *= w;
                 }
-                const int32_t v = s_cv[c][bb];
-                int lo = 0, hi = len;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_col[mid] < v) lo = mid + 1;
-                    else hi = mid;
-                }
-                s_pos[t] = (lo < len && s_col[lo] == v) ? lo : -1;  // -1 unreachable with a matching pattern
-                for (int k = 0; k < 9; ++k) s_k[t][k] = K[k];
+                const double dot = mu * (H[0][0] + H[1][1] + H[2][2]);
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+#pragma unroll
+                    for (int y = 0; y < 3; ++y)
+                        s_k[lane][d * 3 + y] = vol * (lam * H[d][y] + mu * H[y][d] + (d == y ? dot : 0.0));
+                const unsigned long long old = atomicOr(&R.hit[p], (unsigned long long)(bb + 1) << (4 * c));
+                if ((old >> (4 * c)) & 15) s_dup = 1;
             }
             __syncthreads();
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int blk = lane + 64 * q;
-                if (blk < len)
-                    for (int c = 0; c < nc; ++c) {  // cells ascending; a cell meets a block at most once
-                        const int2 *pp = reinterpret_cast<const int2 *>(&s_pos[c * NPE]);
-                        int hit = -1;
-#pragma unroll
-                        for (int h = 0; h < NPE / 2; ++h) {
-                            const int2 v = pp[h];
-                            hit = v.x == blk ? 2 * h : hit;
-                            hit = v.y == blk ? 2 * h + 1 : hit;
-                        }
-                        if (hit >= 0)
-#pragma unroll
-                            for (int k = 0; k < 9; ++k) acc[q][k] += s_k[c * NPE + hit][k];
+            if (s_dup) {   // a cell names a node twice: the later local node counts
+                if (c < nc) atomicAnd(&R.hit[p], ~(15ull << (4 * c)));
+                __syncthreads();
+                for (int b = 0; b < NPE; ++b) {
+                    if (c < nc && bb == b) {
+                        atomicAnd(&R.hit[p], ~(15ull << (4 * c)));
+                        atomicOr(&R.hit[p], (unsigned long long)(bb + 1) << (4 * c));
                     }
+                    __syncthreads();
+                }
             }
-            __syncthreads();
-        }
+            auto add = [&](int blk, double (&v)[9]) {
+                unsigned long long hit = R.hit[blk];
+                while (hit) {   // cells ascending
+                    const int cc = __builtin_ctzll(hit) >> 2;
+                    const double *K = s_k[cc * NPE + (int)((hit >> (4 * cc)) & 15) - 1];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int blk = lane + 64 * q;
-            if (blk < len)
+                    for (int k = 0; k < 9; ++k) v[k] += K[k];
+                    hit &= ~(15ull << (4 * cc));
+                }
+            };
+            if (lane < len) add(lane, acc);
+            for (int blk = lane + 64; blk < len; blk += 64) {
+                double o[9], *dst = A.val + (r0 + blk) * 9;
 #pragma unroll
-                for (int k = 0; k < 9; ++k) A.val[(r0 + blk) * 9 + k] = acc[q][k];
+                for (int k = 0; k < 9; ++k) o[k] = cb == 0 ? 0.0 : dst[k];
+                add(blk, o);
+#pragma unroll
+                for (int k = 0; k < 9; ++k) dst[k] = o[k];
+            }
         }
+        if (lane < len)
+#pragma unroll
+            for (int k = 0; k < 9; ++k) A.val[(r0 + lane) * 9 + k] = acc[k];
+        __syncthreads();
     }
 }
 
-// Dirichlet elimination, one thread per row.  Lifting with the unconstrained
-// values first, then rows/columns of constrained DOFs zeroed, unit diagonal,
-// b_D = u_D.
-__global__ void k_dirichlet(int64_t n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                            double *__restrict__ val, double *__restrict__ b, const uint8_t *__restrict__ mask,
-                            const double *__restrict__ ubc) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        bool mi[3] = {mask[i * 3] != 0, mask[i * 3 + 1] != 0, mask[i * 3 + 2] != 0};
-        double bi[3] = {b[i * 3], b[i * 3 + 1], b[i * 3 + 2]};
-        for (int64_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
-            const int64_t J = col[k];
-            double *blk = val + k * 9;
-            for (int q = 0; q < 3; ++q) {
-                if (!mask[J * 3 + q]) continue;
-                double u = ubc ? ubc[J * 3 + q] : 0.0;
-                for (int p = 0; p < 3; ++p) bi[p] -= blk[p * 3 + q] * u;
+// Columns and values of the rows of a pattern whose row pointer the caller holds.
+// The flag is read after `also`, launches that need neither.
+template <typename F>
+static void stiffness_rows(const AsmArgs &a, int degree, int64_t nnzb, hipStream_t s, F &&also) {
+    DBuf<int32_t> ovf(1);
+    TE_CHECK_HIP(hipMemsetAsync(ovf.p, 0, sizeof(int32_t), s));
+    const unsigned gs = (unsigned)std::min<int64_t>(a.n, 1 << 18);
+    if (degree == 1) hipLaunchKernelGGL(k_stiff<1>, dim3(gs), dim3(64), 0, s, a, nnzb, ovf.p);
+    else hipLaunchKernelGGL(k_stiff<2>, dim3(gs), dim3(64), 0, s, a, nnzb, ovf.p);
+    TE_CHECK_HIP(hipGetLastError());
+    also();
+    int32_t h = 0;
+    TE_CHECK_HIP(hipMemcpyAsync(&h, ovf.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    TE_CHECK_HIP(hipStreamSynchronize(s));
+    TE_REQUIRE(h == 0, TE_EINVAL, h == 1 ? "a node couples to more than 192 nodes"
+                                         : "row_ptr does not match this mesh's sparsity pattern");
+}
+
+// Dirichlet elimination, eight lanes per row.  Lifting with the unconstrained
+// values first (every eighth block per lane, the eight sums added in a fixed
+// order), then rows/columns of constrained DOFs zeroed, unit diagonal,
+// b_D = u_D.  One thread per row strode over the columns and values of 64 rows
+// at a time: 0.273 ms on 524,576 P2 nodes (14.3 M blocks); now 0.080.
+__global__ void __launch_bounds__(256) k_dirichlet(int64_t n, const int64_t *__restrict__ row_ptr,
+                                                   const int32_t *__restrict__ col, double *__restrict__ val,
+                                                   double *__restrict__ b, const uint8_t *__restrict__ mask,
+                                                   const double *__restrict__ ubc) {
+    const int l = threadIdx.x & 7;
+    for (int64_t i0 = blockIdx.x * (int64_t)32; i0 < n; i0 += (int64_t)gridDim.x * 32) {
+        const int64_t i = i0 + (threadIdx.x >> 3);
+        double lift[3] = {0.0, 0.0, 0.0};
+        bool mi[3] = {false, false, false};
+        if (i < n) {
+            for (int p = 0; p < 3; ++p) mi[p] = mask[i * 3 + p] != 0;
+            for (int64_t k = row_ptr[i] + l; k < row_ptr[i + 1]; k += 8) {
+                const int64_t J = col[k];
+                const bool mj[3] = {mask[J * 3] != 0, mask[J * 3 + 1] != 0, mask[J * 3 + 2] != 0};
+                if (!(mi[0] || mi[1] || mi[2] || mj[0] || mj[1] || mj[2])) continue;
+                double *blk = val + k * 9;
+                for (int q = 0; q < 3; ++q) {
+                    if (!mj[q]) continue;
+                    const double u = ubc ? ubc[J * 3 + q] : 0.0;
+                    for (int p = 0; p < 3; ++p) lift[p] += blk[p * 3 + q] * u;
+                }
+                for (int p = 0; p < 3; ++p)
+                    for (int q = 0; q < 3; ++q)
+                        if (mi[p] || mj[q]) blk[p * 3 + q] = (J == i && p == q) ? 1.0 : 0.0;
             }
-            for (int p = 0; p < 3; ++p)
-                for (int q = 0; q < 3; ++q)
-                    if (mi[p] || mask[J * 3 + q]) blk[p * 3 + q] = (J == i && p == q) ? 1.0 : 0.0;
         }
-        for (int p = 0; p < 3; ++p) b[i * 3 + p] = mi[p] ? (ubc ? ubc[i * 3 + p] : 0.0) : bi[p];
+        for (int o = 4; o > 0; o >>= 1)
+            for (int p = 0; p < 3; ++p) lift[p] += __shfl_xor(lift[p], o, 64);
+        if (i < n && l < 3) {
+            const double bi = b[i * 3 + l] - (l == 0 ? lift[0] : l == 1 ? lift[1] : lift[2]);
+            const bool m = l == 0 ? mi[0] : l == 1 ? mi[1] : mi[2];
+            b[i * 3 + l] = m ? (ubc ? ubc[i * 3 + l] : 0.0) : bi;
+        }
     }
 }
 
@@ -911,28 +1102,21 @@ static void check_mesh(const te_mesh *m) {
 static void pattern_impl(const te_mesh *m, Incidence &I, int64_t *row_ptr, int32_t *col, hipStream_t s) {
     const int npe = m->degree == 1 ? 4 : 10;
     const int64_t n = m->n_nodes;
-    DBuf<int32_t> ovf(1);
+    DBuf<int32_t> ovf(1), cnt;
+    DBuf<int64_t> bs;
     TE_CHECK_HIP(hipMemsetAsync(ovf.p, 0, sizeof(int32_t), s));
-    unsigned g = (unsigned)((n + ABLK - 1) / ABLK);
+    if (!col) cnt.alloc(n);
+    hipLaunchKernelGGL(k_pattern, dim3((unsigned)std::min<int64_t>(n, 1 << 18)), dim3(64), 0, s, m->cells, npe,
+                       I.start.p, I.inc.p, n, cnt.p, row_ptr, col, ovf.p);
+    TE_CHECK_HIP(hipGetLastError());
+    int32_t h = 0;
+    TE_CHECK_HIP(hipMemcpyAsync(&h, ovf.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    TE_CHECK_HIP(hipStreamSynchronize(s));
+    TE_REQUIRE(h == 0, TE_EINVAL, h == 1 ? "a node couples to more than 192 nodes"
+                                         : "row_ptr does not match this mesh's sparsity pattern");
     if (!col) {
-        DBuf<int32_t> cnt(n);
-        hipLaunchKernelGGL(k_pattern, dim3(g), dim3(ABLK), 0, s, m->cells, npe, I.start.p, I.inc.p, n, 0, cnt.p,
-                           nullptr, nullptr, ovf.p);
-        TE_CHECK_HIP(hipGetLastError());
-        int32_t h = 0;
-        TE_CHECK_HIP(hipMemcpyAsync(&h, ovf.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        scan_counts(cnt.p, row_ptr, n, bs, s);
         TE_CHECK_HIP(hipStreamSynchronize(s));
-        TE_REQUIRE(h == 0, TE_EINVAL, "a node couples to more than %d nodes", PCAP);
-        scan_counts(cnt.p, row_ptr, n, s);
-    } else {
-        hipLaunchKernelGGL(k_pattern, dim3(g), dim3(ABLK), 0, s, m->cells, npe, I.start.p, I.inc.p, n, 1, nullptr,
-                           row_ptr, col, ovf.p);
-        TE_CHECK_HIP(hipGetLastError());
-        int32_t h = 0;
-        TE_CHECK_HIP(hipMemcpyAsync(&h, ovf.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        TE_CHECK_HIP(hipStreamSynchronize(s));
-        TE_REQUIRE(h == 0, TE_EINVAL, h == 1 ? "a node couples to more than 192 nodes"
-                                             : "row_ptr does not match this mesh's sparsity pattern");
     }
 }
 
@@ -945,7 +1129,7 @@ extern "C" int fe_assemble_pattern(const te_mesh *mesh, int64_t *row_ptr, int64_
         check_mesh(mesh);
         TE_REQUIRE(row_ptr && nnzb_out, TE_EINVAL, "row_ptr / nnzb_out is NULL");
         Incidence I;
-        build_incidence(mesh, mesh->degree == 1 ? 4 : 10, I, stream);
+        build_incidence(mesh, mesh->degree == 1 ? 4 : 10, I, stream, false);
         pattern_impl(mesh, I, row_ptr, nullptr, stream);
         TE_CHECK_HIP(hipMemcpyAsync(nnzb_out, row_ptr + mesh->n_nodes, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
         TE_CHECK_HIP(hipStreamSynchronize(stream));
@@ -978,16 +1162,11 @@ extern "C" int fe_assemble_thermoelastic(const te_mesh *mesh, const te_material 
         TE_CHECK_HIP(hipStreamSynchronize(stream));
         TE_REQUIRE(nnzb == A->nnzb, TE_EINVAL, "A.nnzb (%lld) != row_ptr[N] (%lld)", (long long)A->nnzb,
                    (long long)nnzb);
-        pattern_impl(mesh, I, A->row_ptr, A->col_idx, stream);
         AsmArgs a{mesh->coords, mesh->cells, npe, I.start.p, I.inc.p, mesh->n_nodes, lam, mu, calpha, mat->T_ref,
                   nullptr, T, f, A->row_ptr, A->col_idx, A->val, b, 1};
-        const unsigned gs = (unsigned)std::min<int64_t>(mesh->n_nodes, 1 << 18);
-        if (mesh->degree == 1) hipLaunchKernelGGL(k_stiff<1>, dim3(gs), dim3(64), 0, stream, a);
-        else hipLaunchKernelGGL(k_stiff<2>, dim3(gs), dim3(64), 0, stream, a);
-        TE_CHECK_HIP(hipGetLastError());
-        launch_load(a, mesh->degree, stream);
+        stiffness_rows(a, mesh->degree, nnzb, stream, [&] { launch_load(a, mesh->degree, stream); });
         if (dir_mask) {
-            unsigned gd = (unsigned)std::min<int64_t>((mesh->n_nodes + 255) / 256, 1 << 20);
+            unsigned gd = (unsigned)std::min<int64_t>((mesh->n_nodes + 31) / 32, 1 << 20);
             hipLaunchKernelGGL(k_dirichlet, dim3(gd), dim3(256), 0, stream, mesh->n_nodes, A->row_ptr, A->col_idx,
                                A->val, b, dir_mask, u_bc);
             TE_CHECK_HIP(hipGetLastError());
@@ -1073,42 +1252,30 @@ extern "C" int fe_assemble_thermoelastic_materials(const te_mesh *mesh, const te
                    (long long)nnzb);
         // node -> (face, local node) entries of the pressure faces, in face order
         const bool has_p = pressure && pressure->n_faces > 0;
-        DBuf<int64_t> pptr, pent;
+        Incidence PF;
+        DBuf<int32_t> fcnt;
+        DBuf<int64_t> fbs;
         const int npf = mesh->degree == 1 ? 3 : 6;
         if (has_p) {
             TE_REQUIRE(pressure->faces && pressure->p, TE_EINVAL, "pressure faces / values are NULL");
-            std::vector<int32_t> fh;
-            download(fh, pressure->faces, (size_t)pressure->n_faces * npf, stream);
-            std::vector<int64_t> cnt(n + 1, 0);
-            const int a0 = mesh->degree == 1 ? 0 : 3;  // P2 vertices carry no pressure load
-            for (int64_t q = 0; q < (int64_t)fh.size(); ++q) {
-                TE_REQUIRE(fh[q] >= 0 && fh[q] < n, TE_EINVAL, "pressure face %lld has a node outside the mesh",
-                           (long long)(q / npf));
-                if (q % npf >= a0) ++cnt[fh[q] + 1];
-            }
-            for (int64_t i = 0; i < n; ++i) cnt[i + 1] += cnt[i];
-            std::vector<int64_t> ent(cnt[n]), fill(cnt.begin(), cnt.end() - 1);
-            for (int64_t q = 0; q < (int64_t)fh.size(); ++q)
-                if (q % npf >= a0) ent[fill[fh[q]]++] = q;
-            upload(pptr, cnt, stream);
-            upload(pent, ent, stream);
+            const int64_t q = first_bad_node(pressure->faces, pressure->n_faces * npf, n, stream);
+            TE_REQUIRE(q < 0, TE_EINVAL, "pressure face %lld has a node outside the mesh", (long long)(q / npf));
+            // P2 vertices carry no pressure load
+            entry_lists(pressure->faces, pressure->n_faces, npf, mesh->degree == 1 ? 0 : 3, n, true, PF, fcnt, fbs,
+                        stream);
         }
-        pattern_impl(mesh, I, A->row_ptr, A->col_idx, stream);
         AsmArgs a{mesh->coords, mesh->cells, npe, I.start.p, I.inc.p, n, 0.0, 0.0, 0.0, mat->T_ref,
                   coef.p, T, f, A->row_ptr, A->col_idx, A->val, b, 1};
-        const unsigned gs = (unsigned)std::min<int64_t>(n, 1 << 18);
-        if (mesh->degree == 1) hipLaunchKernelGGL(k_stiff<1>, dim3(gs), dim3(64), 0, stream, a);
-        else hipLaunchKernelGGL(k_stiff<2>, dim3(gs), dim3(64), 0, stream, a);
-        TE_CHECK_HIP(hipGetLastError());
-        launch_load(a, mesh->degree, stream);
-        if (has_p) {
+        stiffness_rows(a, mesh->degree, nnzb, stream, [&] {
+            launch_load(a, mesh->degree, stream);
+            if (!has_p) return;
             const unsigned gp = (unsigned)std::min<int64_t>((n + 255) / 256, 1 << 20);
-            hipLaunchKernelGGL(k_pressure, dim3(gp), dim3(256), 0, stream, n, pptr.p, pent.p, npf, pressure->faces,
-                               pressure->p, mesh->coords, b);
+            hipLaunchKernelGGL(k_pressure, dim3(gp), dim3(256), 0, stream, n, PF.start.p, PF.inc.p, npf,
+                               pressure->faces, pressure->p, mesh->coords, b);
             TE_CHECK_HIP(hipGetLastError());
-        }
+        });
         if (dir_mask) {
-            const unsigned gd = (unsigned)std::min<int64_t>((n + 255) / 256, 1 << 20);
+            const unsigned gd = (unsigned)std::min<int64_t>((n + 31) / 32, 1 << 20);
             hipLaunchKernelGGL(k_dirichlet, dim3(gd), dim3(256), 0, stream, n, A->row_ptr, A->col_idx, A->val, b,
                                dir_mask, u_bc);
             TE_CHECK_HIP(hipGetLastError());
