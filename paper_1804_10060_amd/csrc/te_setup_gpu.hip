@@ -452,14 +452,27 @@ __global__ void __launch_bounds__(64 * (BR / 3))
 }
 
 // ---- strength of connection and diagonal -----------------------------------------
-__global__ void k_fro(int64_t nnzb, int bb, const double *__restrict__ val, double *__restrict__ fro) {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nnzb; k += (int64_t)gridDim.x * blockDim.x) {
-        double acc = 0.0;
-        for (int e = 0; e < bb; ++e) {
-            const double v = val[k * bb + e];
-            acc = __dadd_rn(acc, __dmul_rn(v, v));
+// Frobenius norms, one wave per 64 blocks: read in one piece into LDS (rows of
+// bb | 1 doubles, so that the lanes' sums meet different banks), each lane adds
+// one block's squares in order.  9-double blocks read by one thread each, 72
+// bytes apart, took 0.81 ms for 14.3 M 3x3 blocks; now 0.21.
+__global__ void __launch_bounds__(64) k_fro(int64_t nnzb, int bb, const double *__restrict__ val,
+                                            double *__restrict__ fro) {
+    extern __shared__ double s_v[];
+    const int lane = threadIdx.x, ld = bb | 1;
+    for (int64_t k0 = blockIdx.x * (int64_t)64; k0 < nnzb; k0 += (int64_t)gridDim.x * 64) {
+        const int m = (int)(nnzb - k0 < 64 ? nnzb - k0 : 64);
+        for (int t = lane; t < m * bb; t += 64) s_v[t / bb * ld + t % bb] = val[k0 * bb + t];
+        __syncthreads();
+        if (lane < m) {
+            double acc = 0.0;
+            for (int e = 0; e < bb; ++e) {
+                const double v = s_v[lane * ld + e];
+                acc = __dadd_rn(acc, __dmul_rn(v, v));
+            }
+            fro[k0 + lane] = __dsqrt_rn(acc);
         }
-        fro[k] = __dsqrt_rn(acc);
+        __syncthreads();
     }
 }
 __global__ void k_diag_fro(int64_t n, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
@@ -471,10 +484,18 @@ __global__ void k_diag_fro(int64_t n, const int64_t *__restrict__ ptr, const int
         dn[i] = d;
     }
 }
+// Rows of a pattern, eight lanes each: neighbouring lanes read neighbouring
+// entries, and a row of 27 entries is four steps deep instead of 27 (k_strength
+// 0.56 -> 0.10 ms, k_strong_sym 0.93 -> 0.19 ms for 524,576 such rows).
+constexpr int RL = 8;
+__device__ __forceinline__ int64_t row_of8() { return (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / RL; }
+__device__ __forceinline__ int64_t row_stride8() { return (int64_t)gridDim.x * blockDim.x / RL; }
+__device__ __forceinline__ int row_lane8() { return threadIdx.x % RL; }
+
 __global__ void k_strength(int64_t n, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
                            const double *__restrict__ dn, double *__restrict__ s /* in: fro, out: strength */) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
+    for (int64_t i = row_of8(); i < n; i += row_stride8())
+        for (int64_t k = ptr[i] + row_lane8(); k < ptr[i + 1]; k += RL) {
             const int32_t j = col[k];
             s[k] = (j == i) ? 0.0 : __ddiv_rn(s[k], __dsqrt_rn(__dmul_rn(dn[i], dn[j])));
         }
@@ -490,161 +511,79 @@ __global__ void k_diag_points(int64_t n, int b, const int64_t *__restrict__ ptr,
 }
 
 // ---- smoothed prolongator, numeric ---------------------------------------------------
-// P_iJ = [agg i = J] Q_i - w D_i^-1 sum_{j in row i, agg j = J} A_ij Q_j   (BS x 6 blocks);
-// one thread per row, terms in the order of A's row, the tentative part last
-template <int BS>
-__global__ void k_p_numeric(int64_t n, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                            const double *__restrict__ val, const int32_t *__restrict__ agg,
-                            const double *__restrict__ Q, const double *__restrict__ d, double omega,
-                            const int64_t *__restrict__ pptr, const int32_t *__restrict__ pcol,
-                            double *__restrict__ pval, int32_t *__restrict__ flag) {
-    constexpr int K = 6;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p0 = pptr[i], p1 = pptr[i + 1];
-        for (int64_t e = p0 * BS * K; e < p1 * BS * K; ++e) pval[e] = 0.0;
-        auto find = [&](int32_t a) -> int64_t {
-            int64_t lo = p0, hi = p1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (pcol[mid] < a) lo = mid + 1;
-                else hi = mid;
-            }
-            return (lo < p1 && pcol[lo] == a) ? lo : -1;
-        };
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-            const int32_t j = col[k];
-            const int32_t a = agg[j];
-            if (a < 0) continue;
-            const int64_t at = find(a);
-            if (at < 0) {
-                atomicOr(flag, 8);
-                continue;
-            }
-            double *o = pval + at * BS * K;
-            const double *av = val + k * BS * BS;
-            const double *qv = Q + (int64_t)j * BS * K;
-            for (int pp = 0; pp < BS; ++pp) {
-                const double f = omega / d[i * BS + pp];
-                for (int r = 0; r < BS; ++r) {
-                    const double ar = av[pp * BS + r];
-                    if (ar == 0.0) continue;
-                    for (int c = 0; c < K; ++c) o[pp * K + c] -= f * ar * qv[r * K + c];
-                }
-            }
-        }
-        const int32_t ai = agg[i];
-        if (ai >= 0) {
-            const int64_t at = find(ai);
-            if (at < 0) {
-                atomicOr(flag, 8);
-                continue;
-            }
-            double *o = pval + at * BS * K;
-            const double *qv = Q + i * BS * K;
-            for (int e = 0; e < BS * K; ++e) o[e] += qv[e];
-        }
-    }
-}
-
-// The same with one wave per row: lane (p, c) owns entry (p, c) of every
-// block of the row and accumulates in LDS, in the same order as above (A's row,
-// then the rows of the block, the tentative part last).  Dynamic LDS: mcap
-// blocks of BS x 6 values, then mcap column indices.
+// P_iJ = [agg i = J] Q_i - w D_i^-1 sum_{j in row i, agg j = J} A_ij Q_j   (BS x 6 blocks),
+// one wave per row.  Lane (g, c) owns column
+// c of output block g of the ten taken at a time and adds the terms of the A
+// entries whose aggregate is that block's, in A's row order, in registers; the
+// tentative part comes last.
+//   Bound by latency: an entry at a time for the whole wave, accumulated in LDS
+// by 18 of 64 lanes, took 3.09 ms on a 524,576-node P2 disc (27 entries and five
+// aggregates per row); now 1.87 ms.
 template <int BS>
 __global__ void __launch_bounds__(64) k_p_wave(int64_t n, const int64_t *__restrict__ ptr,
                                                const int32_t *__restrict__ col, const double *__restrict__ val,
                                                const int32_t *__restrict__ agg, const double *__restrict__ Q,
                                                const double *__restrict__ d, double omega,
                                                const int64_t *__restrict__ pptr, const int32_t *__restrict__ pcol,
-                                               double *__restrict__ pval, int32_t *__restrict__ flag, int mcap) {
-    constexpr int K = 6, BB = BS * K;
-    static_assert(BB <= 64, "block larger than a wave");
-    extern __shared__ double s_dyn[];
-    double *s_acc = s_dyn;
-    int32_t *s_pc = reinterpret_cast<int32_t *>(s_dyn + (size_t)mcap * BB);
-    const int lane = threadIdx.x;
-    const bool on = lane < BB;
-    const int p = on ? lane / K : 0, c = on ? lane % K : 0;
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        const int64_t p0 = pptr[i];
-        const int m = (int)(pptr[i + 1] - p0);
-        if (m > mcap) {  // uniform; cannot happen with mcap = the longest row
-            if (lane == 0) atomicOr(flag, 4);
-            continue;
-        }
-        for (int t = lane; t < m * BB; t += 64) s_acc[t] = 0.0;
-        for (int t = lane; t < m; t += 64) s_pc[t] = pcol[p0 + t];
-        __syncthreads();
-        auto find = [&](int32_t a) -> int {
-            int lo = 0, hi = m;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s_pc[mid] < a) lo = mid + 1;
-                else hi = mid;
-            }
-            return (lo < m && s_pc[lo] == a) ? lo : -1;
-        };
-        const double f = on ? omega / d[i * BS + p] : 0.0;
-        // the row's entries 64 at a time: every lane looks up one entry's
-        // column, aggregate and output slot at once; then the entries are
-        // applied in order, the block values and Q rows of U entries loaded
-        // before any of them is added (the updates of one slot keep their order)
-        const int64_t k1 = ptr[i + 1];
-        for (int64_t kc = ptr[i]; kc < k1; kc += 64) {
-            const int cnt = (int)((k1 - kc) < 64 ? (k1 - kc) : 64);
-            int jl = 0, atl = -1;
-            if (lane < cnt) {
-                jl = col[kc + lane];
-                const int32_t a = agg[jl];
-                if (a >= 0) {
-                    atl = find(a);
-                    if (atl < 0) {
-                        atomicOr(flag, 8);
-                        atl = -2;
-                    }
-                }
-            }
-            constexpr int U = 4;
-            for (int u0 = 0; u0 < cnt; u0 += U) {
-                double ar[U][BS], qr[U][BS];
-                int at[U];
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    const int u = u0 + t < cnt ? u0 + t : cnt - 1;
-                    at[t] = u0 + t < cnt ? __shfl(atl, u) : -1;
-                    const int32_t j = __shfl(jl, u);
-                    const double *av = val + (kc + u) * BS * BS + p * BS;
-                    const double *qv = Q + (int64_t)j * BS * K + c;
-#pragma unroll
-                    for (int r = 0; r < BS; ++r) {
-                        ar[t][r] = on ? av[r] : 0.0;
-                        qr[t][r] = on ? qv[r * K] : 0.0;
-                    }
-                }
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    if (at[t] < 0 || !on) continue;
-                    double o = s_acc[at[t] * BB + lane];
-                    for (int r = 0; r < BS; ++r) {
-                        if (ar[t][r] == 0.0) continue;
-                        o -= f * ar[t][r] * qr[t][r];
-                    }
-                    s_acc[at[t] * BB + lane] = o;
-                }
-            }
-        }
+                                               double *__restrict__ pval, int32_t *__restrict__ flag) {
+    constexpr int K = 6, BB = BS * K, NG = 64 / K;
+    __shared__ int32_t s_j[64];
+    const int lane = threadIdx.x, g = lane / K, c = lane - g * K;
+    for (int64_t i = xcd_logical_block(blockIdx.x, gridDim.x); i < n; i += gridDim.x) {
+        const int64_t p0 = pptr[i], k0 = ptr[i];
+        const int m = (int)(pptr[i + 1] - p0), len = (int)(ptr[i + 1] - k0);
         const int32_t ai = agg[i];
-        if (ai >= 0) {
-            const int at = find(ai);
-            if (at < 0) {
-                if (lane == 0) atomicOr(flag, 8);
-            } else if (on) {
-                s_acc[at * BB + lane] += Q[i * BS * K + lane];
+        double f[BS];
+#pragma unroll
+        for (int p = 0; p < BS; ++p) f[p] = omega / d[i * BS + p];
+        int64_t want = 0, found = 0;   // entries with an aggregate, and those whose block exists
+        for (int sg = 0; sg < m; sg += NG) {
+            const bool own = g < NG && sg + g < m;
+            const int32_t pc = own ? pcol[p0 + sg + g] : -1;
+            double acc[BS];
+#pragma unroll
+            for (int p = 0; p < BS; ++p) acc[p] = 0.0;
+            for (int kc = 0; kc < len; kc += 64) {
+                const int cnt = len - kc < 64 ? len - kc : 64;
+                int32_t j = 0, a = -1;
+                if (lane < cnt) {
+                    j = col[k0 + kc + lane];
+                    a = agg[j];
+                }
+                __syncthreads();   // the last chunk's nodes are read
+                s_j[lane] = j;
+                if (sg == 0) want += __popcll(__ballot(a >= 0));
+                uint64_t mine = 0;   // the entries of this lane's block
+#pragma unroll
+                for (int t = 0; t < NG; ++t) {
+                    const int32_t pt = __shfl(pc, t * K, 64);
+                    const uint64_t b = __ballot(a >= 0 && a == pt);
+                    if (g == t) mine = b;
+                    found += __popcll(b);
+                }
+                __syncthreads();
+                while (mine) {
+                    const int u = __builtin_ctzll(mine);
+                    mine &= mine - 1;
+                    const double *av = val + (k0 + kc + u) * (BS * BS);
+                    const double *qv = Q + (int64_t)s_j[u] * BB + c;
+                    double qr[BS];
+#pragma unroll
+                    for (int r = 0; r < BS; ++r) qr[r] = qv[r * K];
+#pragma unroll
+                    for (int p = 0; p < BS; ++p)
+#pragma unroll
+                        for (int r = 0; r < BS; ++r) acc[p] -= f[p] * av[p * BS + r] * qr[r];
+                }
+            }
+            if (own) {
+                const bool tent = pc == ai;
+#pragma unroll
+                for (int p = 0; p < BS; ++p)
+                    pval[(p0 + sg + g) * BB + p * K + c] = acc[p] + (tent ? Q[i * BB + p * K + c] : 0.0);
             }
         }
-        __syncthreads();
-        for (int t = lane; t < m * BB; t += 64) pval[p0 * BB + t] = s_acc[t];
-        __syncthreads();
+        if (lane == 0 && (want != found || (m == 0 && ai >= 0))) atomicOr(flag, 8);
     }
 }
 
@@ -707,41 +646,64 @@ __global__ void k_t_fill(int64_t tn, const int64_t *__restrict__ src, const int3
 // SELL-64: storage position r (slice r/64, lane r%64) holds row order[r]
 // BB > 0: the block size fixed at compile time, so a block's loads are all
 // issued before its stores; BB = 0 takes it from bb
+// One workgroup of four waves per slice, wave w the entries w, w + 4, ... of its
+// rows, whose blocks are read with neighbouring lanes on neighbouring doubles
+// and turned in LDS.  14.3 M 3x3 blocks: 2.31 ms with one wave per slice and each
+// lane reading its own row's blocks, 1.50 with four, now 1.10; 2.8 M 3x6 blocks
+// 0.75, 0.55 and 0.53.
 template <int BB>
-__global__ void k_pack_sell(int64_t nr, int bb_rt, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                            const double *__restrict__ val, const int32_t *__restrict__ order,
-                            const int32_t *__restrict__ colmap, const int32_t *__restrict__ slice_off,
-                            int64_t nslices, int32_t *__restrict__ scol, double *__restrict__ sval,
-                            float *__restrict__ sval32) {
+__global__ void __launch_bounds__(256) k_pack_sell(int64_t nr, int bb_rt, const int64_t *__restrict__ ptr,
+                                                   const int32_t *__restrict__ col, const double *__restrict__ val,
+                                                   const int32_t *__restrict__ order,
+                                                   const int32_t *__restrict__ colmap,
+                                                   const int32_t *__restrict__ slice_off, int64_t nslices,
+                                                   int32_t *__restrict__ scol, double *__restrict__ sval,
+                                                   float *__restrict__ sval32) {
+    constexpr bool TURN = BB > 0;
+    constexpr int LD = BB | 1;
+    __shared__ int64_t s_s0[64];
+    __shared__ int32_t s_len[64];
+    __shared__ double s_v[4][TURN ? 64 * LD : 1];
     const int bb = BB > 0 ? BB : bb_rt;
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < nslices * 64;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t sl = r / 64, l = r % 64;
-        const int64_t o0 = slice_off[sl], w = slice_off[sl + 1] - o0;
-        const bool real = r < nr;
-        const int64_t o = real ? order[r] : 0;
-        const int64_t s0 = real ? ptr[o] : 0;
-        const int64_t len = real ? ptr[o + 1] - s0 : 0;
-        int32_t last = 0;
-        for (int64_t k = 0; k < w; ++k) {
-            if (k < len) last = colmap[col[s0 + k]];
-            scol[(o0 + k) * 64 + l] = last;
+    const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int64_t sl = blockIdx.x; sl < nslices; sl += gridDim.x) {
+        const int64_t r = sl * 64 + l;
+        const int64_t o0 = slice_off[sl];
+        const int w = (int)(slice_off[sl + 1] - o0);
+        const int64_t o = r < nr ? order[r] : 0;
+        const int64_t s0 = r < nr ? ptr[o] : 0;
+        const int len = r < nr ? (int)(ptr[o + 1] - s0) : 0;
+        if constexpr (TURN) {
+            __syncthreads();   // the last slice is done with s_s0, s_len
+            if (wv == 0) {
+                s_s0[l] = s0;
+                s_len[l] = len;
+            }
+        }
+        for (int k0 = 0; k0 < w; k0 += 4) {
+            const int k = k0 + wv;
+            // beyond the row's end its last column, or 0 for a row without entries
+            if (k < w) scol[(o0 + k) * 64 + l] = len > 0 ? colmap[col[s0 + (k < len ? k : len - 1)]] : 0;
             const int64_t e0 = (o0 + k) * bb * 64;
-            if constexpr (BB > 0) {
-                double v[BB];
+            if constexpr (TURN) {
+                __syncthreads();
 #pragma unroll
-                for (int x = 0; x < BB; ++x) v[x] = k < len ? val[(s0 + k) * BB + x] : 0.0;
-#pragma unroll
-                for (int x = 0; x < BB; ++x) {
-                    sval[e0 + sell_val_off<sell_vw<double>()>(x, BB, (int)l)] = v[x];
-                    if (sval32) sval32[e0 + sell_val_off<sell_vw<float>()>(x, BB, (int)l)] = (float)v[x];
+                for (int t = 0; t < BB; ++t) {
+                    const int e = t * 64 + l, row = e / BB, x = e - row * BB;
+                    s_v[wv][row * LD + x] = k < s_len[row] ? val[(s_s0[row] + k) * BB + x] : 0.0;
                 }
+                __syncthreads();
+            }
+            if (k >= w) continue;
+            auto put = [&](int x, double v) {
+                sval[e0 + sell_val_off<sell_vw<double>()>(x, bb, l)] = v;
+                if (sval32) sval32[e0 + sell_val_off<sell_vw<float>()>(x, bb, l)] = (float)v;
+            };
+            if constexpr (TURN) {
+#pragma unroll
+                for (int x = 0; x < BB; ++x) put(x, s_v[wv][l * LD + x]);
             } else {
-                for (int x = 0; x < bb; ++x) {
-                    const double v = k < len ? val[(s0 + k) * bb + x] : 0.0;
-                    sval[e0 + sell_val_off<sell_vw<double>()>(x, bb, (int)l)] = v;
-                    if (sval32) sval32[e0 + sell_val_off<sell_vw<float>()>(x, bb, (int)l)] = (float)v;
-                }
+                for (int x = 0; x < bb; ++x) put(x, k < len ? val[(s0 + k) * bb + x] : 0.0);
             }
         }
     }
@@ -1118,9 +1080,11 @@ void dev_strength(const DBsr &A, DBuf<double> &s, hipStream_t st) {
     TE_REQUIRE(A.br == A.bc, TE_EINVAL, "strength of a non-square block matrix");
     s.alloc(std::max<int64_t>(A.nnzb, 1));
     DBuf<double> dn(std::max<int64_t>(A.nr, 1));
-    hipLaunchKernelGGL(k_fro, dim3(grid_for(A.nnzb)), dim3(256), 0, st, A.nnzb, A.br * A.bc, A.val, s.p);
+    const int bb = A.br * A.bc;
+    hipLaunchKernelGGL(k_fro, dim3(grid_for(A.nnzb, 64)), dim3(64), 64 * (bb | 1) * sizeof(double), st, A.nnzb, bb, A.val,
+                       s.p);
     hipLaunchKernelGGL(k_diag_fro, dim3(grid_for(A.nr)), dim3(256), 0, st, A.nr, A.ptr, A.col, s.p, dn.p);
-    hipLaunchKernelGGL(k_strength, dim3(grid_for(A.nr)), dim3(256), 0, st, A.nr, A.ptr, A.col, dn.p, s.p);
+    hipLaunchKernelGGL(k_strength, dim3(grid_for(A.nr * RL)), dim3(256), 0, st, A.nr, A.ptr, A.col, dn.p, s.p);
     TE_CHECK_HIP(hipGetLastError());
     TE_CHECK_HIP(hipStreamSynchronize(st));
 }
@@ -1140,26 +1104,17 @@ void dev_smoothed_p(const DBsr &A, const DBuf<int32_t> &agg, int64_t nagg, const
     P.bc = 6;
     P.nr = A.nr;
     P.nc = nagg;
-    const int64_t mx = symbolic<true>(A, nullptr, nullptr, agg.p, 64, P, s);
+    symbolic<true>(A, nullptr, nullptr, agg.p, 64, P, s);
     P.val_own.alloc(std::max<int64_t>(P.nnzb * P.br * P.bc, 1));
     P.bind();
     DBuf<int32_t> flag(1);
     TE_CHECK_HIP(hipMemsetAsync(flag.p, 0, sizeof(int32_t), s));
-    const size_t lds = (size_t)std::max<int64_t>(mx, 1) * (P.br * 6 * sizeof(double) + sizeof(int32_t));
-    if (lds <= (size_t)48 << 10) {
-        const int mcap = (int)std::max<int64_t>(mx, 1);
-        if (A.br == 3)
-            hipLaunchKernelGGL(k_p_wave<3>, dim3(wave_grid(A.nr)), dim3(64), lds, s, A.nr, A.ptr, A.col, A.val, agg.p,
-                               Q.p, d.p, omega, P.ptr, P.col, P.val_own.p, flag.p, mcap);
-        else
-            hipLaunchKernelGGL(k_p_wave<6>, dim3(wave_grid(A.nr)), dim3(64), lds, s, A.nr, A.ptr, A.col, A.val, agg.p,
-                               Q.p, d.p, omega, P.ptr, P.col, P.val_own.p, flag.p, mcap);
-    } else if (A.br == 3)
-        hipLaunchKernelGGL(k_p_numeric<3>, dim3(grid_for(A.nr)), dim3(256), 0, s, A.nr, A.ptr, A.col, A.val, agg.p,
-                           Q.p, d.p, omega, P.ptr, P.col, P.val_own.p, flag.p);
+    if (A.br == 3)
+        hipLaunchKernelGGL(k_p_wave<3>, dim3(wave_grid(A.nr)), dim3(64), 0, s, A.nr, A.ptr, A.col, A.val, agg.p, Q.p,
+                           d.p, omega, P.ptr, P.col, P.val_own.p, flag.p);
     else
-        hipLaunchKernelGGL(k_p_numeric<6>, dim3(grid_for(A.nr)), dim3(256), 0, s, A.nr, A.ptr, A.col, A.val, agg.p,
-                           Q.p, d.p, omega, P.ptr, P.col, P.val_own.p, flag.p);
+        hipLaunchKernelGGL(k_p_wave<6>, dim3(wave_grid(A.nr)), dim3(64), 0, s, A.nr, A.ptr, A.col, A.val, agg.p, Q.p,
+                           d.p, omega, P.ptr, P.col, P.val_own.p, flag.p);
     TE_CHECK_HIP(hipGetLastError());
     TE_REQUIRE(read_flag(flag, s) == 0, TE_EHIP, "prolongator pattern misses a column");
 }
@@ -1491,7 +1446,7 @@ void dev_pack(Sell &S, const DBsr &M, const std::vector<int64_t> &hptr, const st
         if (fp32) S.val32.alloc(std::max<int64_t>(S.padded * bb, 1));
         else S.val32.release();
         auto kern = bb == 9 ? k_pack_sell<9> : bb == 18 ? k_pack_sell<18> : k_pack_sell<0>;
-        hipLaunchKernelGGL(kern, dim3(grid_for(S.nslices * 64)), dim3(256), 0, s, M.nr, bb, M.ptr, M.col, M.val,
+        hipLaunchKernelGGL(kern, dim3(wave_grid(S.nslices)), dim3(256), 0, s, M.nr, bb, M.ptr, M.col, M.val,
                            dorder.p, dmap.p, S.slice_off.p, S.nslices, S.col.p, S.val.p, fp32 ? S.val32.p : nullptr);
     }
     TE_CHECK_HIP(hipGetLastError());
@@ -1550,8 +1505,8 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {  // splitmix64 (Steele, 
 // mirror (j, i) (binary search in the sorted row j).
 __global__ void k_strong_sym(int64_t nr, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
                              const double *__restrict__ s, double theta, uint8_t *__restrict__ flag) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nr; i += (int64_t)gridDim.x * blockDim.x)
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
+    for (int64_t i = row_of8(); i < nr; i += row_stride8())
+        for (int64_t k = ptr[i] + row_lane8(); k < ptr[i + 1]; k += RL) {
             const int32_t j = col[k];
             if (j == i || !(s[k] >= theta)) continue;
             flag[k] = 1;
@@ -1576,38 +1531,69 @@ __global__ void k_mis_init(int64_t nr, const int64_t *__restrict__ ptr, const ui
     }
 }
 
-// out[i] = max(own, max over strong neighbours j of val(j)), val from the
-// current state and keys (first pass) or from the previous pass's output
-template <bool FIRST>
+// A round of the selection, eight lanes per row (a thread per row, every row in
+// two passes: 2 x 0.19 ms a round on a 524,576-node P2 disc; now at most 0.06 +
+// 0.08, falling as the nodes are decided).  m1[i] = the largest key* of i
+// and its strong neighbours, for the rows that the round needs: the undecided
+// ones and their strong neighbours (need[i] = round, set by the round before;
+// every row in round 0).
 __global__ void k_mis_max(int64_t nr, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
                           const uint8_t *__restrict__ flag, const int8_t *__restrict__ state,
-                          const int64_t *__restrict__ pk, const int64_t *__restrict__ in, int64_t *__restrict__ out) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nr; i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t m = FIRST ? state[i] * kKeyState + pk[i] : in[i];
-        for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
+                          const int64_t *__restrict__ pk, const int32_t *__restrict__ need, int32_t round,
+                          int64_t *__restrict__ m1) {
+    const int l = row_lane8();
+    for (int64_t i = row_of8(); i < nr; i += row_stride8()) {
+        if (need[i] != round) continue;
+        int64_t m = state[i] * kKeyState + pk[i];
+        for (int64_t k = ptr[i] + l; k < ptr[i + 1]; k += RL) {
             if (!flag[k]) continue;
             const int32_t j = col[k];
-            const int64_t v = FIRST ? state[j] * kKeyState + pk[j] : in[j];
+            const int64_t v = state[j] * kKeyState + pk[j];
             m = v > m ? v : m;
         }
-        out[i] = m;
+        for (int o = RL / 2; o > 0; o >>= 1) {
+            const int64_t v = __shfl_xor(m, o, RL);
+            m = v > m ? v : m;
+        }
+        if (l == 0) m1[i] = m;
     }
 }
 
-// undecided i joins if the distance-2 maximum is its own key*, is excluded if
-// that maximum belongs to a member; counts the nodes still undecided
-__global__ void k_mis_step(int64_t nr, const int64_t *__restrict__ pk, const int64_t *__restrict__ m2,
-                           int8_t *__restrict__ state, int32_t *__restrict__ left) {
+// an undecided i joins if the largest m1 of it and its strong neighbours (the
+// distance-2 maximum) is its own key*, is excluded if that maximum belongs to a
+// member, and otherwise asks for the next round's m1 and sets *left
+__global__ void k_mis_step(int64_t nr, const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
+                           const uint8_t *__restrict__ flag, const int64_t *__restrict__ pk,
+                           const int64_t *__restrict__ m1, int8_t *__restrict__ state, int32_t *__restrict__ need,
+                           int32_t round, int32_t *__restrict__ left) {
+    const int l = row_lane8();
     int32_t c = 0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nr; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = row_of8(); i < nr; i += row_stride8()) {
         if (state[i] != kUndecided) continue;
-        const int64_t own = kUndecided * kKeyState + pk[i];
-        if (m2[i] == own) state[i] = kIn;
-        else if (m2[i] / kKeyState == kIn) state[i] = kOut;
-        else ++c;
+        int64_t m = m1[i];
+        for (int64_t k = ptr[i] + l; k < ptr[i + 1]; k += RL)
+            if (flag[k]) {
+                const int64_t v = m1[col[k]];
+                m = v > m ? v : m;
+            }
+        for (int o = RL / 2; o > 0; o >>= 1) {
+            const int64_t v = __shfl_xor(m, o, RL);
+            m = v > m ? v : m;
+        }
+        if (m == kUndecided * kKeyState + pk[i]) {
+            if (l == 0) state[i] = kIn;
+        } else if (m / kKeyState == kIn) {
+            if (l == 0) state[i] = kOut;
+        } else {
+            if (l == 0) {
+                need[i] = round + 1;
+                c = 1;
+            }
+            for (int64_t k = ptr[i] + l; k < ptr[i + 1]; k += RL)
+                if (flag[k]) need[col[k]] = round + 1;
+        }
     }
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(left, c);
+    if (c) *left = 1;
 }
 
 // phase 1: a root's id, or the id of the (unique) root among the strong
@@ -2007,25 +1993,33 @@ int64_t dev_aggregate_mis2(const DBsr &A, const DBuf<double> &s, double theta, u
     const unsigned g = grid_for(n);
     DBuf<uint8_t> flag(std::max<int64_t>(A.nnzb, 1));
     DBuf<int8_t> state(n);
-    DBuf<int64_t> pk(n), m1(n), m2(n);
-    DBuf<int32_t> left(1), rid(n), agg1(n), dagg(n), orphan(1);
+    DBuf<int64_t> pk(n), m1(n);
+    // rounds between two looks at the nodes left: one beyond the last does nothing
+    constexpr int CHECK = 4;
+    DBuf<int32_t> left(CHECK), need(n), rid(n), agg1(n), dagg(n), orphan(1);
+    const unsigned g8 = grid_for(n * RL);
     TE_CHECK_HIP(hipMemsetAsync(flag.p, 0, std::max<int64_t>(A.nnzb, 1), st));
+    TE_CHECK_HIP(hipMemsetAsync(need.p, 0, n * sizeof(int32_t), st));
     TE_CHECK_HIP(hipMemsetAsync(orphan.p, 0, sizeof(int32_t), st));
-    hipLaunchKernelGGL(k_strong_sym, dim3(g), dim3(256), 0, st, n, A.ptr, A.col, s.p, theta, flag.p);
+    hipLaunchKernelGGL(k_strong_sym, dim3(g8), dim3(256), 0, st, n, A.ptr, A.col, s.p, theta, flag.p);
     hipLaunchKernelGGL(k_mis_init, dim3(g), dim3(256), 0, st, n, A.ptr, flag.p, seed, pk.p, state.p);
     TE_CHECK_HIP(hipGetLastError());
     // every round selects at least the undecided node of largest key, so at
     // most n rounds; in practice a few tens
-    for (int64_t round = 0;; ++round) {
+    for (int32_t round = 0;; round += CHECK) {
         TE_REQUIRE(round <= n, TE_EINVAL, "parallel aggregation did not finish");
-        TE_CHECK_HIP(hipMemsetAsync(left.p, 0, sizeof(int32_t), st));
-        hipLaunchKernelGGL((k_mis_max<true>), dim3(g), dim3(256), 0, st, n, A.ptr, A.col, flag.p, state.p, pk.p,
-                           nullptr, m1.p);
-        hipLaunchKernelGGL((k_mis_max<false>), dim3(g), dim3(256), 0, st, n, A.ptr, A.col, flag.p, state.p, pk.p,
-                           m1.p, m2.p);
-        hipLaunchKernelGGL(k_mis_step, dim3(g), dim3(256), 0, st, n, pk.p, m2.p, state.p, left.p);
+        TE_CHECK_HIP(hipMemsetAsync(left.p, 0, CHECK * sizeof(int32_t), st));
+        for (int c = 0; c < CHECK; ++c) {
+            hipLaunchKernelGGL(k_mis_max, dim3(g8), dim3(256), 0, st, n, A.ptr, A.col, flag.p, state.p, pk.p, need.p,
+                               round + c, m1.p);
+            hipLaunchKernelGGL(k_mis_step, dim3(g8), dim3(256), 0, st, n, A.ptr, A.col, flag.p, pk.p, m1.p, state.p,
+                               need.p, round + c, left.p + c);
+        }
         TE_CHECK_HIP(hipGetLastError());
-        if (read_flag(left, st) == 0) break;
+        int32_t h = 0;
+        TE_CHECK_HIP(hipMemcpyAsync(&h, left.p + CHECK - 1, sizeof(h), hipMemcpyDeviceToHost, st));
+        TE_CHECK_HIP(hipStreamSynchronize(st));
+        if (h == 0) break;
     }
     // aggregate ids by ascending root
     std::vector<int8_t> hs;
