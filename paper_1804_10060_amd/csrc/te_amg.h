@@ -128,6 +128,7 @@ struct amg_handle {
     te::DBuf<double> u, r, r_old, z, p, q, t, b;
     te::DBuf<double> partials, sums;
     te::DBuf<char> scal;
+    te::PinBuf pin;                // what the host reads of scal each iteration
     te::DBuf<int32_t> colsel;      // [64] column selector of copy_cols
     // launch shape of amg_pcg_solve_multi over a set of handles (te_autotune_multi):
     // persistent grid multiplier and work-item order (0: as given, 1: largest first)

@@ -87,6 +87,27 @@ struct DBuf {
     size_t bytes() const { return n * sizeof(T); }
 };
 
+// Owning pinned host buffer: the device copies into it without staging.
+struct PinBuf {
+    char *p = nullptr;
+    size_t n = 0;
+    PinBuf() = default;
+    PinBuf(const PinBuf &) = delete;
+    PinBuf &operator=(const PinBuf &) = delete;
+    ~PinBuf() {
+        if (p) (void)hipHostFree(p);
+    }
+    void alloc(size_t bytes) {   // once
+        const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&p), bytes, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            p = nullptr;
+            set_error("hipHostMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+            throw Error{TE_ENOMEM};
+        }
+        n = bytes;
+    }
+};
+
 // Copies between pageable host memory and the device.  Transfers of a few MB
 // and more go through a process-wide pinned staging buffer in chunks (the
 // DMA of one chunk overlaps the host copy of the next), which runs at the
