@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <cstdio>
 #include <string>
@@ -218,6 +219,9 @@ struct CgScalars {
     int32_t active[64];
     int32_t flag[64];  // 1: (p,Ap) <= 0, 2: (r,z) <= 0, 3: NaN
 };
+
+// what the host reads of CgScalars in an iteration: rr .. flag
+constexpr size_t kPinBytes = sizeof(CgScalars) - offsetof(CgScalars, rr);
 
 // ---- kernel launchers (te_kernels.hip) ------------------------------------
 template <typename T>

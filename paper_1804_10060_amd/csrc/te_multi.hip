@@ -28,29 +28,49 @@ struct Phase {
     int br = 0, bc = 0;
     int epi = 0;             // sparse: which epilogue
     int vop = 0;             // vector op
-    DBuf<char> items;
-    DBuf<int64_t> tile0;
-    DBuf<int32_t> mesh_of;
+    // in the set's table (Table): offsets first, addresses once it is on the device
+    size_t at_items = 0, at_tile0 = 0, at_mesh = 0;
+    const void *items = nullptr;
+    const int64_t *tile0 = nullptr;
+    const int32_t *mesh_of = nullptr;
     int nitems = 0;
     int64_t ntiles = 0;
     const double *coef = nullptr;  // per-mesh scalar for vector ops
-    int gmult = 1;                 // persistent grid: gmult x the resident workgroups
+    int gmult = 0;                 // grid: gmult x the resident workgroups, or (0) one per tile
+
+    void bind(const char *base) {
+        items = base + at_items;
+        tile0 = reinterpret_cast<const int64_t *>(base + at_tile0);
+        mesh_of = reinterpret_cast<const int32_t *>(base + at_mesh);
+    }
+};
+
+// The items, tile offsets and mesh numbers of all phases, put together on the
+// host and uploaded once.
+struct Table {
+    std::vector<char> h;
+    DBuf<char> d;
+    template <class T>
+    size_t add(const std::vector<T> &v) {
+        const size_t at = (h.size() + 15) / 16 * 16;
+        h.resize(at + v.size() * sizeof(T));
+        if (!v.empty()) std::memcpy(h.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
 };
 
 enum Epis { E_DOT, E_RESID, E_RESIDN, E_SET, E_ADD, E_INIT, E_STEP_LZ, E_STEP_L, E_STEP_Z, E_STEP };
 
 template <class Item>
-void upload_items(Phase &P, const std::vector<Item> &items, const std::vector<int64_t> &tiles,
-                  const std::vector<int32_t> &mesh, hipStream_t s) {
+void add_items(Phase &P, const std::vector<Item> &items, const std::vector<int64_t> &tiles,
+               const std::vector<int32_t> &mesh, Table &tab) {
     P.nitems = (int)items.size();
     std::vector<int64_t> t0(items.size() + 1, 0);
     for (size_t i = 0; i < items.size(); ++i) t0[i + 1] = t0[i] + tiles[i];
     P.ntiles = t0.back();
-    std::vector<char> raw(items.size() * sizeof(Item));
-    if (!items.empty()) std::memcpy(raw.data(), items.data(), raw.size());
-    upload(P.items, raw, s);
-    upload(P.tile0, t0, s);
-    upload(P.mesh_of, mesh, s);
+    P.at_items = tab.add(items);
+    P.at_tile0 = tab.add(t0);
+    P.at_mesh = tab.add(mesh);
 }
 
 inline int64_t tiles_of(const Sell &A) {
@@ -61,7 +81,8 @@ inline int64_t tiles_of(const Sell &A) {
 template <class Epi>
 GItem<double, Epi> gitem(const Sell &A, const double *x, const Epi &e, int mesh) {
     GItem<double, Epi> g{};
-    g.fmt = A.format;
+    TE_REQUIRE(A.format == (A.br == 3 ? FMT_SELL : FMT_ROWWAVE), TE_EINVAL, "grouped product: %d-row blocks in format %d",
+               A.br, A.format);
     if (A.format == FMT_SELL) g.sv = view<double>(A, A.val.p);
     else g.rv = rview<double>(A, A.val.p);
     g.x = x;
@@ -76,15 +97,17 @@ struct MultiState {
     bool flexible = false;
     int deg = 2;
     int Lmax = 1;
-    int gmult = 1;            // grid multiplier of every grouped launch
+    int gmult = 0;            // Phase::gmult of every grouped launch
     std::vector<int> order;   // mesh order of the work items
     // device scalars
     DBuf<double> rz, pq, alpha, beta, rr, bb, tol2, sums;
-    DBuf<int32_t> active, cand, flag, iters, tailmask;
+    DBuf<int32_t> marks;      // active, cand, flag, iters, tailmask: n each
+    int32_t *active = nullptr, *cand = nullptr, *flag = nullptr, *iters = nullptr, *tailmask = nullptr;
     DBuf<double> partials;
     MultiScal S{};
     // phases
-    Phase ap, update, dotrz, pupdate, tres, dense;
+    Table tab;
+    Phase ap, update, dotrz, pupdate, tres, self, dense;
     std::vector<Phase> jac, pre, resid, restrict_, prolong, postinit, post;  // per level (and step)
     std::vector<std::vector<Phase>> pre_steps, post_steps;
 };
@@ -95,42 +118,42 @@ double *level_x(amg_handle *h, int l) { return l == 0 ? h->z.p : h->L[l].w64.x.p
 template <int BR, int BC>
 void launch_sparse(const Phase &P, const int32_t *active, double *partials, hipStream_t s) {
     switch (P.epi) {
-        case E_DOT: group_launch<BR, BC, EpiDot>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+        case E_DOT: group_launch<BR, BC, EpiDot>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                  partials, s, P.gmult); break;
         case E_RESID:
-            group_launch<BR, BC, EpiResid<double, false>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiResid<double, false>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                           partials, s, P.gmult);
             break;
         case E_RESIDN:
-            group_launch<BR, BC, EpiResid<double, true>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiResid<double, true>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                          partials, s, P.gmult);
             break;
         case E_SET:
-            group_launch<BR, BC, EpiSet<double>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiSet<double>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                  partials, s, P.gmult);
             break;
         case E_ADD:
-            group_launch<BR, BC, EpiAdd<double>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiAdd<double>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                  partials, s, P.gmult);
             break;
         case E_INIT:
-            group_launch<BR, BC, EpiChebInit<double>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiChebInit<double>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                       partials, s, P.gmult);
             break;
         case E_STEP_LZ:
-            group_launch<BR, BC, EpiChebStep<double, true, true>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiChebStep<double, true, true>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                                   partials, s, P.gmult);
             break;
         case E_STEP_L:
-            group_launch<BR, BC, EpiChebStep<double, true, false>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiChebStep<double, true, false>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                                    partials, s, P.gmult);
             break;
         case E_STEP_Z:
-            group_launch<BR, BC, EpiChebStep<double, false, true>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiChebStep<double, false, true>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                                    partials, s, P.gmult);
             break;
         default:
-            group_launch<BR, BC, EpiChebStep<double, false, false>>(P.items.p, P.tile0.p, P.nitems, P.ntiles, active,
+            group_launch<BR, BC, EpiChebStep<double, false, false>>(P.items, P.tile0, P.nitems, P.ntiles, active,
                                                                     partials, s, P.gmult);
     }
 }
@@ -145,43 +168,43 @@ void run(const Phase &P, const int32_t *active, double *partials, hipStream_t s)
         else if (key == 63) launch_sparse<6, 3>(P, active, partials, s);
         else TE_REQUIRE(false, TE_EINVAL, "unsupported block shape in a grouped phase");
     } else if (P.kind == 1) {
-        const VItem *it = (const VItem *)P.items.p;
+        const VItem *it = (const VItem *)P.items;
         switch (P.vop) {
-            case VOP_UPDATE: group_vec_launch<VOP_UPDATE>(it, P.tile0.p, P.nitems, P.ntiles, active,
+            case VOP_UPDATE: group_vec_launch<VOP_UPDATE>(it, P.tile0, P.nitems, P.ntiles, active,
                                                           P.coef, partials, s, P.gmult); break;
-            case VOP_DOTRZ: group_vec_launch<VOP_DOTRZ>(it, P.tile0.p, P.nitems, P.ntiles, active,
+            case VOP_DOTRZ: group_vec_launch<VOP_DOTRZ>(it, P.tile0, P.nitems, P.ntiles, active,
                                                         P.coef, partials, s, P.gmult); break;
-            case VOP_PUPDATE: group_vec_launch<VOP_PUPDATE>(it, P.tile0.p, P.nitems, P.ntiles, active,
+            case VOP_PUPDATE: group_vec_launch<VOP_PUPDATE>(it, P.tile0, P.nitems, P.ntiles, active,
                                                             P.coef, partials, s, P.gmult); break;
-            case VOP_JACOBI: group_vec_launch<VOP_JACOBI>(it, P.tile0.p, P.nitems, P.ntiles, active,
+            case VOP_JACOBI: group_vec_launch<VOP_JACOBI>(it, P.tile0, P.nitems, P.ntiles, active,
                                                           P.coef, partials, s, P.gmult); break;
-            default: group_vec_launch<VOP_DOTSELF>(it, P.tile0.p, P.nitems, P.ntiles, active,
+            default: group_vec_launch<VOP_DOTSELF>(it, P.tile0, P.nitems, P.ntiles, active,
                                                    P.coef, partials, s, P.gmult);
         }
     } else {
-        const unsigned g = (unsigned)std::min<int64_t>(P.ntiles, (int64_t)GROUP_GRID * P.gmult);
-        hipLaunchKernelGGL(k_group_dense, dim3(g), dim3(BLK), 0, s, (const DItem *)P.items.p, P.tile0.p, P.nitems,
+        const unsigned g = group_grid(P.ntiles, GROUP_GRID, P.gmult);
+        hipLaunchKernelGGL(k_group_dense, dim3(g), dim3(BLK), 0, s, (const DItem *)P.items, P.tile0, P.nitems,
                            active);
         TE_CHECK_HIP(hipGetLastError());
     }
 }
 
 void reduce(const Phase &P, int nv, double *partials, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_group_reduce, dim3(P.nitems, nv), dim3(WAVE), 0, s, partials, P.tile0.p, P.mesh_of.p, nv,
+    hipLaunchKernelGGL(k_group_reduce, dim3(P.nitems, nv), dim3(WAVE), 0, s, partials, P.tile0, P.mesh_of, nv,
                        out);
     TE_CHECK_HIP(hipGetLastError());
 }
 
 // ---- building the phase tables ---------------------------------------------
 void build_phases(MultiState &M, hipStream_t s) {
-    const int n = M.n;
+    M.tab.h.clear();
     // CG phases on level 0
     {
         std::vector<GItem<double, EpiDot>> it;
         std::vector<int64_t> t;
         std::vector<int32_t> mo;
         std::vector<GItem<double, EpiResid<double, true>>> it2;
-        std::vector<VItem> up, rz, pu;
+        std::vector<VItem> up, rz, pu, bb;
         std::vector<int64_t> tv;
         for (int m : M.order) {
             amg_handle *h = M.H[m];
@@ -194,18 +217,21 @@ void build_phases(MultiState &M, hipStream_t s) {
             up.push_back(VItem{h->u.p, h->r.p, M.flexible ? h->r_old.p : nullptr, h->p.p, h->q.p, 0.0, nv, m});
             rz.push_back(VItem{h->r.p, nullptr, M.flexible ? h->r_old.p : nullptr, h->z.p, nullptr, 0.0, nv, m});
             pu.push_back(VItem{h->p.p, nullptr, nullptr, h->z.p, nullptr, 0.0, nv, m});
+            bb.push_back(VItem{nullptr, nullptr, nullptr, h->b.p, nullptr, 0.0, nv, m});
             tv.push_back((nv + VTILE - 1) / VTILE);
         }
         M.ap.kind = 0; M.ap.br = 3; M.ap.bc = 3; M.ap.epi = E_DOT;
-        upload_items(M.ap, it, t, mo, s);
+        add_items(M.ap, it, t, mo, M.tab);
         M.tres.kind = 0; M.tres.br = 3; M.tres.bc = 3; M.tres.epi = E_RESIDN;
-        upload_items(M.tres, it2, t, mo, s);
+        add_items(M.tres, it2, t, mo, M.tab);
         M.update.kind = 1; M.update.vop = VOP_UPDATE; M.update.coef = M.alpha.p;
-        upload_items(M.update, up, tv, mo, s);
+        add_items(M.update, up, tv, mo, M.tab);
+        M.self.kind = 1; M.self.vop = VOP_DOTSELF;
+        add_items(M.self, bb, tv, mo, M.tab);
         M.dotrz.kind = 1; M.dotrz.vop = VOP_DOTRZ;
-        upload_items(M.dotrz, rz, tv, mo, s);
+        add_items(M.dotrz, rz, tv, mo, M.tab);
         M.pupdate.kind = 1; M.pupdate.vop = VOP_PUPDATE; M.pupdate.coef = M.beta.p;
-        upload_items(M.pupdate, pu, tv, mo, s);
+        add_items(M.pupdate, pu, tv, mo, M.tab);
     }
     const int steps = M.deg - 1;
     M.jac.resize(M.Lmax);
@@ -263,15 +289,15 @@ void build_phases(MultiState &M, hipStream_t s) {
         }
         if (mo.empty()) continue;
         M.jac[l].kind = 1; M.jac[l].vop = VOP_JACOBI;
-        upload_items(M.jac[l], jv, jt, mo, s);
+        add_items(M.jac[l], jv, jt, mo, M.tab);
         M.resid[l].kind = 0; M.resid[l].br = bs; M.resid[l].bc = bs; M.resid[l].epi = E_RESID;
-        upload_items(M.resid[l], ri, tres_, mo, s);
+        add_items(M.resid[l], ri, tres_, mo, M.tab);
         M.restrict_[l].kind = 0; M.restrict_[l].br = rbr; M.restrict_[l].bc = rbc; M.restrict_[l].epi = E_SET;
-        upload_items(M.restrict_[l], rs, tr, mo, s);
+        add_items(M.restrict_[l], rs, tr, mo, M.tab);
         M.prolong[l].kind = 0; M.prolong[l].br = pbr; M.prolong[l].bc = pbc; M.prolong[l].epi = E_ADD;
-        upload_items(M.prolong[l], pa, tp, mo, s);
+        add_items(M.prolong[l], pa, tp, mo, M.tab);
         M.postinit[l].kind = 0; M.postinit[l].br = bs; M.postinit[l].bc = bs; M.postinit[l].epi = E_INIT;
-        upload_items(M.postinit[l], pinit, tres_, mo, s);
+        add_items(M.postinit[l], pinit, tres_, mo, M.tab);
         // pre-smoothing steps start from x = 0; post-smoothing steps accumulate
         M.pre_steps[l].resize(steps);
         M.post_steps[l].resize(steps);
@@ -279,10 +305,10 @@ void build_phases(MultiState &M, hipStream_t s) {
             const bool last = k + 1 == steps;
             Phase &Pp = M.pre_steps[l][k];
             Pp.kind = 0; Pp.br = bs; Pp.bc = bs;
-            if (last && k == 0) { Pp.epi = E_STEP_LZ; upload_items(Pp, s_lz[k], tres_, mo, s); }
-            else if (last) { Pp.epi = E_STEP_L; upload_items(Pp, s_l[k], tres_, mo, s); }
-            else if (k == 0) { Pp.epi = E_STEP_Z; upload_items(Pp, s_z[k], tres_, mo, s); }
-            else { Pp.epi = E_STEP; upload_items(Pp, s_n[k], tres_, mo, s); }
+            if (last && k == 0) { Pp.epi = E_STEP_LZ; add_items(Pp, s_lz[k], tres_, mo, M.tab); }
+            else if (last) { Pp.epi = E_STEP_L; add_items(Pp, s_l[k], tres_, mo, M.tab); }
+            else if (k == 0) { Pp.epi = E_STEP_Z; add_items(Pp, s_z[k], tres_, mo, M.tab); }
+            else { Pp.epi = E_STEP; add_items(Pp, s_n[k], tres_, mo, M.tab); }
             // post-smoothing: same operators, rin = r after the init, never x = 0
             std::vector<GItem<double, EpiChebStep<double, true, false>>> q_l;
             std::vector<GItem<double, EpiChebStep<double, false, false>>> q_n;
@@ -299,8 +325,8 @@ void build_phases(MultiState &M, hipStream_t s) {
             }
             Phase &Pq = M.post_steps[l][k];
             Pq.kind = 0; Pq.br = bs; Pq.bc = bs;
-            if (last) { Pq.epi = E_STEP_L; upload_items(Pq, q_l, tres_, mo, s); }
-            else { Pq.epi = E_STEP; upload_items(Pq, q_n, tres_, mo, s); }
+            if (last) { Pq.epi = E_STEP_L; add_items(Pq, q_l, tres_, mo, M.tab); }
+            else { Pq.epi = E_STEP; add_items(Pq, q_n, tres_, mo, M.tab); }
         }
     }
     // dense coarse solves, each mesh on its own coarsest level
@@ -316,14 +342,19 @@ void build_phases(MultiState &M, hipStream_t s) {
             mo.push_back(m);
         }
         M.dense.kind = 2;
-        upload_items(M.dense, di, dt, mo, s);
+        add_items(M.dense, di, dt, mo, M.tab);
     }
-    for (Phase *P : {&M.ap, &M.update, &M.dotrz, &M.pupdate, &M.tres, &M.dense}) P->gmult = M.gmult;
+    upload(M.tab.d, M.tab.h, s);
+    auto finish = [&](Phase &P) {
+        P.gmult = M.gmult;
+        P.bind(M.tab.d.p);
+    };
+    for (Phase *P : {&M.ap, &M.update, &M.dotrz, &M.pupdate, &M.tres, &M.self, &M.dense}) finish(*P);
     for (auto *V : {&M.jac, &M.resid, &M.restrict_, &M.prolong, &M.postinit})
-        for (Phase &P : *V) P.gmult = M.gmult;
+        for (Phase &P : *V) finish(P);
     for (auto *V : {&M.pre_steps, &M.post_steps})
         for (auto &row : *V)
-            for (Phase &P : row) P.gmult = M.gmult;
+            for (Phase &P : row) finish(P);
 }
 
 // The work-item order of the grouped phases: the meshes as given (0), or
@@ -366,14 +397,14 @@ void tail(MultiState &M, const int32_t *mask, hipStream_t s) {
 }
 
 void iteration(MultiState &M, hipStream_t s) {
-    run(M.ap, M.active.p, M.partials.p, s);
+    run(M.ap, M.active, M.partials.p, s);
     reduce(M.ap, 1, M.partials.p, M.sums.p, s);
     hipLaunchKernelGGL(k_multi_alpha, dim3((M.n + 63) / 64), dim3(64), 0, s, M.S, M.sums.p, M.n);
-    run(M.update, M.active.p, M.partials.p, s);
+    run(M.update, M.active, M.partials.p, s);
     reduce(M.update, 1, M.partials.p, M.sums.p, s);
     hipLaunchKernelGGL(k_multi_rr, dim3((M.n + 63) / 64), dim3(64), 0, s, M.S, M.sums.p, M.n);
     TE_CHECK_HIP(hipGetLastError());
-    tail(M, M.active.p, s);
+    tail(M, M.active, s);
 }
 
 __global__ void k_set_rz(MultiScal S, const double *__restrict__ rzf, int n) {
@@ -405,7 +436,7 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
     M.H.assign(hs, hs + n);
     M.deg = hs[0]->opt.cheb_degree;
     // launch shape chosen by te_autotune_multi for this set (kept in the handles)
-    M.gmult = std::max(1, hs[0]->multi_grid);
+    M.gmult = hs[0]->multi_grid;
     M.order = mesh_order(hs, n, hs[0]->multi_order);
     for (int m = 0; m < n; ++m) {
         TE_REQUIRE(hs[m] && b[m] && u[m], TE_EINVAL, "NULL handle or vector %d", m);
@@ -443,17 +474,20 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
 
     for (auto *p : {&M.rz, &M.pq, &M.alpha, &M.beta, &M.rr, &M.bb, &M.tol2}) p->alloc(n);
     M.sums.alloc(2 * n);
-    for (auto *p : {&M.active, &M.cand, &M.flag, &M.iters, &M.tailmask}) {
-        p->alloc(n);
-        TE_CHECK_HIP(hipMemsetAsync(p->p, 0, n * sizeof(int32_t), s));
-    }
+    M.marks.alloc(5 * (size_t)n);
+    TE_CHECK_HIP(hipMemsetAsync(M.marks.p, 0, M.marks.bytes(), s));
+    M.active = M.marks.p;
+    M.cand = M.active + n;
+    M.flag = M.cand + n;
+    M.iters = M.flag + n;
+    M.tailmask = M.iters + n;
     TE_CHECK_HIP(hipMemsetAsync(M.alpha.p, 0, n * sizeof(double), s));
     TE_CHECK_HIP(hipMemsetAsync(M.beta.p, 0, n * sizeof(double), s));
     M.S = MultiScal{M.rz.p, M.pq.p, M.alpha.p, M.beta.p, M.rr.p, M.bb.p, M.tol2.p,
-                    M.active.p, M.cand.p, M.flag.p, M.iters.p};
+                    M.active, M.cand, M.flag, M.iters};
     build_phases(M, s);
     int64_t maxt = 0;
-    for (const Phase *P : {&M.ap, &M.update, &M.dotrz}) maxt = std::max(maxt, P->ntiles);
+    for (const Phase *P : {&M.ap, &M.update, &M.dotrz, &M.self}) maxt = std::max(maxt, P->ntiles);
     M.partials.alloc(2 * maxt + 2);
 
     // inputs into each mesh's storage order
@@ -463,24 +497,8 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
         permute_gather(u[m], h->u.p, h->L[0].perm.p, h->L[0].n, 3, 1, s);
     }
     // |b|^2 and the initial residual
-    {
-        Phase bb;
-        std::vector<VItem> it;
-        std::vector<int64_t> t;
-        std::vector<int32_t> mo;
-        for (int m = 0; m < n; ++m) {
-            const int64_t nv = hs[m]->L[0].n * 3;
-            it.push_back(VItem{nullptr, nullptr, nullptr, hs[m]->b.p, nullptr, 0.0, nv, m});
-            t.push_back((nv + VTILE - 1) / VTILE);
-            mo.push_back(m);
-        }
-        bb.kind = 1;
-        bb.vop = VOP_DOTSELF;
-        upload_items(bb, it, t, mo, s);
-        DBuf<double> part(2 * bb.ntiles + 2);
-        run(bb, nullptr, part.p, s);
-        reduce(bb, 1, part.p, M.bb.p, s);
-    }
+    run(M.self, nullptr, M.partials.p, s);
+    reduce(M.self, 1, M.partials.p, M.bb.p, s);
     run(M.tres, nullptr, M.partials.p, s);
     reduce(M.tres, 1, M.partials.p, M.sums.p, s);
     std::vector<double> bbh, rrh;
@@ -505,9 +523,9 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
         TE_CHECK_HIP(hipMemcpyAsync(hs[m]->r.p, hs[m]->t.p, hs[m]->L[0].n * 3 * sizeof(double),
                                     hipMemcpyDeviceToDevice, s));
     TE_CHECK_HIP(hipMemcpyAsync(M.tol2.p, tol2.data(), n * sizeof(double), hipMemcpyHostToDevice, s));
-    TE_CHECK_HIP(hipMemcpyAsync(M.active.p, act.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    vcycle_all(M, M.active.p, s);
-    run(M.dotrz, M.active.p, M.partials.p, s);
+    TE_CHECK_HIP(hipMemcpyAsync(M.active, act.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    vcycle_all(M, M.active, s);
+    run(M.dotrz, M.active, M.partials.p, s);
     reduce(M.dotrz, 2, M.partials.p, M.sums.p, s);
     hipLaunchKernelGGL(k_set_rz, dim3((n + 63) / 64), dim3(64), 0, s, M.S, M.sums.p, n);
     TE_CHECK_HIP(hipGetLastError());
@@ -524,7 +542,7 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
     TE_CHECK_HIP(hipStreamEndCapture(s, &g_it));
     TE_CHECK_HIP(hipGraphInstantiate(&x_it, g_it, nullptr, nullptr, 0));
     TE_CHECK_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    tail(M, M.tailmask.p, s);
+    tail(M, M.tailmask, s);
     TE_CHECK_HIP(hipStreamEndCapture(s, &g_tail));
     TE_CHECK_HIP(hipGraphInstantiate(&x_tail, g_tail, nullptr, nullptr, 0));
     struct GraphGuard {
@@ -538,16 +556,24 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
         }
     } gg{g_it, g_tail, x_it, x_tail};
 
-    std::vector<int32_t> flags, cand, itv;
+    std::vector<int32_t> cand(n), itv;
+    // active, cand and flag in one copy, to pinned memory where they fit
+    const size_t mb = 3 * (size_t)n * sizeof(int32_t);
+    PinBuf &pin = hs[0]->pin;
+    if (!pin.p) pin.alloc(kPinBytes);
+    std::vector<int32_t> own;
+    if (mb > pin.n) own.resize(3 * (size_t)n);
+    int32_t *marks = own.empty() ? reinterpret_cast<int32_t *>(pin.p) : own.data();
     std::vector<double> trh;
     int n_active = 0;
     for (int m = 0; m < n; ++m) n_active += act[m];
     for (int it = 0; n_active > 0 && it < o.maxit; ++it) {
         TE_CHECK_HIP(hipGraphLaunch(x_it, s));
-        fetch_vec(act, M.active.p, n, s);
-        fetch_vec(cand, M.cand.p, n, s);
-        fetch_vec(flags, M.flag.p, n, s);
+        TE_CHECK_HIP(hipMemcpyAsync(marks, M.active, mb, hipMemcpyDeviceToHost, s));
         TE_CHECK_HIP(hipStreamSynchronize(s));
+        std::copy(marks, marks + n, act.begin());
+        std::copy(marks + n, marks + 2 * n, cand.begin());
+        const int32_t *flags = marks + 2 * n;
         for (int m = 0; m < n; ++m) {
             TE_REQUIRE(flags[m] != 3, TE_ENAN, "NaN in the CG recurrence of mesh %d", m);
             TE_REQUIRE(flags[m] == 0, TE_EINDEF, "CG breakdown in mesh %d (%s)", m,
@@ -557,7 +583,7 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
         for (int m = 0; m < n; ++m) any = any || cand[m];
         if (any) {
             // true residual of the meshes whose recurrence passed
-            run(M.tres, M.cand.p, M.partials.p, s);
+            run(M.tres, M.cand, M.partials.p, s);
             reduce(M.tres, 1, M.partials.p, M.sums.p, s);
             fetch_vec(trh, M.sums.p, n, s);
             TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -577,11 +603,11 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
                     any_tail = true;
                 }
             }
-            TE_CHECK_HIP(hipMemcpyAsync(M.cand.p, cand.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+            TE_CHECK_HIP(hipMemcpyAsync(M.cand, cand.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
             if (any_tail) {
-                TE_CHECK_HIP(hipMemcpyAsync(M.tailmask.p, tm.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+                TE_CHECK_HIP(hipMemcpyAsync(M.tailmask, tm.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
                 TE_CHECK_HIP(hipGraphLaunch(x_tail, s));
-                TE_CHECK_HIP(hipMemcpyAsync(M.active.p, act.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
+                TE_CHECK_HIP(hipMemcpyAsync(M.active, act.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s));
                 TE_CHECK_HIP(hipStreamSynchronize(s));
             }
         }
@@ -594,7 +620,7 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
     for (int m = 0; m < n; ++m) permute_scatter(hs[m]->u.p, u[m], hs[m]->L[0].perm.p, hs[m]->L[0].n, 3, 1, s);
     TE_CHECK_HIP(hipEventRecord(ev1, s));
     fetch_vec(trh, M.sums.p, n, s);
-    fetch_vec(itv, M.iters.p, n, s);
+    fetch_vec(itv, M.iters, n, s);
     TE_CHECK_HIP(hipStreamSynchronize(s));
     float ms = 0.f;
     TE_CHECK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
@@ -619,8 +645,8 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
 
 namespace te {
 namespace {
-// Launch shape of the grouped phases for one set of hierarchies: the
-// persistent grid (1, 2 or 4 times the resident workgroups) and the work-item
+// Launch shape of the grouped phases for one set of hierarchies: the grid (one workgroup per tile, or persistent with 1, 2 or 4 times the resident
+// workgroups) and the work-item
 // order (meshes as given, or largest first), timed on one V-cycle of every
 // mesh plus the level-0 product (median of 5 after a warm-up, HIP events),
 // the best kept in every handle.  Overwrites the handles' solve workspace.
@@ -651,9 +677,9 @@ int autotune_multi_impl(amg_handle **hs, int n, char *report, int64_t len, hipSt
     upload(ones, std::vector<int32_t>(n, 1), s);
     std::string rep;
     float best_t = INFINITY, def_t = 0.f;
-    int best_g = 1, best_o = 0;
+    int best_g = 0, best_o = 0;
     for (int how : {0, 1}) {
-        for (int gm : {1, 2, 4}) {
+        for (int gm : {0, 1, 2, 4}) {
             M.order = mesh_order(hs, n, how);
             M.gmult = gm;
             build_phases(M, s);
@@ -672,7 +698,7 @@ int autotune_multi_impl(amg_handle **hs, int n, char *report, int64_t len, hipSt
                 TE_CHECK_HIP(hipEventElapsedTime(&t[r], ev.a, ev.b));
             }
             std::sort(t, t + 5);
-            if (how == 0 && gm == 1) def_t = t[2];
+            if (how == 0 && gm == 0) def_t = t[2];
             if (t[2] < best_t) {
                 best_t = t[2];
                 best_g = gm;
@@ -685,8 +711,11 @@ int autotune_multi_impl(amg_handle **hs, int n, char *report, int64_t len, hipSt
         hs[m]->multi_order = best_o;
     }
     char buf[256];
-    std::snprintf(buf, sizeof buf, "multi-mesh %d systems: grid %dx resident, %s order: %.4f ms per V-cycle + "
-                  "product (default %.4f ms)\n", n, best_g, best_o ? "largest-first" : "given", best_t, def_t);
+    char shape[32];
+    if (best_g == 0) std::snprintf(shape, sizeof shape, "of one tile per group");
+    else std::snprintf(shape, sizeof shape, "%dx resident", best_g);
+    std::snprintf(buf, sizeof buf, "multi-mesh %d systems: grid %s, %s order: %.4f ms per V-cycle + "
+                  "product (default %.4f ms)\n", n, shape, best_o ? "largest-first" : "given", best_t, def_t);
     rep += buf;
     if (report && len > 0) std::snprintf(report, (size_t)len, "%s", rep.c_str());
     return TE_OK;

@@ -22,7 +22,6 @@ struct GItem {
     const T *x;
     Epi epi;
     int32_t mesh;
-    int32_t fmt;
 };
 
 template <int BR, int BC, typename T, class Epi>
@@ -51,13 +50,16 @@ __global__ void __launch_bounds__(GBLK) k_group(const GItem<T, Epi> *__restrict_
         const int64_t unit = (t - tile0[it]) * GW + threadIdx.x / WAVE;
         double red = 0.0;
         if (active == nullptr || active[G.mesh]) {
-            if (G.fmt == FMT_SELL) {
+            // one format per block height: with both in one kernel the 6x6 Chebyshev
+            // steps held 164 to 226 registers, two or three waves per SIMD, and took
+            // 146 to 159 us on eight meshes; now 60 registers and 85 us
+            if constexpr (BR == 3) {
                 // the operator values are read once per product: non-temporal loads
                 if (unit < G.sv.nslices) sell1_body<BR, BC, T, T, T, Epi, true>(G.sv, G.x, G.epi, unit, lane, red);
             } else {
                 if (unit < G.rv.nrows)
-                    roww_body<BR, BC, T, T, T, Epi>(G.rv, G.x, G.epi, unit, lane, red,
-                                                    wb + (threadIdx.x / WAVE) * WAVE);
+                    roww_body<BR, BC, T, T, T, Epi, false, BC == 6>(G.rv, G.x, G.epi, unit, lane, red,
+                                                                    wb + (threadIdx.x / WAVE) * WAVE);
             }
         }
         if (Epi::kReduce) {
@@ -252,12 +254,21 @@ int64_t resident_groups(K kernel, int threads) {
     return std::max<int64_t>(1, (int64_t)ncu * std::max(per_cu, 1));
 }
 
+// gmult 0: a workgroup per tile (the device takes the next tile as soon as one
+// ends); otherwise a persistent grid of gmult * resident workgroups, each with a
+// range of tiles.  Eight meshes of 13,000 to 119,000 nodes: 6x6 products 88 to 98
+// us persistent, 72 to 85 one by one, 3x3 products 79 and 74; the solve 34.8 and
+// 31.8 ms.
+inline unsigned group_grid(int64_t ntiles, int64_t resident, int gmult) {
+    return (unsigned)std::min<int64_t>(ntiles, gmult == 0 ? 1 << 23 : resident * gmult);
+}
+
 template <int BR, int BC, class Epi>
 void group_launch(const void *items, const int64_t *tile0, int nitems, int64_t ntiles, const int32_t *active,
-                  double *partials, hipStream_t s, int gmult = 1) {
+                  double *partials, hipStream_t s, int gmult) {
     if (nitems == 0 || ntiles == 0) return;
     static const int64_t cap = resident_groups(k_group<BR, BC, double, Epi>, GBLK);
-    const unsigned g = (unsigned)std::min<int64_t>(ntiles, cap * gmult);
+    const unsigned g = group_grid(ntiles, cap, gmult);
     hipLaunchKernelGGL((k_group<BR, BC, double, Epi>), dim3(g), dim3(GBLK), 0, s,
                        (const GItem<double, Epi> *)items, tile0, nitems, active, partials);
     TE_CHECK_HIP(hipGetLastError());
@@ -265,9 +276,9 @@ void group_launch(const void *items, const int64_t *tile0, int nitems, int64_t n
 
 template <int OP>
 void group_vec_launch(const VItem *items, const int64_t *tile0, int nitems, int64_t ntiles, const int32_t *active,
-                      const double *coef, double *partials, hipStream_t s, int gmult = 1) {
+                      const double *coef, double *partials, hipStream_t s, int gmult) {
     if (nitems == 0 || ntiles == 0) return;
-    const unsigned g = (unsigned)std::min<int64_t>(ntiles, (int64_t)GROUP_GRID * gmult);
+    const unsigned g = group_grid(ntiles, GROUP_GRID, gmult);
     hipLaunchKernelGGL(k_group_vec<OP>, dim3(g), dim3(BLK), 0, s, items, tile0, nitems, active, coef, partials);
     TE_CHECK_HIP(hipGetLastError());
 }

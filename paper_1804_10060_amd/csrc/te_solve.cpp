@@ -551,7 +551,7 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
     // ten vectors; 1 GB of it takes 0.3 ms, 20 to 30 iterations wait 0.5 to 0.75.
     // With two pageable copies and the wait before it: 14,739-unknown cube 1.28 ->
     // 0.96 ms a solve, 69,000-node P2 disc 11.2 -> 9.6 ms.
-    if (!h->pin.p) h->pin.alloc(sizeof(CgScalars) - offsetof(CgScalars, rr));
+    if (!h->pin.p) h->pin.alloc(kPinBytes);
     const char *pin = h->pin.p;
     const double *pin_rr = reinterpret_cast<const double *>(pin);
     const int32_t *pin_flag = reinterpret_cast<const int32_t *>(pin + offsetof(CgScalars, flag) - offsetof(CgScalars, rr));
@@ -568,7 +568,7 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
         cg_update(h->u.p, h->r.p, mixed ? h->r_old.p : nullptr, h->p.p, h->q.p, S->alpha, rows, m, part, s);
         reduce_partials(part, dot_nblocks(rows), m, S->rr, s);
         h->prof.end(TE_K_VECTOR);
-        TE_CHECK_HIP(hipMemcpyAsync(h->pin.p, S->rr, h->pin.n, hipMemcpyDeviceToHost, s));
+        TE_CHECK_HIP(hipMemcpyAsync(h->pin.p, S->rr, kPinBytes, hipMemcpyDeviceToHost, s));
         TE_CHECK_HIP(hipEventRecord(ev.c, s));
         bool ahead = ahead_ok && it < o.maxit;
         if (ahead) precondition(h, h->r.p, h->z.p, m, mixed, s);
