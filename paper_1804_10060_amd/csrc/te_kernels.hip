@@ -452,16 +452,19 @@ static inline const Tune &tune_of(const Sell &A) {
 }
 
 // Block rows per wave of the SELL multi-RHS product for nrhs columns: 16
-// rows (4 lanes each) for at most 4 columns, else 4 rows of 16 lanes; one
-// row per wave for the lane-per-column kernel (tile 0, above 16 columns).
+// rows (4 lanes each) for at most 4 columns, 8 rows of 8 lanes for at most 8,
+// else 4 rows of 16 lanes; one row per wave for the lane-per-column kernel
+// (tile 0, above 16 columns).  Five columns on 95,700 P1 nodes: 93 to 120 us a
+// product with 16 lanes per row, 54 to 76 with 8 (four entries in flight instead
+// of two: no faster).
 static inline int multi_rows(int nrhs, int mtile) {
     if (mtile == 0 && nrhs > 16) return 1;   // k_sellw
-    return nrhs <= 4 ? 16 : 4;
+    return nrhs <= 4 ? 16 : nrhs <= 8 ? 8 : 4;
 }
 // Columns per lane: the column tile (16, 32 or 64 columns per pass over the
 // matrix, tuned) over the 16 lanes of a row.
 static inline int multi_cols(int nrhs, int mtile) {
-    if (nrhs <= 4) return 1;
+    if (nrhs <= 8) return 1;
     const int need = (nrhs + 15) / 16;   // 1..4
     const int s = std::min(need, mtile / 16);
     return s >= 4 ? 4 : (s >= 2 ? 2 : 1);
@@ -598,6 +601,7 @@ static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, 
                                g);
         };
         if (R == 16) go(k_sellm<BR, BC, VT, XT, AT, Epi, 16, 1>);
+        else if (R == 8) go(k_sellm<BR, BC, VT, XT, AT, Epi, 8, 1>);
         else if (S == 1) go(k_sellm<BR, BC, VT, XT, AT, Epi, 4, 1>);
         else if (S == 2) go(k_sellm<BR, BC, VT, XT, AT, Epi, 4, 2>);
         else go(k_sellm<BR, BC, VT, XT, AT, Epi, 4, 4>);
