@@ -454,19 +454,22 @@ static inline const Tune &tune_of(const Sell &A) {
 // Block rows per wave of the SELL multi-RHS product for nrhs columns: 16
 // rows (4 lanes each) for at most 4 columns, 8 rows of 8 lanes for at most 8,
 // else 4 rows of 16 lanes; one row per wave for the lane-per-column kernel
-// (tile 0, above 16 columns).  Five columns on 95,700 P1 nodes: 93 to 120 us a
+// (tile 0, above 32 columns).  Five columns on 95,700 P1 nodes: 93 to 120 us a
 // product with 16 lanes per row, 54 to 76 with 8 (four entries in flight instead
 // of two: no faster).
 static inline int multi_rows(int nrhs, int mtile) {
-    if (mtile == 0 && nrhs > 16) return 1;   // k_sellw
+    if (mtile == 0 && nrhs > 32) return 1;   // k_sellw
     return nrhs <= 4 ? 16 : nrhs <= 8 ? 8 : 4;
 }
 // Columns per lane: the column tile (16, 32 or 64 columns per pass over the
-// matrix, tuned) over the 16 lanes of a row.
+// matrix, tuned; 32 where tile 0 does not mean a lane per column) over the 16
+// lanes of a row.  24 columns on 95,700 P1 nodes with a lane per column: 145 to
+// 203 us a product, with two columns on each of 16 lanes 142 to 188, with one on
+// each of 32 194 to 234.
 static inline int multi_cols(int nrhs, int mtile) {
     if (nrhs <= 8) return 1;
     const int need = (nrhs + 15) / 16;   // 1..4
-    const int s = std::min(need, mtile / 16);
+    const int s = std::min(need, (mtile == 0 ? 32 : mtile) / 16);
     return s >= 4 ? 4 : (s >= 2 ? 2 : 1);
 }
 

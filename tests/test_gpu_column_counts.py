@@ -1,5 +1,5 @@
 """Several right-hand sides at the column counts where the products change their
-lanes per row (4, 8, 16 lanes, then a lane per column), on meshes whose rows do
+lanes per row (4, 8, 16, 16 lanes of two columns, then a lane per column), on meshes whose rows do
 not fill the last wave.
 
 Every column against the solve of that column alone: the sums of a row run over
@@ -16,7 +16,7 @@ from tests.gpu_util import dev, gpu_assemble, matrix_to_host, say, torch_cuda
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m", [2, 4, 5, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("m", [2, 4, 5, 7, 8, 9, 16, 17, 32, 33])
 @pytest.mark.parametrize("degree", [1, 2])
 def test_columns_match_single_solves(m, degree):
     import paper_1804_10060_amd as te
