@@ -378,7 +378,7 @@ __device__ __forceinline__ void roww_body(const RowView<VT> &A, const XT *__rest
 // finishes the row with apply<BR>(row, acc, red, pre).  The lane-per-row
 // product issues load before its entry loop, so those reads are in flight
 // while the operator streams instead of after it; apply(row, acc, red) does
-// both at the end.  Inputs that are only streamed are read non-temporally.
+// both at the end.  load_m and apply_m are the same for column j of m.  Inputs that are only streamed are read non-temporally.
 template <typename T>
 struct EpiSet {  // y = A x
     static constexpr bool kReduce = false;
@@ -398,8 +398,12 @@ struct EpiSet {  // y = A x
     __device__ void apply(int64_t r, AT *acc, double &red) const {
         apply<BR>(r, acc, red, load<BR>(r));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t, int, int) const {
+        return {};
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &) const {
+    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &, const Pre<BR> &) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) y[(r * BR + i) * m + j] = T(acc[i]);
     }
@@ -426,8 +430,12 @@ struct EpiAdd {  // y += A x
     __device__ void apply(int64_t r, AT *acc, double &red) const {
         apply<BR>(r, acc, red, load<BR>(r));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t, int, int) const {
+        return {};
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &) const {
+    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &, const Pre<BR> &) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) {
             int64_t q = (r * BR + i) * m + j;
@@ -465,12 +473,19 @@ struct EpiResid {  // y = g - A x  (optionally red += y^2)
     __device__ void apply(int64_t r, AT *acc, double &red) const {
         apply<BR>(r, acc, red, load<BR>(r));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t r, int j, int m) const {
+        Pre<BR> p;
+#pragma unroll
+        for (int i = 0; i < BR; ++i) p.g[i] = g[(r * BR + i) * m + j];
+        return p;
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &red) const {
+    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &red, const Pre<BR> &p) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) {
             int64_t q = (r * BR + i) * m + j;
-            AT v = AT(g[q]) - acc[i];
+            AT v = AT(p.g[i]) - acc[i];
             st_out(&y[q], T(v));
             if (NORM) red += double(v) * double(v);
         }
@@ -504,13 +519,20 @@ struct EpiDot {  // q = A p, red += p.q   (float64 outer CG)
     __device__ void apply(int64_t r, AT *acc, double &red) const {
         apply<BR>(r, acc, red, load<BR>(r));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t r, int j, int m) const {
+        Pre<BR> v;
+#pragma unroll
+        for (int i = 0; i < BR; ++i) v.p[i] = p[(r * BR + i) * m + j];
+        return v;
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &red) const {
+    __device__ void apply_m(int64_t r, int j, int m, AT *acc, double &red, const Pre<BR> &v) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) {
             int64_t k = (r * BR + i) * m + j;
             st_out(&q[k], double(acc[i]));
-            red += p[k] * double(acc[i]);
+            red += v.p[i] * double(acc[i]);
         }
     }
 };
@@ -554,14 +576,24 @@ struct EpiChebInit {
     __device__ void apply(int64_t row, AT *acc, double &red) const {
         apply<BR>(row, acc, red, load<BR>(row));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t row, int j, int m) const {
+        Pre<BR> p;
+#pragma unroll
+        for (int i = 0; i < BR; ++i) {
+            p.g[i] = g[(row * BR + i) * m + j];
+            p.v[i] = dinv[row * BR + i];
+        }
+        return p;
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t row, int j, int m, AT *acc, double &) const {
+    __device__ void apply_m(int64_t row, int j, int m, AT *acc, double &, const Pre<BR> &p) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) {
             int64_t q = (row * BR + i) * m + j;
-            T rv = T(AT(g[q]) - acc[i]);
+            T rv = T(AT(p.g[i]) - acc[i]);
             st_out(&r[q], rv);
-            st_out(&d[q], T(dinv[row * BR + i] * rv * inv_theta));
+            st_out(&d[q], T(p.v[i] * rv * inv_theta));
         }
     }
 };
@@ -619,15 +651,28 @@ struct EpiChebStep {
     __device__ void apply(int64_t row, AT *acc, double &red) const {
         apply<BR>(row, acc, red, load<BR>(row));
     }
+    template <int BR>
+    __device__ Pre<BR> load_m(int64_t row, int j, int m) const {
+        Pre<BR> p;
+#pragma unroll
+        for (int i = 0; i < BR; ++i) {
+            const int64_t q = (row * BR + i) * m + j;
+            p.r[i] = rin[q];
+            p.d[i] = d[q];
+            p.v[i] = dinv[row * BR + i];
+            p.x[i] = XZERO ? T(0) : x[q];
+        }
+        return p;
+    }
     template <int BR, typename AT>
-    __device__ void apply_m(int64_t row, int j, int m, AT *acc, double &) const {
+    __device__ void apply_m(int64_t row, int j, int m, AT *acc, double &, const Pre<BR> &p) const {
 #pragma unroll
         for (int i = 0; i < BR; ++i) {
             int64_t q = (row * BR + i) * m + j;
-            T rn = T(AT(rin[q]) - acc[i]);
-            T dv = d[q];
-            T dn = c1 * dv + c2 * (dinv[row * BR + i] * rn);
-            T xv = XZERO ? T(0) : x[q];
+            T rn = T(AT(p.r[i]) - acc[i]);
+            T dv = p.d[i];
+            T dn = c1 * dv + c2 * (p.v[i] * rn);
+            T xv = p.x[i];
             if (LAST) {
                 st_out(&x[q], T(xv + dv + dn));
             } else {

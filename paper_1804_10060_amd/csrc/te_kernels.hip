@@ -68,8 +68,13 @@ __global__ void __launch_bounds__(512) k_sell1s(SellView<VT> A, const XT *__rest
 // the right-hand sides on the lanes (at most 64); the block values are
 // wave-uniform (scalar loads), the row's column indices come 64 at a time
 // and are taken by readlane, and the x rows of 4 entries are loaded before
-// any of them is used.  The default above 16 columns; the tuner may pick
+// any of them is used.  The default above 32 columns; the tuner may pick
 // the row groups below instead.
+//   Bound by the x rows that the L2s deliver (64 columns on 334,368 P1 nodes:
+// 7.4 GB a product, 11 TB/s, while 0.8 GB come from memory): more entries in
+// flight and a last batch padded with repeated entries both took longer (0.75 to
+// 1.1 ms).  The epilogue's inputs are loaded before the entries: Chebyshev start
+// and steps 875, 806 and 765 us -> 781, 757 and 726 there.
 template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
 __global__ void __launch_bounds__(512) k_sellw(SellView<VT> A, const XT *__restrict__ x, Epi epi, int nrhs,
                                                double *__restrict__ partials, int wpb) {
@@ -84,6 +89,9 @@ __global__ void __launch_bounds__(512) k_sellw(SellView<VT> A, const XT *__restr
         const int rl = (int)(row % WAVE);
         const int off = A.slice_off[row / WAVE];
         const int len = A.rowlen[row];
+        const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
+        typename Epi::template Pre<BR> pre{};
+        if (lane < nrhs) pre = epi.template load_m<BR>(out, lane, nrhs);
         AT acc[BR];
 #pragma unroll
         for (int i = 0; i < BR; ++i) acc[i] = AT(0);
@@ -120,10 +128,7 @@ __global__ void __launch_bounds__(512) k_sellw(SellView<VT> A, const XT *__restr
                 }
             }
         }
-        if (lane < nrhs) {
-            const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
-            epi.template apply_m<BR>(out, lane, nrhs, acc, red);
-        }
+        if (lane < nrhs) epi.template apply_m<BR>(out, lane, nrhs, acc, red, pre);
     }
     if (Epi::kReduce) {
         lds[threadIdx.x] = red;
@@ -193,6 +198,10 @@ __global__ void __launch_bounds__(512) k_sellm(SellView<VT> A, const XT *__restr
         const int rl = (int)(rr % WAVE);
         const int off = A.slice_off[rr / WAVE];
         const int lmax = __builtin_amdgcn_readfirstlane(A.rowlen[row0]);
+        const int64_t out = A.rowmap ? (int64_t)A.rowmap[rr] : rr;
+        typename Epi::template Pre<BR> pre[S];
+#pragma unroll
+        for (int t = 0; t < S; ++t) pre[t] = epi.template load_m<BR>(out, min(j + t * T, nrhs - 1), nrhs);
         AT acc[S][BR];
 #pragma unroll
         for (int t = 0; t < S; ++t)
@@ -233,10 +242,9 @@ __global__ void __launch_bounds__(512) k_sellm(SellView<VT> A, const XT *__restr
             }
         }
         if (live) {
-            const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
 #pragma unroll
             for (int t = 0; t < S; ++t)
-                if (j + t * T < nrhs) epi.template apply_m<BR>(out, j + t * T, nrhs, acc[t], red[t]);
+                if (j + t * T < nrhs) epi.template apply_m<BR>(out, j + t * T, nrhs, acc[t], red[t], pre[t]);
         }
     }
     if (Epi::kReduce) {
@@ -420,7 +428,7 @@ __global__ void __launch_bounds__(1024) k_rowm(RowView<VT> A, const XT *__restri
     if (S == 1 && wpr == 1) {
         if (live && j < nrhs) {
             const int64_t out = A.rowmap ? (int64_t)A.rowmap[row] : row;
-            epi.template apply_m<BR>(out, j, nrhs, acc, red);
+            epi.template apply_m<BR>(out, j, nrhs, acc, red, epi.template load_m<BR>(out, j, nrhs));
         }
         return;
     }
@@ -439,7 +447,7 @@ __global__ void __launch_bounds__(1024) k_rowm(RowView<VT> A, const XT *__restri
         if (jo >= nrhs) continue;
         AT t[1] = {AT(0)};
         for (int w = 0; w < wpr; ++w) t[0] += buf[((grp * wpr + w) * BR + i) * C + jo];
-        epi.template apply_m<1>(out * BR + i, jo, nrhs, t, red);
+        epi.template apply_m<1>(out * BR + i, jo, nrhs, t, red, epi.template load_m<1>(out * BR + i, jo, nrhs));
     }
 }
 
