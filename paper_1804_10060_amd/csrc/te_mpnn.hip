@@ -27,7 +27,7 @@
 // Sums over the vertices (means, bias and weight gradients, loss) are
 // per-workgroup partials added in a fixed order in double: deterministic, no
 // atomics.  On 334,368 vertices a training step (forward, backward, Adam) went
-// from 22.8 to 4.9 ms.
+// from 22.8 to 4.7 ms.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
 // A workgroup takes tiles of 16 MT vertices (contiguous, in XCD order: the
 // gathered rows of a tile stay in one L2).  Each wave gathers 4 MT of them
 // with its 64 lanes on the channels: the wave's neighbour entries are one
-// list, each lane looks up one entry's vertex and weights, the rows of eight
+// list, each lane looks up one entry's vertex and weights, the rows of 24
 // entries are loaded together.  The rows meet in LDS, and each wave multiplies
 // them by its 16 output channels' weights, which stay in 80 registers for
 // all tiles (v_mfma_f32_16x16x4: lane (q, i) holds channels 16 kb + 4 q + s of
@@ -206,8 +206,9 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
 // Bound: 2 * 320 * 64 flop per vertex (0.09 ms on 334,368 vertices at the
 // float32 matrix rate) and about 1.5 KB of rows per vertex (0.10 ms); what is
 // left is the latency of the gather's dependent loads.  334,368 vertices, per
-// layer: forward 1.72 -> 0.43 ms, backward (two kernels) 1.62 -> 0.44 ms, with
-// one wave per vertex and vector FMAs before; 4,624 vertices: 45 -> 14 us.
+// layer: forward 1.72 -> 0.39 ms, backward (two kernels) 1.62 -> 0.41 ms, with
+// one wave per vertex and vector FMAs before; with the rows of eight entries 0.42
+// and 0.44 ms.
 template <int MT, bool BWD>
 __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, const int64_t *__restrict__ gp,
                                                     const int32_t *__restrict__ gi, const float *__restrict__ xf,
@@ -217,7 +218,7 @@ __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, c
                                                     float *__restrict__ aout, const float *__restrict__ gate,
                                                     float *__restrict__ hout, float *__restrict__ gout,
                                                     double *__restrict__ part) {
-    constexpr int VT = 16 * MT, VW = VT / MW, EU = 8;
+    constexpr int VT = 16 * MT, VW = VT / MW, EU = 24;
     __shared__ float T[VT][LROW];
     const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
     const int i16 = lane & 15, q = lane >> 4, col = 16 * w + i16;
