@@ -312,20 +312,28 @@ __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, c
         }
         while (cur < VW) flush();
         __syncthreads();
+        // a slab's 64 terms in a sum of their own: shorter float32 sums than one
+        // over all 320 (relative error of the network's output 2.3e-7 -> 1.5e-7)
         f32x4 acc[MT];
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[m][r] = gv;
 #pragma unroll
-        for (int kb = 0; kb < MK / 16; ++kb)
+        for (int p = 0; p < MK / MH; ++p) {
+            f32x4 sl[MT] = {};
 #pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                const f32x4 a = *reinterpret_cast<const f32x4 *>(&T[16 * m + i16][16 * kb + 4 * q]);
+            for (int kb = p * (MH / 16); kb < (p + 1) * (MH / 16); ++kb)
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], wr[kb * 4 + t], acc[m], 0, 0, 0);
-            }
+                for (int m = 0; m < MT; ++m) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(&T[16 * m + i16][16 * kb + 4 * q]);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        sl[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], wr[kb * 4 + t], sl[m], 0, 0, 0);
+                }
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] += sl[m];
+        }
         // lane (q, i) holds rows 4 q + r of channel col
 #pragma unroll
         for (int m = 0; m < MT; ++m)
