@@ -395,12 +395,13 @@ struct AsmArgs {
 // formed once and applied to all JT cases, whose nodal values are read row by
 // row of T and f (neighbouring lanes read neighbouring nodes).  With many
 // cases the geometry of a node's cells is thus formed nrhs / 8 times instead
-// of nrhs times: 64 cases with body forces on
-// 334,368 P1 nodes 23.0 -> 7.4 ms (what is left is the nodal reads, 8.8 TB/s
+// of nrhs times.  The workgroups of one XCD take neighbouring nodes, whose values
+// then come from its L2.  64 cases with body forces on
+// 334,368 P1 nodes 23.0 -> 7.4 -> 5.9 ms (what is left is the nodal reads
 // through the L1), one case on 524,576 P2 nodes 0.31 -> 0.18 ms.
 template <int DEG, int JT>
 __global__ void __launch_bounds__(ABLK) k_load(AsmArgs A) {
-    const int64_t i = (int64_t)blockIdx.x * ABLK + threadIdx.x;
+    const int64_t i = xcd_logical_block(blockIdx.x, gridDim.x) * ABLK + threadIdx.x;
     if (i >= A.n) return;
     constexpr int NPE = DEG == 1 ? 4 : 10;
     const int j0 = JT * blockIdx.y;
