@@ -114,10 +114,10 @@ __global__ void __launch_bounds__(MB) k_in(int64_t n, const float *__restrict__ 
         const float xv = c < MF ? X[v * MF + c] : 0.f;
         if (c < MF) Xc[v * MF + c] = xv;
         if (c < 3) maskc[v * 3 + c] = mask[v * 3 + c];
-        float a = b;
+        double ad = b;   // added in double: the layers amplify what is rounded here
 #pragma unroll
-        for (int k = 0; k < MF; ++k) a += lane_val(xv, k) * win[k];
-        a = a > 0.f ? a : 0.f;
+        for (int k = 0; k < MF; ++k) ad += double(lane_val(xv, k)) * win[k];
+        const float a = ad > 0.0 ? float(ad) : 0.f;
         h0[v * MH + c] = a;
         cs += a;
     }
@@ -149,18 +149,20 @@ __device__ __forceinline__ double sum_parts64(int nparts, const double *__restri
 
 // out[c] = sum_k v[k] M(k, c) over 64 k, the 16 lane groups taking 4 k each;
 // M row-major [k][c], or its transpose.  Valid in threads 0..63; v in LDS.
-template <bool TRANS>
-__device__ __forceinline__ float vec_mat64(const float *v, const float *__restrict__ M, float *lds) {
+// Added in double: every vertex receives the result, so its rounding does not
+// average out.
+template <bool TRANS, typename V>
+__device__ __forceinline__ double vec_mat64(const V *v, const float *__restrict__ M, double *lds) {
     const int c = threadIdx.x & 63, y = threadIdx.x / 64;
-    float t = 0.f;
+    double t = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int k = 4 * y + q;
-        t += v[k] * (TRANS ? M[c * MH + k] : M[k * MH + c]);
+        t += double(v[k]) * (TRANS ? M[c * MH + k] : M[k * MH + c]);
     }
     lds[threadIdx.x] = t;
     __syncthreads();
-    float o = 0.f;
+    double o = 0.0;
     if (threadIdx.x < 64)
 #pragma unroll
         for (int k = 0; k < SB / 64; ++k) o += lds[k * 64 + threadIdx.x];
@@ -172,16 +174,16 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
                                                const float *__restrict__ P, int l, float *__restrict__ g,
                                                float *__restrict__ gw) {
     __shared__ double lds[SB];
-    __shared__ float gs[64], ldf[SB];
+    __shared__ double gs[64];
     const int c = threadIdx.x;
     const double s = sum_parts64(nparts, part, lds);
     if (c < 64) {
-        gs[c] = float(s / double(n));
-        g[c] = gs[c];
+        gs[c] = s / double(n);
+        g[c] = float(gs[c]);
     }
     __syncthreads();
-    const float a = vec_mat64<false>(gs, P + off_wg(l), ldf);
-    if (c < 64) gw[c] = P[off_b(l) + c] + a;
+    const double a = vec_mat64<false>(gs, P + off_wg(l), lds);
+    if (c < 64) gw[c] = float(P[off_b(l) + c] + a);
 }
 
 // One message-passing layer, forward or backward.  Both are one product of
@@ -390,19 +392,20 @@ __global__ void __launch_bounds__(MB) k_out(int64_t n, const float *__restrict__
     float wo[16][MO];
     out_weights(P, j, wo);
     for (int64_t v = blockIdx.x * (int64_t)OV + threadIdx.x / 4; v < n; v += (int64_t)gridDim.x * OV) {
-        float hv[16], t[MO] = {0.f, 0.f, 0.f};
+        float hv[16];
+        double t[MO] = {0.0, 0.0, 0.0};   // the kernel is bound by the rows: the sums cost nothing in double
         load_row16(h, v, j, hv);
 #pragma unroll
         for (int k = 0; k < 16; ++k)
 #pragma unroll
-            for (int c = 0; c < MO; ++c) t[c] += hv[k] * wo[k][c];
+            for (int c = 0; c < MO; ++c) t[c] += double(hv[k]) * wo[k][c];
 #pragma unroll
         for (int c = 0; c < MO; ++c) {
             t[c] += __shfl_xor(t[c], 1, 64);
             t[c] += __shfl_xor(t[c], 2, 64);
         }
         if (j < MO) {
-            const float o = (j == 0 ? t[0] : (j == 1 ? t[1] : t[2])) + P[OFF_BOUT + j];
+            const float o = float((j == 0 ? t[0] : (j == 1 ? t[1] : t[2])) + P[OFF_BOUT + j]);
             const float yv = mask[v * 3 + j] ? o * 0.f : o;
             y[v * MO + j] = yv;
             if (yuser) yuser[v * MO + j] = yv;
@@ -664,7 +667,7 @@ __global__ void __launch_bounds__(SB) k_layer_small(int nparts, const double *__
                                                     const float *__restrict__ g, const float *__restrict__ P, int l,
                                                     float *__restrict__ grad, float *__restrict__ gg) {
     __shared__ double lds[SB];
-    __shared__ float gb[64], ldf[SB];
+    __shared__ float gb[64];
     const int c = threadIdx.x;
     const double s = sum_parts64(nparts, part, lds);
     if (c < 64) {
@@ -673,8 +676,8 @@ __global__ void __launch_bounds__(SB) k_layer_small(int nparts, const double *__
     }
     __syncthreads();
     for (int t = threadIdx.x; t < MH * MH; t += SB) grad[off_wg(l) + t] = g[t / MH] * gb[t % MH];
-    const float t = vec_mat64<true>(gb, P + off_wg(l), ldf);
-    if (c < 64) gg[c] = t;
+    const double t = vec_mat64<true>(gb, P + off_wg(l), lds);
+    if (c < 64) gg[c] = float(t);
 }
 
 // the input layer's bias gradient from partial column sums
