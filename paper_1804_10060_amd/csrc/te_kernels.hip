@@ -70,11 +70,12 @@ __global__ void __launch_bounds__(512) k_sell1s(SellView<VT> A, const XT *__rest
 // and are taken by readlane, and the x rows of 4 entries are loaded before
 // any of them is used.  The default above 32 columns; the tuner may pick
 // the row groups below instead.
-//   Bound by the x rows that the L2s deliver (64 columns on 334,368 P1 nodes:
-// 7.4 GB a product, 11 TB/s, while 0.8 GB come from memory): more entries in
-// flight and a last batch padded with repeated entries both took longer (0.75 to
-// 1.1 ms).  The epilogue's inputs are loaded before the entries: Chebyshev start
-// and steps 875, 806 and 765 us -> 781, 757 and 726 there.
+//   Bound by the walk over a row's blocks (dependent loads, eight waves per SIMD
+// at most), not by memory: 64 columns on 334,368 P1 nodes gather 7.4 GB of x a
+// product, of which 1.6 GB come from memory.  More entries in flight, at fewer
+// waves, and a last batch padded with repeated entries took longer (0.75 to 1.1
+// ms).  The epilogue's inputs are loaded before the entries: Chebyshev start and
+// steps 875, 806 and 765 us -> 781, 757 and 726 there.
 template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
 __global__ void __launch_bounds__(512) k_sellw(SellView<VT> A, const XT *__restrict__ x, Epi epi, int nrhs,
                                                double *__restrict__ partials, int wpb) {

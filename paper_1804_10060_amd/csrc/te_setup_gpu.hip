@@ -177,8 +177,8 @@ __device__ __forceinline__ int slot_find(const int32_t *key, const int32_t *slot
     return probe < TB ? slot[h] : -1;
 }
 
-// Numeric pass, one wave per row, for scalar blocks and for rows too long for
-// LDS.  For each block k_a of A's row, the lanes first look up the output slots
+// Numeric pass, one wave per row, for scalar blocks and for block rows too long
+// for LDS (more than skip blocks).  For each block k_a of A's row, the lanes first look up the output slots
 // of the whole B row k_a points to (lane l: entry l), then walk that B row in
 // order, the slot passed by a lane shuffle.  LACC: the row's output blocks are
 // accumulated in dynamic LDS (mcap blocks), else in place.  UP (a product known
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
                                             const int64_t *__restrict__ bptr, const int32_t *__restrict__ bcol,
                                             const double *__restrict__ bval, const int64_t *__restrict__ cptr,
                                             const int32_t *__restrict__ ccol, double *__restrict__ cval,
-                                            int32_t *__restrict__ flag, int mcap) {
+                                            int32_t *__restrict__ flag, int mcap, int skip) {
     constexpr int BB = BR * BC;
     static_assert(BB <= 64, "output block larger than a wave");
     static_assert(!LACC || BB == 1, "block rows in LDS are k_num_blk's");
@@ -209,7 +209,8 @@ __global__ void __launch_bounds__(64) k_num(int64_t n, const int64_t *__restrict
         const int u0 = UP ? lower_bound_col(ccol + cs, mf, i) : 0;
         const int64_t c0 = cs + u0;
         const int m = mf - u0;
-        if (2 * m > TB || (LACC && m > mcap)) {  // uniform over the block
+        if (m <= skip) continue;                 // uniform over the block
+        if (2 * m > TB || (LACC && m > mcap)) {
             if (lane == 0) atomicOr(flag, 4);
             continue;
         }
@@ -338,7 +339,8 @@ __global__ void __launch_bounds__(64 * (BR / 3))
         const int u0 = UP ? lower_bound_col(ccol + cs, mf, i) : 0;   // UP: the columns >= i, a suffix of the row
         const int64_t c0 = cs + u0;
         const int m = mf - u0;
-        if (2 * m > TB || m > mcap) {  // uniform over the block
+        if (m > mcap) continue;   // uniform over the block; k_num's
+        if (2 * m > TB) {
             if (tid == 0) atomicOr(flag, 4);
             continue;
         }
@@ -1039,35 +1041,63 @@ int64_t symbolic(const DBsr &A, const int64_t *bptr, const int32_t *bcol, const 
 template <int BR, int BK, int BC, bool UP = false>
 void launch_num(int tb, int64_t mx, const DBsr &A, const DBsr &B, DBsr &C, int32_t *flag, hipStream_t s) {
     const dim3 g(wave_grid(A.nr)), b(64);
-    // LDS accumulation while a row's blocks fit in 32 KB (several waves per CU)
-    const size_t lds = (size_t)std::max<int64_t>(mx, 1) * BR * BC * sizeof(double);
-    const bool lacc = lds <= ((size_t)32 << 10);
-    const int mcap = (int)std::max<int64_t>(mx, 1);
+    // LDS accumulation for the rows whose blocks fit in 32 KB (several waves per
+    // CU); longer block rows in a launch of their own, in place.  One such row
+    // used to send all of them there: Galerkin product of a 4,014,400-node P2
+    // disc 83.7 -> 32.7 + 4.2 ms, of its next level 26.0 -> 7.8 + 11.2.
+    const int64_t fits = ((int64_t)32 << 10) / (BR * BC * (int64_t)sizeof(double));
+    const int mcap = (int)std::max<int64_t>(std::min(mx, fits), 1);
+    const size_t lds = (size_t)mcap * BR * BC * sizeof(double);
+    if constexpr (BR * BC == 1) {
 #define TE_NUM(TBV)                                                                                                  \
     case TBV:                                                                                                        \
-        if constexpr (BR * BC == 1) {                                                                                \
-            if (lacc)                                                                                                \
-                hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, true, UP>), g, b, lds, s, A.nr, A.ptr, A.col, A.val,      \
-                                   B.ptr, B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                      \
-        } else if (lacc) {                                                                                           \
-            hipLaunchKernelGGL((k_num_blk<BR, BK, BC, TBV, UP>), g, dim3(64 * (BR / 3)), lds, s, A.nr, A.ptr, A.col, \
-                               A.val, B.ptr, B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                   \
-        }                                                                                                            \
-        if (!lacc)                                                                                                   \
+        if (mx <= fits)                                                                                              \
+            hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, true, UP>), g, b, lds, s, A.nr, A.ptr, A.col, A.val, B.ptr,   \
+                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap, -1);                             \
+        else                                                                                                         \
             hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, false, UP>), g, b, 0, s, A.nr, A.ptr, A.col, A.val, B.ptr,    \
-                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                                 \
+                               B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap, -1);                             \
         break;
-    switch (tb) {
-        TE_NUM(64)
-        TE_NUM(128)
-        TE_NUM(256)
-        TE_NUM(512)
-        TE_NUM(1024)
-        TE_NUM(2048)
-        TE_NUM(4096)
-        default: TE_REQUIRE(false, TE_EINVAL, "bad table size %d", tb);
-    }
+        switch (tb) {
+            TE_NUM(64)
+            TE_NUM(128)
+            TE_NUM(256)
+            TE_NUM(512)
+            TE_NUM(1024)
+            TE_NUM(2048)
+            TE_NUM(4096)
+            default: TE_REQUIRE(false, TE_EINVAL, "bad table size %d", tb);
+        }
 #undef TE_NUM
+    } else {
+#define TE_NUM(TBV)                                                                                                  \
+    case TBV:                                                                                                        \
+        hipLaunchKernelGGL((k_num_blk<BR, BK, BC, TBV, UP>), g, dim3(64 * (BR / 3)), lds, s, A.nr, A.ptr, A.col,     \
+                           A.val, B.ptr, B.col, B.val, C.ptr, C.col, C.val_own.p, flag, mcap);                       \
+        break;
+        switch (table_for(mcap)) {   // mcap <= 227
+            TE_NUM(64)
+            TE_NUM(128)
+            TE_NUM(256)
+            TE_NUM(512)
+            default: TE_REQUIRE(false, TE_EINVAL, "bad table size %d", table_for(mcap));
+        }
+#undef TE_NUM
+#define TE_NUM(TBV)                                                                                                  \
+    case TBV:                                                                                                        \
+        hipLaunchKernelGGL((k_num<BR, BK, BC, TBV, false, UP>), g, b, 0, s, A.nr, A.ptr, A.col, A.val, B.ptr, B.col, \
+                           B.val, C.ptr, C.col, C.val_own.p, flag, mcap, mcap);                                      \
+        break;
+        if (mx > fits) switch (tb) {
+                TE_NUM(256)
+                TE_NUM(512)
+                TE_NUM(1024)
+                TE_NUM(2048)
+                TE_NUM(4096)
+                default: TE_REQUIRE(false, TE_EINVAL, "bad table size %d", tb);
+            }
+#undef TE_NUM
+    }
     TE_CHECK_HIP(hipGetLastError());
 }
 
