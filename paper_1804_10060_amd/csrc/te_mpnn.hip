@@ -169,7 +169,8 @@ __device__ __forceinline__ double vec_mat64(const V *v, const float *__restrict_
     return o;
 }
 
-// g = colsum/n (from partials), gw = g W_g + b (forward); one workgroup
+// g = colsum/n (from partials), gw = g W_g + b (forward) as two floats, the value
+// and what its rounding left; one workgroup
 __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restrict__ part, int64_t n,
                                                const float *__restrict__ P, int l, float *__restrict__ g,
                                                float *__restrict__ gw) {
@@ -183,7 +184,11 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
     }
     __syncthreads();
     const double a = vec_mat64<false>(gs, P + off_wg(l), lds);
-    if (c < 64) gw[c] = float(P[off_b(l) + c] + a);
+    if (c < 64) {
+        const double v = P[off_b(l) + c] + a;
+        gw[c] = float(v);
+        gw[MH + c] = float(v - double(float(v)));
+    }
 }
 
 // One message-passing layer, forward or backward.  Both are one product of
@@ -200,7 +205,7 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
 // A workgroup takes tiles of 16 MT vertices (contiguous, in XCD order: the
 // gathered rows of a tile stay in one L2).  Each wave gathers 4 MT of them
 // with its 64 lanes on the channels: the wave's neighbour entries are one
-// list, each lane looks up one entry's vertex and weights, the rows of 24
+// list, each lane looks up one entry's vertex and weights, the rows of 20
 // entries are loaded together.  The rows meet in LDS, and each wave multiplies
 // them by its 16 output channels' weights, which stay in 80 registers for
 // all tiles (v_mfma_f32_16x16x4: lane (q, i) holds channels 16 kb + 4 q + s of
@@ -208,7 +213,7 @@ __global__ void __launch_bounds__(SB) k_global(int nparts, const double *__restr
 // Bound: 2 * 320 * 64 flop per vertex (0.09 ms on 334,368 vertices at the
 // float32 matrix rate) and about 1.5 KB of rows per vertex (0.10 ms); what is
 // left is the latency of the gather's dependent loads.  334,368 vertices, per
-// layer: forward 1.72 -> 0.39 ms, backward (two kernels) 1.62 -> 0.41 ms, with
+// layer: forward 1.72 -> 0.40 ms, backward (two kernels) 1.62 -> 0.41 ms, with
 // one wave per vertex and vector FMAs before; with the rows of eight entries 0.42
 // and 0.44 ms.
 template <int MT, bool BWD>
@@ -220,7 +225,7 @@ __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, c
                                                     float *__restrict__ aout, const float *__restrict__ gate,
                                                     float *__restrict__ hout, float *__restrict__ gout,
                                                     double *__restrict__ part) {
-    constexpr int VT = 16 * MT, VW = VT / MW, EU = 24;
+    constexpr int VT = 16 * MT, VW = VT / MW, EU = 20;
     __shared__ float T[VT][LROW];
     const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
     const int i16 = lane & 15, q = lane >> 4, col = 16 * w + i16;
@@ -232,7 +237,9 @@ __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, c
 #pragma unroll
         for (int t = 0; t < 4; ++t) wr[kb * 4 + t] = BWD ? M[col * MH + k0 + t] : M[(k0 + t) * MH + col];
     }
-    const float gv = BWD ? gvec[col] / float(n) : gvec[col];
+    // forward: the rounding of gw is the same for every vertex and would not
+    // average out, so its remainder goes in first and its value last
+    const float gv = BWD ? gvec[col] / float(n) : gvec[MH + col], ghi = BWD ? 0.f : gvec[col];
     double cs = 0.0;
     const int64_t nb = gridDim.x, x = blockIdx.x & 7, xi = blockIdx.x >> 3;
     const int64_t lb = x * (nb >> 3) + (x < (nb & 7) ? x : (nb & 7)) + xi;   // workgroups of one XCD adjacent
@@ -336,6 +343,9 @@ __global__ void __launch_bounds__(MB, 2) k_mp_layer(int64_t n, int64_t ntiles, c
 #pragma unroll
             for (int m = 0; m < MT; ++m) acc[m] += sl[m];
         }
+        if (!BWD)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] += ghi;
         // lane (q, i) holds rows 4 q + r of channel col
 #pragma unroll
         for (int m = 0; m < MT; ++m)
@@ -816,7 +826,7 @@ extern "C" int mpnn_create(int64_t n, const int64_t *row_ptr, const int32_t *col
             H->a[l].alloc(n * MH);
             H->g[l].alloc(MH);
         }
-        H->gw.alloc(MH);
+        H->gw.alloc(2 * MH);
         H->y.alloc(n * MO);
         H->gh.alloc(n * MH);
         for (auto &b : H->ga) b.alloc(n * MH);
