@@ -323,7 +323,7 @@ typedef struct {
  * nrhs columns is used, plus Gram and update buffers that the first block
  * solve adds to the handle (kept for later calls).  Block CG
  * with MIXED is TE_EINVAL; a block P^T A P that is not positive definite is
- * TE_EINDEF.  Synchronises `stream`.
+ * TE_EINDEF.  Synchronises `stream`, also when it fails in the solve.
  * Returns TE_OK, TE_ENOTCONV (some column hit maxit), TE_EINDEF, TE_ENAN,
  * TE_EINVAL, TE_EHIP. */
 int amg_pcg_solve(amg_handle *h, const double *b, double *u, int32_t nrhs,

@@ -11,6 +11,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <type_traits>
 
 #include "te_amg.h"
@@ -466,6 +467,15 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
     const bool mixed = o.precision == TE_PREC_MIXED;
     TE_REQUIRE(o.precision == TE_PREC_FP64 || mixed, TE_EINVAL, "unknown precision %d", o.precision);
     TE_REQUIRE(!mixed || h->opt.build_fp32, TE_EINVAL, "mixed precision needs build_fp32 at setup");
+    // a failed solve leaves nothing running on the handle's vectors either (the
+    // V-cycle launched before the host has looked, or any launch before a HIP error)
+    struct IdleOnError {
+        hipStream_t s;
+        int before = std::uncaught_exceptions();
+        ~IdleOnError() {
+            if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(s);
+        }
+    } idle{s};
     if (o.block && m > 1) return block_solve_impl(h, b_nat, u_nat, m, o, rep, s);
     Level &L0 = h->L[0];
     const int64_t n = L0.n, rows = n * 3, nv = rows * m;
