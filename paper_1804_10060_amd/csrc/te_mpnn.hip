@@ -428,21 +428,22 @@ __global__ void __launch_bounds__(MB) k_out(int64_t n, const float *__restrict__
 // ---------------------------------------------------------------------------
 // dL/dy (MSE against a target: 2 (y - t) / 3n; or given) with constrained
 // entries zero, gh = gy W_out^T, ga = gh where the last layer's gate a is open;
-// per block: the loss, the output layer's gradients (64 x 3 and 3 values,
-// float partials at wpart) and the column sums of ga.  Lanes as in k_out.
-constexpr int OPART = MH * MO + MO;
+// per block: the loss, the output layer's gradients (64 x 3 float partials at
+// wpart, the three of the bias in double at bpart) and the column sums of ga.
+// Lanes as in k_out.
+constexpr int OPART = MH * MO;
 template <bool MSE>
 __global__ void __launch_bounds__(MB) k_out_bwd(int64_t n, const float *__restrict__ P, const float *__restrict__ h,
                                                 const float *__restrict__ a, const uint8_t *__restrict__ mask,
                                                 const float *__restrict__ y, const float *__restrict__ in,
                                                 float *__restrict__ gh, float *__restrict__ ga,
                                                 double *__restrict__ lpart, double *__restrict__ part,
-                                                float *__restrict__ wpart) {
-    __shared__ double s_cs[MW][MH], s_l[MW];
+                                                float *__restrict__ wpart, double *__restrict__ bpart) {
+    __shared__ double s_cs[MW][MH], s_l[MW], s_b[MW][MO];
     __shared__ float s_w[MW][OPART];
     const int j = threadIdx.x & 3, lane = threadIdx.x & 63, w = threadIdx.x / 64;
-    float wo[16][MO], gw[16][MO], gb[MO] = {0.f, 0.f, 0.f};
-    double cs[16], ls = 0.0;
+    float wo[16][MO], gw[16][MO];
+    double cs[16], gb[MO] = {0.0, 0.0, 0.0}, ls = 0.0;
     out_weights(P, j, wo);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
@@ -511,7 +512,7 @@ __global__ void __launch_bounds__(MB) k_out_bwd(int64_t n, const float *__restri
         if (j == 0) {
             s_l[w] = ls;
 #pragma unroll
-            for (int c = 0; c < MO; ++c) s_w[w][MH * MO + c] = gb[c];
+            for (int c = 0; c < MO; ++c) s_b[w][c] = gb[c];
         }
     }
     __syncthreads();
@@ -525,6 +526,11 @@ __global__ void __launch_bounds__(MB) k_out_bwd(int64_t n, const float *__restri
         float v = 0.f;
         for (int k = 0; k < MW; ++k) v += s_w[k][t];
         wpart[blockIdx.x * (int64_t)OPART + t] = v;
+    }
+    if (t < MO) {
+        double v = 0.0;
+        for (int k = 0; k < MW; ++k) v += s_b[k][t];
+        bpart[blockIdx.x * (int64_t)MO + t] = v;
     }
     if (MSE && t == 0) {
         double v = 0.0;
@@ -641,11 +647,11 @@ __global__ void __launch_bounds__(MB) k_wgrad_in(int64_t n, const float *__restr
 // Sums over the parts of nel-element partial tables, in double: a workgroup
 // takes 64 elements, its four waves a quarter of the parts each (in order),
 // the quarters added in order.  The sum of element e goes to out(e).
-template <class Out>
-__device__ __forceinline__ void sum_table(int nparts, int nel, const float *__restrict__ part, Out out) {
+template <typename T, class Out>
+__device__ __forceinline__ void sum_table(int nparts, int nel, const T *__restrict__ part, int block, Out out) {
     __shared__ double lds[MW][64];
     const int lane = threadIdx.x & 63, y = threadIdx.x / 64;
-    const int e = blockIdx.x * 64 + lane;
+    const int e = block * 64 + lane;
     const int b0 = nparts * y / MW, b1 = nparts * (y + 1) / MW;
     double s = 0.0;
     if (e < nel)
@@ -662,12 +668,20 @@ __device__ __forceinline__ void sum_table(int nparts, int nel, const float *__re
 }
 __global__ void __launch_bounds__(MB) k_sum_parts(int nparts, int nel, const float *__restrict__ part,
                                                   float *__restrict__ out) {
-    sum_table(nparts, nel, part, [&](int e, double t) { out[e] = float(t); });
+    sum_table(nparts, nel, part, blockIdx.x, [&](int e, double t) { out[e] = float(t); });
+}
+// the output layer's tables: the last workgroup takes the bias
+__global__ void __launch_bounds__(MB) k_sum_out(int nparts, const float *__restrict__ wpart,
+                                                const double *__restrict__ bpart, float *__restrict__ grad) {
+    if (blockIdx.x < OPART / 64)
+        sum_table(nparts, OPART, wpart, blockIdx.x, [&](int e, double t) { grad[OFF_WOUT + e] = float(t); });
+    else
+        sum_table(nparts, MO, bpart, 0, [&](int e, double t) { grad[OFF_BOUT + e] = float(t); });
 }
 // the [320][64] table of a layer to its five matrices
 __global__ void __launch_bounds__(MB) k_sum_layer(int nparts, const float *__restrict__ part, int l,
                                                   float *__restrict__ grad) {
-    sum_table(nparts, MK * MH, part, [&](int e, double t) {
+    sum_table(nparts, MK * MH, part, blockIdx.x, [&](int e, double t) {
         grad[off_slab(l, e / (MH * MH)) + e % (MH * MH)] = float(t);
     });
 }
@@ -778,7 +792,7 @@ struct mpnn_handle {
     te::DBuf<float> xf, invdl;  // float centred coordinates, 1 / (deg l) per vertex
     te::DBuf<float> h[te::ML + 1], m[te::ML], d[te::ML], a[te::ML], g[te::ML], gw;
     te::DBuf<float> y, gh, ga[2], gg, part;
-    te::DBuf<double> dpart, lpart;
+    te::DBuf<double> dpart, lpart, bpart;
     te::DBuf<float> X;     // last forward input (borrowed copy)
     te::DBuf<uint8_t> mask;
     bool have_forward = false;
@@ -834,6 +848,7 @@ extern "C" int mpnn_create(int64_t n, const int64_t *row_ptr, const int32_t *col
         H->part.alloc((size_t)RED_BLOCKS * MK * MH);
         H->dpart.alloc((size_t)LAYER_BLOCKS * MH);
         H->lpart.alloc(RED_BLOCKS);
+        H->bpart.alloc((size_t)RED_BLOCKS * MO);
         H->X.alloc(n * MF);
         H->mask.alloc(n * 3);
         TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -908,7 +923,7 @@ extern "C" int mpnn_forward(mpnn_handle *H, const float *P, const float *X, cons
 static void backward_tail(mpnn_handle *H, const float *P, float *grad, int np, hipStream_t s) {
     const int64_t n = H->n;
     const int nw = nparts_for(n);
-    hipLaunchKernelGGL(k_sum_parts, dim3((OPART + 63) / 64), dim3(MB), 0, s, np, OPART, H->part.p, grad + OFF_WOUT);
+    hipLaunchKernelGGL(k_sum_out, dim3(OPART / 64 + 1), dim3(MB), 0, s, np, H->part.p, H->bpart.p, grad);
     int cur = 0;
     for (int l = ML - 1; l >= 0; --l) {
         hipLaunchKernelGGL(k_layer_small, dim3(1), dim3(SB), 0, s, np, H->dpart.p, H->g[l].p, P, l, grad, H->gg.p);
@@ -937,7 +952,8 @@ extern "C" int mpnn_backward(mpnn_handle *H, const float *P, const float *target
         const int64_t n = H->n;
         const int np = nparts_for(n);
         hipLaunchKernelGGL(k_out_bwd<true>, dim3(np), dim3(MB), 0, s, n, P, H->h[ML].p, H->a[ML - 1].p, H->mask.p,
-                           H->y.p, target, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p);
+                           H->y.p, target, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p,
+                           H->bpart.p);
         TE_CHECK_HIP(hipGetLastError());
         backward_tail(H, P, grad, np, s);
         std::vector<double> lp;
@@ -956,7 +972,8 @@ extern "C" int mpnn_backward_from(mpnn_handle *H, const float *P, const float *g
         TE_REQUIRE(H->have_forward, TE_EINVAL, "mpnn_backward_from needs a preceding mpnn_forward");
         const int np = nparts_for(H->n);
         hipLaunchKernelGGL(k_out_bwd<false>, dim3(np), dim3(MB), 0, s, H->n, P, H->h[ML].p, H->a[ML - 1].p, H->mask.p,
-                           H->y.p, gy, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p);
+                           H->y.p, gy, H->gh.p, H->ga[0].p, H->lpart.p, H->dpart.p, H->part.p,
+                           H->bpart.p);
         TE_CHECK_HIP(hipGetLastError());
         backward_tail(H, P, grad, np, s);
         return TE_OK;
