@@ -24,10 +24,12 @@
 // adjoints of the neighbour mean and of the directional sums are gathers too:
 //   dL/dh_u gains (sum_{v in N(u)} ga_v / deg_v) W_n^T
 //                 + sum_k (sum_{v in N(u)} w^k_vu ga_v) W_dk^T.
-// Sums over the vertices (means, bias and weight gradients, loss) are
-// per-workgroup partials added in a fixed order in double: deterministic, no
-// atomics.  On 334,368 vertices a training step (forward, backward, Adam) went
-// from 22.8 to 4.7 ms.
+// Sums over the vertices are per-workgroup partials added in a fixed order in
+// double: deterministic, no atomics.  A workgroup forms its part of the means,
+// of the bias gradients and of the loss in double too, its part of the weight
+// gradients in float32 chains whose length does not grow with the mesh
+// (WCHAIN).  On 334,368 vertices a training step (forward, backward, Adam) went
+// from 22.8 to 4.8 ms.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -50,7 +52,8 @@ constexpr double S_U = 1.0e-3;
 constexpr int MB = 256, MW = MB / 64;
 constexpr int MK = 5 * MH;        // concatenated layer input: own row, neighbour mean, three directional sums
 constexpr int LROW = MK + 4;      // its LDS row, padded so that 16 rows read 16 bytes each without bank conflicts
-constexpr int RED_BLOCKS = 512;
+constexpr int RED_BLOCKS = 512;   // workgroups of the weight-gradient passes, more on meshes beyond 524,288 vertices
+constexpr int WCHAIN = 32;        // vertices whose products are added in one float32 chain
 constexpr int LAYER_BLOCKS = 768; // workgroups of a layer: the three a CU holds at once (LDS), on 256 CUs
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -543,9 +546,14 @@ __global__ void __launch_bounds__(MB) k_out_bwd(int64_t n, const float *__restri
 //   part[b][k][c] = sum_v [h | m | d](v, k) ga(v, c),  k < 320, c < 64
 // A wave holds 80 of the 320 rows (20 MFMA tiles of 16 x 16 in 80 registers);
 // four vertices per v_mfma_f32_16x16x4, operands straight from global memory
-// (16 channels of four rows: 64-byte pieces), two steps in flight.
+// (16 channels of four rows: 64-byte pieces), two steps in flight.  The tiles
+// are closed every WCHAIN vertices and added to 80 registers of their own, and a
+// chunk has at most WCHAIN of these chains, so no float32 sum has more than 64
+// steps; as one chain per chunk, vertices of equal sign were off by 157 units of
+// the last place at 334,368 and by 691 at 1,500,001, now by 12 and 14.
 // Bound: the float32 matrix rate and the rows, 0.09 and 0.10 ms per layer on
-// 334,368 vertices; 1.31 (three LDS-tiled vector products) -> 0.28 ms.
+// 334,368 vertices; 1.31 (three LDS-tiled vector products) -> 0.28 ms, of which
+// the second set of registers takes 0.006.
 __global__ void __launch_bounds__(MB, 2) k_wgrad(int64_t n, const float *__restrict__ h, const float *__restrict__ m,
                                                  const float *__restrict__ d, const float *__restrict__ ga,
                                                  float *__restrict__ part) {
@@ -559,11 +567,11 @@ __global__ void __launch_bounds__(MB, 2) k_wgrad(int64_t n, const float *__restr
         base[t] = (slab == 0 ? h : (slab == 1 ? m : d + (slab - 2) * MH)) + c0 + i16;
         ld[t] = slab < 2 ? MH : MD;
     }
-    f32x4 acc[MTW][4];
+    f32x4 sum[MTW][4];
 #pragma unroll
     for (int t = 0; t < MTW; ++t)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < 4; ++c) sum[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int64_t chunk = ((n + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;
     const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
     auto load = [&](int64_t r, float (&x)[MTW], float (&g)[4]) {
@@ -584,19 +592,31 @@ __global__ void __launch_bounds__(MB, 2) k_wgrad(int64_t n, const float *__restr
     if (lo < hi) {
         float x0[MTW], g0[4], x1[MTW], g1[4];
         load(lo, x0, g0);
-        for (int64_t r = lo; r < hi; r += 8) {
-            load(r + 4, x1, g1);   // past the chunk: zeros
+        for (int64_t r = lo; r < hi;) {
+            f32x4 acc[MTW][4];   // a chain of at most WCHAIN vertices
 #pragma unroll
             for (int t = 0; t < MTW; ++t)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0[t], g0[c], acc[t][c], 0, 0, 0);
-            load(r + 8, x0, g0);
+                for (int c = 0; c < 4; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int64_t end = r + WCHAIN < hi ? r + WCHAIN : hi;
+            for (; r < end; r += 8) {
+                load(r + 4, x1, g1);   // past the chunk: zeros
+#pragma unroll
+                for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0[t], g0[c], acc[t][c], 0, 0, 0);
+                load(r + 8, x0, g0);
+#pragma unroll
+                for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1[t], g1[c], acc[t][c], 0, 0, 0);
+            }
 #pragma unroll
             for (int t = 0; t < MTW; ++t)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1[t], g1[c], acc[t][c], 0, 0, 0);
+                for (int c = 0; c < 4; ++c) sum[t][c] += acc[t][c];
         }
     }
     float *o = part + blockIdx.x * (int64_t)(MK * MH);
@@ -605,7 +625,7 @@ __global__ void __launch_bounds__(MB, 2) k_wgrad(int64_t n, const float *__restr
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[((w * MTW + t) * 16 + 4 * q + r) * MH + 16 * c + i16] = acc[t][c][r];
+            for (int r = 0; r < 4; ++r) o[((w * MTW + t) * 16 + 4 * q + r) * MH + 16 * c + i16] = sum[t][c][r];
 }
 
 // The same for the input layer: part[b][k][c] = sum_v X(v, k) ga(v, c),
@@ -614,28 +634,36 @@ __global__ void __launch_bounds__(MB) k_wgrad_in(int64_t n, const float *__restr
                                                  float *__restrict__ part) {
     __shared__ float s_w[MW][MF * MH];
     const int lane = threadIdx.x & 63, w = threadIdx.x / 64, i16 = lane & 15, q = lane >> 4;
-    f32x4 acc[4];
+    f32x4 sum[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < 4; ++c) sum[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int64_t chunk = ((n + gridDim.x - 1) / gridDim.x + 15) / 16 * 16;
     const int64_t lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-    for (int64_t r = lo + 4 * w; r < hi; r += 4 * MW) {
-        const int64_t v = r + q;
-        const bool ok = v < hi;
-        const int64_t vv = ok ? v : lo;
-        const float z = X[vv * MF + (i16 < MF ? i16 : 0)];
-        const float x = ok && i16 < MF ? z : 0.f;
+    for (int64_t r = lo + 4 * w; r < hi;) {
+        f32x4 acc[4];   // a chain of at most WCHAIN vertices
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float y = ga[vv * MH + 16 * c + i16];
-            acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, ok ? y : 0.f, acc[c], 0, 0, 0);
+        for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < WCHAIN / 4; ++t, r += 4 * MW) {
+            const int64_t v = r + q;
+            const bool ok = v < hi;   // past the chunk: zeros
+            const int64_t vv = ok ? v : lo;
+            const float z = X[vv * MF + (i16 < MF ? i16 : 0)];
+            const float x = ok && i16 < MF ? z : 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float y = ga[vv * MH + 16 * c + i16];
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, ok ? y : 0.f, acc[c], 0, 0, 0);
+            }
         }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sum[c] += acc[c];
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            if (4 * q + r < MF) s_w[w][(4 * q + r) * MH + 16 * c + i16] = acc[c][r];
+            if (4 * q + r < MF) s_w[w][(4 * q + r) * MH + 16 * c + i16] = sum[c][r];
     __syncthreads();
     for (int e = threadIdx.x; e < MF * MH; e += MB) {
         float t = 0.f;
@@ -800,6 +828,13 @@ struct mpnn_handle {
 
 using namespace te;
 
+// Workgroups of the weight-gradient and output passes: 64 vertices each at
+// least, and 1024 (WCHAIN chains of WCHAIN) at most
+static int nparts_for(int64_t n) {
+    const int64_t most = std::max<int64_t>(RED_BLOCKS, (n + WCHAIN * WCHAIN - 1) / (WCHAIN * WCHAIN));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(most, (n + 63) / 64));
+}
+
 extern "C" int64_t mpnn_param_count(void) { return NPARAM; }
 
 extern "C" int mpnn_create(int64_t n, const int64_t *row_ptr, const int32_t *col_idx, const double *coords,
@@ -845,10 +880,11 @@ extern "C" int mpnn_create(int64_t n, const int64_t *row_ptr, const int32_t *col
         H->gh.alloc(n * MH);
         for (auto &b : H->ga) b.alloc(n * MH);
         H->gg.alloc(MH);
-        H->part.alloc((size_t)RED_BLOCKS * MK * MH);
-        H->dpart.alloc((size_t)LAYER_BLOCKS * MH);
-        H->lpart.alloc(RED_BLOCKS);
-        H->bpart.alloc((size_t)RED_BLOCKS * MO);
+        const size_t np = nparts_for(n);
+        H->part.alloc(np * MK * MH);
+        H->dpart.alloc(std::max<size_t>(LAYER_BLOCKS, np) * MH);
+        H->lpart.alloc(np);
+        H->bpart.alloc(np * MO);
         H->X.alloc(n * MF);
         H->mask.alloc(n * 3);
         TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -872,9 +908,6 @@ extern "C" int mpnn_features(mpnn_handle *H, const double *T, double T_ref, cons
         return TE_OK;
     });
 }
-
-// workgroups of the weight-gradient and output passes: 64 vertices each at least
-static int nparts_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(RED_BLOCKS, (n + 63) / 64)); }
 
 // Tiles of 32 vertices; of 16 while that leaves CUs without a tile, so that a
 // small mesh spreads over twice the workgroups.

@@ -8,7 +8,9 @@ and of the channels into the outputs, layer biases one: h_l = h_0 + l, every gat
 is open, and dL/dy reaches every layer unchanged, so each gradient is n times one
 product.
 
-Tolerance: bias gradients are added in double and rounded once (2 u)."""
+Tolerance: bias gradients are added in double and rounded once (2 u).  Weight
+gradients are chains of at most 32 vertices, 32 of which are added before the
+rest is added in double; with the products and the sums of four waves: 72 u."""
 import numpy as np
 import pytest
 
@@ -59,3 +61,15 @@ def test_bias_gradients_are_rounded_once(n):
     errs.update({f"b{l}": _off(g[f"b{l}"], s) for l in range(om.L)})
     say("bias gradients", n, errs)
     assert max(errs.values()) <= 2.0
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_weight_gradients_do_not_grow_with_the_mesh(n):
+    from oracle import mpnn as om
+    g, h0, s, sy = _gradients(n)
+    errs = {"W_in": _off(g["W_in"], (1.0 + np.arange(10) / 16.0)[:, None] * s), "W_out": _off(g["W_out"], (h0 + om.L)[:, None] * sy)}
+    for l in range(om.L):
+        errs[f"W_s{l}"] = _off(g[f"W_s{l}"], (h0 + l)[:, None] * s)
+        errs[f"W_n{l}"] = _off(g[f"W_n{l}"], (h0 + l)[:, None] * s)
+    say("weight gradients", n, errs)
+    assert max(errs.values()) <= 72.0
