@@ -101,8 +101,9 @@ int fe_assemble_pattern(const te_mesh *mesh, int64_t *row_ptr, int64_t *nnzb_out
  *   u_bc: device [N][3] prescribed values or NULL (= 0);
  *   A: row_ptr from fe_assemble_pattern, col_idx/val caller-allocated with
  *      A->nnzb entries; both are overwritten.  b: device [3N], overwritten.
- * Deterministic (gather-based, no atomics in the sums).  Errors: TE_EINVAL,
- * TE_ENOMEM, TE_EHIP. */
+ * Deterministic (gather-based, no atomics in the sums).  Errors: TE_EINVAL (a
+ * row_ptr of another mesh among them: b is left as it was then, the rows of
+ * col_idx and val that fit this mesh are not), TE_ENOMEM, TE_EHIP. */
 int fe_assemble_thermoelastic(const te_mesh *mesh, const te_material *mat, const double *T,
                               const double *f, const uint8_t *dir_mask, const double *u_bc,
                               te_bsr *A, double *b, hipStream_t stream);

@@ -695,16 +695,15 @@ __global__ void __launch_bounds__(64, 4) k_stiff(AsmArgs A, int64_t nnzb, int32_
 }
 
 // Columns and values of the rows of a pattern whose row pointer the caller holds.
-// The flag is read after `also`, launches that need neither.
-template <typename F>
-static void stiffness_rows(const AsmArgs &a, int degree, int64_t nnzb, hipStream_t s, F &&also) {
+// A refused row pointer is found on the way: rows that match are written by then,
+// so the caller writes its other outputs after this.
+static void stiffness_rows(const AsmArgs &a, int degree, int64_t nnzb, hipStream_t s) {
     DBuf<int32_t> ovf(1);
     TE_CHECK_HIP(hipMemsetAsync(ovf.p, 0, sizeof(int32_t), s));
     const unsigned gs = (unsigned)std::min<int64_t>(a.n, 1 << 18);
     if (degree == 1) hipLaunchKernelGGL(k_stiff<1>, dim3(gs), dim3(64), 0, s, a, nnzb, ovf.p);
     else hipLaunchKernelGGL(k_stiff<2>, dim3(gs), dim3(64), 0, s, a, nnzb, ovf.p);
     TE_CHECK_HIP(hipGetLastError());
-    also();
     int32_t h = 0;
     TE_CHECK_HIP(hipMemcpyAsync(&h, ovf.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     TE_CHECK_HIP(hipStreamSynchronize(s));
@@ -1165,7 +1164,8 @@ extern "C" int fe_assemble_thermoelastic(const te_mesh *mesh, const te_material 
                    (long long)nnzb);
         AsmArgs a{mesh->coords, mesh->cells, npe, I.start.p, I.inc.p, mesh->n_nodes, lam, mu, calpha, mat->T_ref,
                   nullptr, T, f, A->row_ptr, A->col_idx, A->val, b, 1};
-        stiffness_rows(a, mesh->degree, nnzb, stream, [&] { launch_load(a, mesh->degree, stream); });
+        stiffness_rows(a, mesh->degree, nnzb, stream);
+        launch_load(a, mesh->degree, stream);
         if (dir_mask) {
             unsigned gd = (unsigned)std::min<int64_t>((mesh->n_nodes + 31) / 32, 1 << 20);
             hipLaunchKernelGGL(k_dirichlet, dim3(gd), dim3(256), 0, stream, mesh->n_nodes, A->row_ptr, A->col_idx,
@@ -1267,14 +1267,14 @@ extern "C" int fe_assemble_thermoelastic_materials(const te_mesh *mesh, const te
         }
         AsmArgs a{mesh->coords, mesh->cells, npe, I.start.p, I.inc.p, n, 0.0, 0.0, 0.0, mat->T_ref,
                   coef.p, T, f, A->row_ptr, A->col_idx, A->val, b, 1};
-        stiffness_rows(a, mesh->degree, nnzb, stream, [&] {
-            launch_load(a, mesh->degree, stream);
-            if (!has_p) return;
+        stiffness_rows(a, mesh->degree, nnzb, stream);
+        launch_load(a, mesh->degree, stream);
+        if (has_p) {
             const unsigned gp = (unsigned)std::min<int64_t>((n + 255) / 256, 1 << 20);
             hipLaunchKernelGGL(k_pressure, dim3(gp), dim3(256), 0, stream, n, PF.start.p, PF.inc.p, npf,
                                pressure->faces, pressure->p, mesh->coords, b);
             TE_CHECK_HIP(hipGetLastError());
-        });
+        }
         if (dir_mask) {
             const unsigned gd = (unsigned)std::min<int64_t>((n + 31) / 32, 1 << 20);
             hipLaunchKernelGGL(k_dirichlet, dim3(gd), dim3(256), 0, stream, n, A->row_ptr, A->col_idx, A->val, b,
