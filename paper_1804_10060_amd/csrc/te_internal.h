@@ -175,9 +175,13 @@ constexpr int FMT_ROWWAVE = 1;
 struct Tune {
     int wpb = 4, spw = 1, remap = 1, nt = 0;
     int mwpb = 4;    // several right-hand sides: waves per workgroup
-    int mtile = 0;   // several right-hand sides on the SELL layout: columns per pass (0: row per wave)
+    int mtile = 0;   // several right-hand sides on the SELL layout: columns per pass (0: row per wave above 32 columns)
     int msplit = 0;  // ... and the column tiles on different XCDs instead of passes
     int xb = 0;      // one wave per row: a slot's lanes share the block column's x entries by lane permutes
+    bool operator==(const Tune &o) const {
+        return wpb == o.wpb && spw == o.spw && remap == o.remap && nt == o.nt && mwpb == o.mwpb && mtile == o.mtile &&
+               msplit == o.msplit && xb == o.xb;
+    }
 };
 
 struct Sell {
@@ -226,6 +230,9 @@ constexpr size_t kPinBytes = sizeof(CgScalars) - offsetof(CgScalars, rr);
 // ---- kernel launchers (te_kernels.hip) ------------------------------------
 template <typename T>
 void sell_apply(const Sell &A, const T *x, T *y, const T *g, int mode, int nrhs, hipStream_t s);
+// c with what does not reach the launch of a product with nrhs columns taken
+// from d: two configurations launch the same if this makes them equal
+Tune effective_tune(const Sell &A, int nrhs, Tune c, const Tune &d);
 void sell_resid_norm(const Sell &A, const double *x, const double *g, double *y, int nrhs, double *partials,
                      hipStream_t s);
 void sell_dot(const Sell &A, const double *p, double *q, int nrhs, double *partials, hipStream_t s);

@@ -525,6 +525,47 @@ static int rowm_waves(const Sell &A, int slots) {
     return w;
 }
 
+static inline int rowm_cols(int nrhs) { return nrhs <= 2 ? 2 : nrhs <= 4 ? 4 : nrhs <= 8 ? 8 : nrhs <= 16 ? 16 : WAVE; }
+
+// column tiles of the row-group product, and whether they can go to different XCDs
+static inline unsigned multi_tiles(int nrhs, int R, int S) {
+    const int tile = (WAVE / R) * S;
+    return (unsigned)((nrhs + tile - 1) / tile);
+}
+static inline bool splits_over_xcds(unsigned tiles) { return tiles == 2 || tiles == 4 || tiles == 8; }
+
+Tune effective_tune(const Sell &A, int nrhs, Tune c, const Tune &d) {
+    if (nrhs == 1) {
+        if (launch_split(A) > 1) {
+            c.wpb = d.wpb;
+            c.spw = d.spw;
+            c.remap = d.remap;
+        }
+        if (A.format == FMT_SELL) c.xb = d.xb;
+        c.mwpb = d.mwpb;
+        c.mtile = d.mtile;
+        c.msplit = d.msplit;
+        return c;
+    }
+    c.wpb = d.wpb;
+    c.spw = d.spw;
+    c.remap = d.remap;
+    c.nt = d.nt;
+    c.xb = d.xb;
+    if (A.format == FMT_ROWWAVE) {
+        const int cols = rowm_cols(nrhs);
+        if (cols < WAVE || rowm_waves(A, 1) > 1) c.mwpb = d.mwpb;
+        c.mtile = d.mtile;
+        c.msplit = d.msplit;
+        return c;
+    }
+    const int R = multi_rows(nrhs, c.mtile), S = multi_cols(nrhs, c.mtile);
+    if (R == 1 || !splits_over_xcds(multi_tiles(nrhs, R, S))) c.msplit = d.msplit;
+    if (R == multi_rows(nrhs, d.mtile) && (R == 1 || S == multi_cols(nrhs, d.mtile))) c.mtile = d.mtile;
+    else if (R > 1) c.mtile = 16 * S;
+    return c;
+}
+
 template <int BR, int BC, typename VT, typename XT, typename AT, class Epi>
 static void launch_rowm(const Sell &A, const VT *val, const XT *x, const Epi &epi, int nrhs, int mwpb, hipStream_t s) {
     auto go = [&](auto kern, int c) {
@@ -534,11 +575,13 @@ static void launch_rowm(const Sell &A, const VT *val, const XT *x, const Epi &ep
         const size_t lds = c == WAVE && wpr == 1 ? 0 : (size_t)waves * BR * c * sizeof(AT);
         hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(waves * WAVE), lds, s, rview(A, val), x, epi, nrhs, wpr);
     };
-    if (nrhs <= 2) go(k_rowm<BR, BC, VT, XT, AT, Epi, 2>, 2);
-    else if (nrhs <= 4) go(k_rowm<BR, BC, VT, XT, AT, Epi, 4>, 4);
-    else if (nrhs <= 8) go(k_rowm<BR, BC, VT, XT, AT, Epi, 8>, 8);
-    else if (nrhs <= 16) go(k_rowm<BR, BC, VT, XT, AT, Epi, 16>, 16);
-    else go(k_rowm<BR, BC, VT, XT, AT, Epi, 64>, 64);
+    switch (rowm_cols(nrhs)) {
+        case 2: go(k_rowm<BR, BC, VT, XT, AT, Epi, 2>, 2); break;
+        case 4: go(k_rowm<BR, BC, VT, XT, AT, Epi, 4>, 4); break;
+        case 8: go(k_rowm<BR, BC, VT, XT, AT, Epi, 8>, 8); break;
+        case 16: go(k_rowm<BR, BC, VT, XT, AT, Epi, 16>, 16); break;
+        default: go(k_rowm<BR, BC, VT, XT, AT, Epi, WAVE>, WAVE);
+    }
     TE_CHECK_HIP(hipGetLastError());
 }
 
@@ -598,12 +641,11 @@ static void launch_t(const Sell &A, const VT *val, const XT *x, const Epi &epi, 
             return;
         }
         const int S = multi_cols(nrhs, t.mtile);
-        const int tile = (WAVE / R) * S;
-        const unsigned tiles = (unsigned)((nrhs + tile - 1) / tile);
+        const unsigned tiles = multi_tiles(nrhs, R, S);
         dim3 grid((unsigned)g, tiles);
         int split = 0;
         int64_t chunk = 0;
-        if (t.msplit && (tiles == 2 || tiles == 4 || tiles == 8)) {
+        if (t.msplit && splits_over_xcds(tiles)) {
             split = (int)tiles;
             chunk = (g + 8 / split - 1) / (8 / split);
             grid = dim3((unsigned)(8 * chunk), 1);

@@ -19,6 +19,7 @@
 #include <sstream>
 #include <string>
 #include <utility>
+#include <vector>
 
 #include "te_amg.h"
 
@@ -97,14 +98,16 @@ float time_op(Sell &A, Tune &slot, const Tune &cand, const T *x, T *y, hipStream
 
 // Waves per workgroup and, on the SELL layout with more than 16 columns,
 // the column tile (16, 32 or 64 columns per pass over the matrix, or 0: one
-// row per wave with a lane per column) of the nrhs-column products; the
-// single-RHS choice in `slot` is kept.
+// row per wave with a lane per column above 32 columns, as 32 below) of the
+// nrhs-column products, each distinct launch once; the single-RHS choice in
+// `slot` is kept.
 template <typename T>
 void tune_multi(Sell &A, Tune &slot, const std::string &key, const T *x, T *y, int nrhs,
                 std::map<std::string, Tune> &cache, hipStream_t s, hipEvent_t e0, hipEvent_t e1, std::string &report) {
     const Tune keep = slot;
     Tune best = keep;
     float best_t = INFINITY, def_t = 0.f;
+    std::vector<Tune> timed;
     const bool tiles = A.format == FMT_SELL && nrhs > 16;
     const std::pair<int, int> shapes[] = {{0, 0}, {64, 0}, {32, 0}, {16, 0}, {32, 1}, {16, 1}};
     for (const auto &sh : shapes) {
@@ -116,8 +119,11 @@ void tune_multi(Sell &A, Tune &slot, const std::string &key, const T *x, T *y, i
             c.mwpb = m;
             c.mtile = mt;
             c.msplit = sh.second;
+            c = effective_tune(A, nrhs, c, keep);
+            if (std::find(timed.begin(), timed.end(), c) != timed.end()) continue;
+            timed.push_back(c);
             const float t = time_op<T>(A, slot, c, x, y, s, e0, e1, nrhs);
-            if (m == 4 && mt == keep.mtile && !sh.second) def_t = t;
+            if (c == keep) def_t = t;
             if (t < best_t) {
                 best_t = t;
                 best = c;
@@ -154,6 +160,7 @@ void tune_one(Sell &A, Tune &slot, const char *dtype, const T *x, T *y, std::map
     }
     const Tune def = slot;   // the operator's untuned configuration
     Tune best;
+    std::vector<Tune> timed;   // each distinct launch once
     float best_t = INFINITY, def_t = 0.f;
     // the shared x entries exist for one wave per row (blocks no wider than tall)
     const int nxb = A.format == FMT_ROWWAVE && A.bc <= A.br ? 2 : 1;
@@ -164,9 +171,11 @@ void tune_one(Sell &A, Tune &slot, const char *dtype, const T *x, T *y, std::map
                     for (int nt : {0, 1}) {
                         Tune c{wpb, spw, remap, nt};
                         c.xb = xb;
+                        c = effective_tune(A, 1, c, def);
+                        if (std::find(timed.begin(), timed.end(), c) != timed.end()) continue;
+                        timed.push_back(c);
                         const float t = time_op<T>(A, slot, c, x, y, s, e0, e1);
-                        if (wpb == def.wpb && spw == def.spw && remap == def.remap && nt == def.nt && xb == def.xb)
-                            def_t = t;
+                        if (c == def) def_t = t;
                         if (t < best_t) {
                             best_t = t;
                             best = c;
