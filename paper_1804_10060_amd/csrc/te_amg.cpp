@@ -634,6 +634,7 @@ static void alloc_work(amg_handle *h, hipStream_t) {
     h->partials.alloc((size_t)np * m * 2 + 64);
     h->sums.alloc(4 * 64);
     h->scal.alloc(cg_scalars_bytes());
+    h->pin.alloc(kPinBytes);
     h->colsel.alloc(64);
 }
 

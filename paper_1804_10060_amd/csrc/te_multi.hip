@@ -560,7 +560,6 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
     // active, cand and flag in one copy, to pinned memory where they fit
     const size_t mb = 3 * (size_t)n * sizeof(int32_t);
     PinBuf &pin = hs[0]->pin;
-    if (!pin.p) pin.alloc(kPinBytes);
     std::vector<int32_t> own;
     if (mb > pin.n) own.resize(3 * (size_t)n);
     int32_t *marks = own.empty() ? reinterpret_cast<int32_t *>(pin.p) : own.data();

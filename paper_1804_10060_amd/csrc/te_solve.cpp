@@ -561,7 +561,6 @@ static int solve_impl(amg_handle *h, const double *b_nat, double *u_nat, int m, 
     // ten vectors; 1 GB of it takes 0.3 ms, 20 to 30 iterations wait 0.5 to 0.75.
     // With two pageable copies and the wait before it: 14,739-unknown cube 1.28 ->
     // 0.96 ms a solve, 69,000-node P2 disc 11.2 -> 9.6 ms.
-    if (!h->pin.p) h->pin.alloc(kPinBytes);
     const char *pin = h->pin.p;
     const double *pin_rr = reinterpret_cast<const double *>(pin);
     const int32_t *pin_flag = reinterpret_cast<const int32_t *>(pin + offsetof(CgScalars, flag) - offsetof(CgScalars, rr));
