@@ -265,7 +265,7 @@ def learned_form_small(torch):
 
 def multi_mesh_form(te, torch, dev):
     """32 P1 discs (DOF log-uniform in [1e4, 5e5], bump fields of seeds
-    2000-2031) in one persistent graph-replayed launch sequence against 32
+    2000-2031) in one graph-replayed sequence of grouped launches against 32
     single float64 solves; the smallest and the largest mesh against the
     stored oracle solutions of those meshes."""
     import numpy as np

@@ -334,9 +334,9 @@ int amg_pcg_solve(amg_handle *h, const double *b, double *u, int32_t nrhs,
  * h[i] (from amg_setup; same Chebyshev degree), right-hand side b[i] and
  * guess/solution u[i] (device [3 N_i] each, float64 only).  Every phase of
  * the CG iteration is one launch over the (mesh, level, row-tile) work, and
- * one iteration is captured once as a HIP graph and replayed; each system keeps its own CG recurrence and stop test, so system
- * i gets the standalone amg_pcg_solve of b[i] (up to the summation order of
- * reductions).  rep: host array of n reports (nrhs = 1 each) or NULL;
+ * one iteration is captured once as a HIP graph and replayed; each system
+ * keeps its own CG recurrence and stop test, so system i gets the standalone
+ * amg_pcg_solve of b[i] (up to the summation order of reductions).  rep: host array of n reports (nrhs = 1 each) or NULL;
  * time_ms is the elapsed time of the whole batch.  The handles' solve
  * workspaces are used, so they must not be in use elsewhere meanwhile.
  * Returns TE_OK, TE_ENOTCONV, TE_EINDEF, TE_ENAN, TE_EINVAL, TE_EHIP. */
@@ -346,8 +346,8 @@ int amg_pcg_solve_multi(amg_handle **h, int32_t n, const double *const *b, doubl
 /* Autotuner of amg_pcg_solve_multi for the set h[0..n-1]: times the grouped
  * launches (one V-cycle of every system plus the level-0 product, median of
  * 5 after a warm-up) for a grid of one workgroup per row tile or a persistent
- * one of 1, 2 or 4 times the workgroups the device holds at once, and for the work items in the order given or
- * largest system first, and keeps the fastest in every handle (later
+ * one of 1, 2 or 4 times the workgroups the device holds at once, and for the
+ * work items in the order given or largest system first, and keeps the fastest in every handle (later
  * amg_pcg_solve_multi calls on them use it).  report (host, may be NULL):
  * text of the choice.  Overwrites the handles' solve workspaces; synchronises.
  * Returns TE_OK, TE_EINVAL, TE_EHIP. */

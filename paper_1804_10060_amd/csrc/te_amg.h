@@ -131,8 +131,8 @@ struct amg_handle {
     te::PinBuf pin;                // what the host reads of scal each iteration
     te::DBuf<int32_t> colsel;      // [64] column selector of copy_cols
     // launch shape of amg_pcg_solve_multi over a set of handles (te_autotune_multi):
-    // persistent grid multiplier (0: one workgroup per tile) and work-item order
-    // (0: as given, 1: largest first)
+    // grid (0: one workgroup per tile, else the multiplier of a persistent one) and
+    // work-item order (0: as given, 1: largest first)
     int multi_grid = 0, multi_order = 0;
     // block-CG workspace, allocated by the first block solve and kept:
     // Gram partials and results, the two small coefficient matrices, X/R partials

@@ -348,14 +348,6 @@ __device__ __forceinline__ void p2_grad(int a, double l0, double l1, double l2, 
     }
 }
 
-__device__ __forceinline__ double p2_val(int a, double l0, double l1, double l2, double l3) {
-    if (a < 4) {
-        const double la = sel4(l0, l1, l2, l3, a);
-        return la * (2.0 * la - 1.0);
-    }
-    return 4.0 * sel4(l0, l1, l2, l3, c_edge[a - 4][0]) * sel4(l0, l1, l2, l3, c_edge[a - 4][1]);
-}
-
 // closed-form P2 mass matrix times 420/|K|
 __device__ __forceinline__ double p2_mass420(int a, int c) {
     if (a < 4 && c < 4) return a == c ? 6.0 : 1.0;

@@ -9,9 +9,12 @@
 // is remapped so that each XCD streams one contiguous range of slices and
 // keeps its own L2 window of x.
 //
-// Multi-RHS products (nrhs > 1, vectors laid out [row][comp][rhs]) use one
-// wave per block row with the right-hand sides on the lanes; the block values
-// are wave-uniform and come through the scalar cache.
+// Multi-RHS products (nrhs > 1, vectors laid out [row][comp][rhs]) of SELL
+// operators take several block rows per wave, each with a group of lanes over
+// its columns (k_sellm); above 32 columns one wave per block row with the
+// right-hand sides on the lanes and the block values through the scalar cache
+// (k_sellw).  Wave-per-row operators put slots of entries times columns on the
+// lanes (k_rowm).
 //
 // Epilogues fuse the vector work of the Chebyshev smoother (Saad, Alg. 12.1),
 // the residual of the V-cycle and the dot products of CG into the product.

@@ -909,8 +909,11 @@ extern "C" int mpnn_features(mpnn_handle *H, const double *T, double T_ref, cons
     });
 }
 
-// Tiles of 32 vertices; of 16 while that leaves CUs without a tile, so that a
-// small mesh spreads over twice the workgroups.
+// Tiles of 32 vertices; of 16 while tiles of 32 would leave some of the
+// LAYER_BLOCKS workgroups without one.  Forward and backward pass with tiles of 16
+// and of 32: 4,624 vertices 81, 206 and 98, 219 us; 8,648: 104, 243 and 122, 256;
+// 23,808: 166, 353 and 169, 358; 15,600, where 975 tiles of 16 leave some
+// workgroups with a second one: 150, 304 and 138, 285.
 static bool wide_tiles(int64_t n) { return (n + 31) / 32 > LAYER_BLOCKS; }
 static int layer_blocks(int64_t n) {
     const int64_t nt = wide_tiles(n) ? (n + 31) / 32 : (n + 15) / 16;

@@ -1,9 +1,10 @@
 // Multi-mesh solve: many independent systems (each with its own SA-AMG
 // hierarchy from amg_setup) advanced together.  Every phase of the CG
-// iteration is ONE persistent launch over a queue of (mesh, level, row-tile)
-// work items, so meshes of uneven size share the GPU instead of running
-// small launches one after another; one whole iteration is captured once as
-// a HIP graph and replayed.  Each mesh keeps its own CG recurrence, its own
+// iteration is ONE launch over the (mesh, level, row-tile) work items of all
+// meshes, a workgroup per tile or, if the tuner finds it faster, a persistent
+// grid, so meshes of uneven size share the GPU instead of running small launches
+// one after another; one whole iteration is captured once as a HIP graph and
+// replayed.  Each mesh keeps its own CG recurrence, its own
 // stop test (the device stops a mesh whose recurrence residual passes; the
 // host then checks the true residual), so mesh i gets the standalone solve
 // of its right-hand side up to the summation order of the dot products.
@@ -644,11 +645,11 @@ int multi_impl(amg_handle **hs, int n, const double *const *b, double *const *u,
 
 namespace te {
 namespace {
-// Launch shape of the grouped phases for one set of hierarchies: the grid (one workgroup per tile, or persistent with 1, 2 or 4 times the resident
-// workgroups) and the work-item
-// order (meshes as given, or largest first), timed on one V-cycle of every
-// mesh plus the level-0 product (median of 5 after a warm-up, HIP events),
-// the best kept in every handle.  Overwrites the handles' solve workspace.
+// Launch shape of the grouped phases for one set of hierarchies: the grid (one
+// workgroup per tile, or persistent with 1, 2 or 4 times the resident
+// workgroups) and the work-item order (meshes as given, or largest first), timed
+// on one V-cycle of every mesh plus the level-0 product (median of 5 after a
+// warm-up, HIP events), the best kept in every handle.  Overwrites the handles' solve workspace.
 int autotune_multi_impl(amg_handle **hs, int n, char *report, int64_t len, hipStream_t s) {
     TE_REQUIRE(hs && n >= 1, TE_EINVAL, "bad argument");
     MultiState M;

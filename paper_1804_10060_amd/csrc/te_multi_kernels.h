@@ -1,6 +1,6 @@
 // Multi-mesh solve: many independent hierarchies advanced together, each
-// phase of the CG iteration one persistent launch over a queue of
-// (mesh, level, row-tile) work, one iteration captured in a HIP graph.
+// phase of the CG iteration one launch over their (mesh, level, row-tile)
+// work, one iteration captured in a HIP graph.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -243,8 +243,8 @@ __global__ void k_multi_beta(MultiScal S, const int32_t *__restrict__ mask, cons
 // ---- launchers -------------------------------------------------------------
 constexpr int GROUP_GRID = 2048;
 
-// Workgroups of a kernel resident on the whole device at once (the grid of a
-// persistent launch); queried once per kernel.
+// Workgroups of a kernel resident on the whole device at once (the unit of a
+// persistent grid); queried once per kernel.
 template <class K>
 int64_t resident_groups(K kernel, int threads) {
     int dev = 0, ncu = 0, per_cu = 0;

@@ -4,8 +4,11 @@
 // for the float64 and float32 copies: for one right-hand side the waves per
 // workgroup, slices (rows) per wave, XCD block order and non-temporal value
 // loads, and for the operators stored one wave per row whether a slot's
-// lanes share the x entries by lane permutes; for the hierarchy's max_nrhs right-hand sides (when above one) the
-// block rows per workgroup of the multi-RHS products.  Choices can be stored
+// lanes share the x entries by lane permutes; for the hierarchy's max_nrhs
+// right-hand sides (when above one) the waves per workgroup and the column tile
+// of the multi-RHS products.  Each distinct launch is timed once: what a
+// configuration cannot change of an operator's launch (the waves that share a
+// row of a small operator, say) keeps its untuned value.  Choices can be stored
 // in and re-read from a small JSON file keyed by the operator's shape class
 // (and the number of right-hand sides), so a second run on a similar problem
 // applies them without timing.

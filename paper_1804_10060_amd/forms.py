@@ -8,7 +8,7 @@ Prints one JSON object.  Workloads (seeded, synthetic):
             P1 disc 104x452x13 (1,993,320 DOF): one 64-column solve (64 CG
             recurrences, and block CG) vs 64 single-column solves;
   multi   : 32 P1 discs with DOF log-uniform in [1e4, 5e5]: one multi-mesh
-            solve (persistent launches, graph replay) vs 32 separate solves;
+            solve (grouped launches, graph replay) vs 32 separate solves;
   learned : P1 disc 80x344x11 (1,003,104 DOF); 2000 training and 200
             held-out load fields solved by the library, the network trained
             by the library's kernels, then held-out solves from the learned
@@ -143,7 +143,7 @@ def multi_form(quick=False):
     te.solve_multi(hs, bs)
     torch.cuda.synchronize()
     t_untuned = time.perf_counter() - t0
-    tune_multi = te.autotune_multi(hs)   # persistent grid and work order of the grouped launches
+    tune_multi = te.autotune_multi(hs)   # grid and work order of the grouped launches
     log(tune_multi.strip())
     torch.cuda.synchronize()
     t0 = time.perf_counter()
